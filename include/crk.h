@@ -600,8 +600,9 @@ crk_status crk_set_hsolve(crk_ctx *ctx, int32_t lanes, int32_t round, int32_t ca
                           double factor);
 
 /* Neighbour walk of crk_build_cells / crk_update_support (tuning only: the
- * neighbour sets do not depend on it): lanes (1, 2, 4, 8 or 16) of a
- * wavefront share one particle's walk; each row is first written to a
+ * rows do not depend on lanes): a wavefront walks for up to 8 consecutive
+ * particles at once, fewer for small sets, and for at most 64 / lanes of
+ * them (lanes 1, 2, 4, 8 or 16); each row is first written to a
  * scratch row of cap slots, and rows longer than cap are walked again into
  * place (0 keeps either value). After an eager build the next walk uses at
  * least 2.5 times that build's mean gather row and, where its longest gather

@@ -4,8 +4,8 @@
 // 1. validate + reduce H (deterministic two-level reduction)
 // 2. key = Morton code of the particle's cell; stable radix sort -> perm
 // 3. gather sorted x, y, z, H into one double4 per particle; cell ranges
-// 4. walk: a group of lanes per particle visits the cells of the hierarchy
-//    level matched to its support and finds the j with r^2 < H_i^2 (the
+// 4. walk: a wavefront takes a few consecutive particles, visits the cells of
+//    the hierarchy level matched to their supports and finds the j with r^2 < H_i^2 (the
 //    gather set, self excluded), and among them the j with r^2 >= H_j^2: j
 //    reaches i only through i's larger support, so the pair is an "extra"
 //    of j. Hits go to a capped scratch row, with exact counts.
@@ -217,93 +217,20 @@ __global__ __launch_bounds__(kBlock) void k_tables(const uint32_t *skey, int64_t
     }
 }
 
-// The cells of one particle's walk. CULL: the walked range lies within half
-// a period of i, so every particle of an (unwrapped) cell has its nearest
-// image in that cell's image: the separation is (x_i - x_j) + c with c in
-// {-L, 0, L} fixed per cell, the same two roundings the minimum-image rule
-// makes, and cells wholly outside the (slightly widened) support are
-// skipped. Otherwise each separation takes the minimum-image rule.
-template <int G, bool DIRECT, bool CULL>
-__device__ __forceinline__ void walk_row(const double4 *__restrict__ posH, int64_t i, const double4 &pi,
-                                         int l, int gshift, uint32_t below, const Levels &v,
-                                         const int32_t *__restrict__ cb, const int32_t *__restrict__ ce_,
-                                         int nck, int lx, int ly, int lz, int mx, int my, int mz,
-                                         double cs, double Hc2, int cap, uint32_t *row,
-                                         const int64_t *__restrict__ goff, int32_t *gidx,
-                                         int32_t *rcnt, const int64_t *__restrict__ eoff,
-                                         int32_t *efill, int32_t *etmp, int32_t &cg) {
-    const double H2 = pi.w * pi.w;
-    const double L = v.L;
-    for (int a = 0; a < mz; a++) {
-        const int kz = lz + a;
-        uint32_t mzb = spread3(wrapc(kz, nck)) << 2;
-        const double cz = kz < 0 ? L : (kz >= nck ? -L : 0.0);
-        const double gz = CULL ? cell_gap(pi.z, kz, cs) : 0.0;
-        const double gz2 = gz * gz;
-        for (int b = 0; b < my; b++) {
-            const int ky = ly + b;
-            uint32_t myb = mzb | (spread3(wrapc(ky, nck)) << 1);
-            const double cy = ky < 0 ? L : (ky >= nck ? -L : 0.0);
-            const double gy = CULL ? cell_gap(pi.y, ky, cs) : 0.0;
-            const double gzy = gz2 + gy * gy;
-            if (CULL && gzy > Hc2) continue;
-            for (int e = 0; e < mx; e++) {
-                const int kx = lx + e;
-                const double gx = CULL ? cell_gap(pi.x, kx, cs) : 0.0;
-                if (CULL && gzy + gx * gx > Hc2) continue;
-                const double cx = kx < 0 ? L : (kx >= nck ? -L : 0.0);
-                uint32_t id = myb | spread3(wrapc(kx, nck));
-                int jb = cb[id], je = ce_[id];
-                for (int j0 = jb; j0 < je; j0 += G) {
-                    int j = j0 + l;
-                    bool hit = false, extra = false;
-                    if (j < je) {
-                        double4 pj = posH[j];
-                        double dx, dy, dz;
-                        if (CULL) {
-                            dx = (pi.x - pj.x) + cx;
-                            dy = (pi.y - pj.y) + cy;
-                            dz = (pi.z - pj.z) + cz;
-                        } else {
-                            dx = min_image(pi.x - pj.x, v.L, v.hL);
-                            dy = min_image(pi.y - pj.y, v.L, v.hL);
-                            dz = min_image(pi.z - pj.z, v.L, v.hL);
-                        }
-                        double r2 = r2_exact(dx, dy, dz);
-                        hit = r2 < H2 && (int64_t)j != i;
-                        extra = hit && !(r2 < pj.w * pj.w);
-                    }
-                    uint32_t hm;
-                    if (G == 1) {
-                        hm = hit;
-                    } else {
-                        uint64_t mh = __ballot(hit);
-                        hm = (uint32_t)((mh >> gshift) & ((G == 64) ? ~0ull : (((uint64_t)1 << G) - 1)));
-                    }
-                    if (hit) {
-                        int pos = cg + (G == 1 ? 0 : __popc(hm & below));
-                        if (DIRECT) {
-                            gidx[goff[i] + pos] = j;
-                            if (extra) etmp[atomicAdd(&efill[j], 1)] = (int32_t)i;
-                        } else {
-                            if (pos < cap) row[pos] = (uint32_t)j | (extra ? 0x80000000u : 0u);
-                            if (extra) atomicAdd(&rcnt[j], 1);
-                        }
-                    }
-                    cg += __popc(hm);
-                }
-            }
-        }
-    }
-}
-
-// Flattened form of the same walk. The cells of a wavefront's groups hold
-// different numbers of particles, so a cell-by-cell loop keeps most lanes
-// idle; here a group first lists its non-empty, non-skipped cells as ranges
-// of sorted particles (in walk order, up to walk_ranges<G>() at a time, in
-// LDS, each with the code of its periodic image shift) and then takes the
-// concatenated candidates G at a time across cell boundaries. The candidate
-// order, hence every row, is the same as the cell-by-cell walk's.
+// The walk of one particle by a group of G lanes (the rows over the scratch
+// rows' slots; the first walk below shares a wavefront among several
+// particles). CULL: the walked range lies within half a period of i, so every
+// particle of an (unwrapped) cell has its nearest image in that cell's image:
+// the separation is (x_i - x_j) + c with c in {-L, 0, L} fixed per cell, the
+// same two roundings the minimum-image rule makes, and cells wholly outside
+// the (slightly widened) support are skipped. Otherwise each separation takes
+// the minimum-image rule.
+//
+// The group lists its non-empty, non-skipped cells as ranges of sorted
+// particles (in walk order: cells z-major, then y, then x; up to
+// walk_ranges<G>() at a time, in LDS, each with the code of its periodic image
+// shift) and then takes the concatenated candidates G at a time across cell
+// boundaries; a ballot over the group orders the hits as a serial walk would.
 //
 // The group first fills its axis tables (fill_axes); a listed cell then
 // costs three table reads, and its range carries the one-byte code of its
@@ -325,17 +252,16 @@ __device__ __forceinline__ void fill_shifts(double (*sh)[3], double L) {
     }
 }
 
-template <int G, bool DIRECT, bool CULL>
+template <int G, bool CULL>
 __device__ __forceinline__ void walk_row_flat(const double4 *__restrict__ posH, int64_t i,
                                               const double4 &pi, int l, int gshift, uint32_t below,
                                               const Levels &v, const int32_t *__restrict__ cb,
                                               const int32_t *__restrict__ ce_, int nck, int lx, int ly,
                                               int lz, int mx, int my, int mz, double cs, double Hc2,
-                                              int cap, uint32_t *row, const int64_t *__restrict__ goff,
-                                              int32_t *gidx, int32_t *rcnt,
-                                              const int64_t *__restrict__ eoff, int32_t *efill,
-                                              int32_t *etmp, int32_t &cg, int32_t *sb, int32_t *sc,
-                                              uint8_t *scode, AxisTab &tab, const double (*shifts)[3]) {
+                                              int64_t first, int32_t *gidx, int32_t *efill, int32_t *etmp,
+                                              int32_t *sb, int32_t *sc, uint8_t *scode, AxisTab &tab,
+                                              const double (*shifts)[3]) {
+    int32_t cg = 0;
     constexpr int NR = walk_ranges<G>();
     const double H2 = pi.w * pi.w;
     const int ncell = mx * my * mz;
@@ -409,14 +335,8 @@ __device__ __forceinline__ void walk_row_flat(const double4 *__restrict__ posH, 
             }
             const uint32_t hm = (uint32_t)((__ballot(hit) >> gshift) & (((uint64_t)1 << G) - 1));
             if (hit) {
-                const int pos = cg + __popc(hm & below);
-                if (DIRECT) {
-                    gidx[goff[i] + pos] = j;
-                    if (extra) etmp[atomicAdd(&efill[j], 1)] = (int32_t)i;
-                } else {
-                    if (pos < cap) row[pos] = (uint32_t)j | (extra ? 0x80000000u : 0u);
-                    if (extra) atomicAdd(&rcnt[j], 1);
-                }
+                gidx[first + cg + __popc(hm & below)] = j;
+                if (extra) etmp[atomicAdd(&efill[j], 1)] = (int32_t)i;
             }
             cg += __popc(hm);
         }
@@ -427,116 +347,457 @@ __device__ __forceinline__ void walk_row_flat(const double4 *__restrict__ posH, 
     }
 }
 
-// Single-pass walk of particle i by a group of G lanes of one wavefront:
-// the group visits i's cells in order and takes each cell's particles G at a
-// time (consecutive, so the loads coalesce). A ballot over the group orders
-// the hits exactly as a serial walk would, so row i is the same list for
-// every G. Row entries go to a per-particle scratch of `cap` slots, with bit
-// 31 marking the pairs that are extras of j; the returned count covers every
-// hit, so a row longer than cap is detected and walked again (DIRECT) into
-// its final place.
-// DIRECT = true is that second walk: it writes the gather row and the
-// extras straight to their final places.
-template <int G, bool DIRECT>
-__device__ __forceinline__ int32_t walk_one(const double4 *__restrict__ posH, int64_t i, int l,
-                                            const Levels &v, const int32_t *__restrict__ cbeg,
-                                            const int32_t *__restrict__ cend, int cap, uint32_t *scratch,
-                                            int32_t *rcnt, const int64_t *__restrict__ goff,
-                                            int32_t *gidx, const int64_t *__restrict__ eoff,
-                                            int32_t *efill, int32_t *etmp, int shift,
-                                            const double (*s_shift)[3]) {
-    const double4 pi = posH[i];
-    const int lane = threadIdx.x & 63;
-    const int gshift = lane - l;
-    const uint32_t below = (l == 0) ? 0u : ((1u << l) - 1u);
-    int32_t cg = 0;
-    uint32_t *row = DIRECT ? nullptr : scratch + (size_t)i * cap;
-    int k = level_for(pi.w * (double)(1 << shift), v);
-    int nck = 1 << (v.bits - k);
-    Grid g{v.L, v.hL, (double)nck / v.L, v.margin, nck};
-    int lx, ly, lz, mx, my, mz;
-    axis_range(pi.x, pi.w, g, lx, mx);
-    axis_range(pi.y, pi.w, g, ly, my);
-    axis_range(pi.z, pi.w, g, lz, mz);
-    const int64_t base = box_base(v, i) + v.off[k];
-    const int32_t *cb = cbeg + base, *ce_ = cend + base;
-    // the support widened by twice the axis margin (far above any rounding)
-    const double cs = v.L / (double)nck;
-    const double Hc = pi.w + 2.0 * v.margin;
-    const bool cull = 2.0 * (Hc + cs) < v.L;
-    bool done = false;
-    if constexpr (G >= 4) {
-        // the flattened walk (narrower groups would need too much LDS for
-        // their range lists, and walk cell by cell)
-        if (mx <= kAxisCells && my <= kAxisCells && mz <= kAxisCells) {
-            constexpr int NG = kBlock / G;
-            constexpr int NR = walk_ranges<G>();
-            __shared__ int32_t s_b[NG][NR], s_c[NG][NR + 1];
-            __shared__ uint8_t s_code[NG][NR];
-            __shared__ AxisTab s_ax[NG];
-            const int grp = threadIdx.x / G;
-            if (cull)
-                walk_row_flat<G, DIRECT, true>(posH, i, pi, l, gshift, below, v, cb, ce_, nck, lx, ly, lz,
-                                               mx, my, mz, cs, Hc * Hc, cap, row, goff, gidx, rcnt, eoff,
-                                               efill, etmp, cg, s_b[grp], s_c[grp], s_code[grp], s_ax[grp],
-                                               s_shift);
-            else
-                walk_row_flat<G, DIRECT, false>(posH, i, pi, l, gshift, below, v, cb, ce_, nck, lx, ly, lz,
-                                                mx, my, mz, cs, INFINITY, cap, row, goff, gidx, rcnt, eoff,
-                                                efill, etmp, cg, s_b[grp], s_c[grp], s_code[grp], s_ax[grp],
-                                                s_shift);
-            done = true;
-        }
-    }
-    if (done) {
-    } else if (cull) {
-        walk_row<G, DIRECT, true>(posH, i, pi, l, gshift, below, v, cb, ce_, nck, lx, ly, lz, mx, my,
-                                  mz, cs, Hc * Hc, cap, row, goff, gidx, rcnt, eoff, efill, etmp, cg);
-    } else {
-        walk_row<G, DIRECT, false>(posH, i, pi, l, gshift, below, v, cb, ce_, nck, lx, ly, lz, mx, my,
-                                   mz, cs, INFINITY, cap, row, goff, gidx, rcnt, eoff, efill, etmp, cg);
-    }
-    return cg;
+// ---- the first walk: a wavefront per P consecutive particles
+//
+// Consecutive particles of the sort lie next to one another, so the cells
+// about one of them are mostly the cells about all of them. The wavefront
+// takes its particles in runs (see walk_run) and lists the cells about the
+// whole run once, 64 cells a step; the concatenated candidates of those cells
+// then go 64 at a time, one per lane, past every particle of the run, whose
+// position and squared support sit in scalar registers. A candidate is loaded
+// and located once for P tests, and a test is the separation, r^2, two
+// compares and the ballot that places the hits.
+//
+// A run's cells are visited in the order of a single particle's walk (z-major,
+// then y, then x, particles ascending within a cell, at the same level), and
+// the cells that only other particles of the run need hold no hit of this one:
+// every row is the list a walk of its own gives, entry for entry.
+//
+// Bound: vector instruction issue (about three quarters of the time), then the
+// latency of a batch; eight wavefronts per SIMD hide it, hence the register
+// bound. A lognormal box of 128^3 (67 gather partners a particle): a group of
+// lanes per particle tested 218 candidates each for 400 vector instructions a
+// particle and 1.67 ms; here 370 candidates a particle pass for 255, 1.21 ms
+// (64^3: 0.355 to 0.18 ms). Of that, listing only cells in reach of some
+// particle of the run took 540 candidates to 370 (1.51 to 1.39 ms), finding a
+// candidate's range from head bits instead of a bisection 70 of 105
+// instructions a batch (to 1.25 ms), and rows gathered in LDS a wait for their
+// stores in every batch (to 1.21 ms).
+
+// cells a run's list may cover, and along one axis at most kAxisCells
+constexpr int kRunCells = 216;
+// ranges listed at a time
+constexpr int kRunRanges = 128;
+// 64-candidate batches whose ranges are found by counting head bits
+constexpr int kHeadWords = 32;
+
+// inclusive sum over the 64 lanes (DPP row shifts, then the row broadcasts)
+__device__ __forceinline__ int wave_incl_scan(int x) {
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, true);   // row_shr 1
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, true);   // row_shr 2
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, true);   // row_shr 4
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, true);   // row_shr 8
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false);  // row_bcast 15
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false);  // row_bcast 31
+    return x;
 }
 
-// First walk (DIRECT = false): one group per particle; ng[i] gets the full
-// count. Second walk (DIRECT = true): a grid of any size whose groups take
-// the particles that compaction listed in longs (rows past cap; longs[0]
-// counts them, the list follows) in turn, so it costs nothing when no row
-// is long.
-template <int G, bool DIRECT>
-__global__ __launch_bounds__(kBlock) void k_walk_scratch(const double4 *__restrict__ posH, int64_t n,
-                                                         Levels v, const int32_t *__restrict__ cbeg,
-                                                         const int32_t *__restrict__ cend, int cap,
-                                                         uint32_t *scratch, int32_t *ng, int32_t *rcnt,
-                                                         const int64_t *__restrict__ goff, int32_t *gidx,
-                                                         const int64_t *__restrict__ eoff, int32_t *efill,
-                                                         int32_t *etmp, int shift, int32_t *longs) {
-    // the shift table first: every wave of the block is still running
+__device__ __forceinline__ double readlane_f64(double x, int lane) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), lane),
+                            __builtin_amdgcn_readlane(__double2loint(x), lane));
+}
+
+// hits of a row kept in LDS until the wavefront's walk ends (rows seldom
+// outgrow them; what does goes straight to the scratch row)
+template <int P>
+constexpr int kRowSlots = P == 8 ? 96 : P == 4 ? 160 : P == 2 ? 256 : 512;
+
+// LDS of one wavefront of the walk
+template <int P>
+struct RunLds {
+    uint32_t row[P][kRowSlots<P>];
+    // squared gap along each axis from particle p to cell e, in cell sides;
+    // along x less p's squared support, so that a sum <= 0 means in reach
+    __align__(16) float g2[3][kAxisCells][P < 4 ? 4 : P];
+    uint64_t head[kHeadWords];                  // bit f set: a range starts at candidate f
+    int32_t b[kRunRanges], c[kRunRanges];       // first particle, offset in the concatenation
+    uint32_t id[3][kAxisCells];                 // Morton bits and image code, as AxisTab
+    uint8_t code[kRunRanges];                   // image shift code
+};
+
+// how a run's separations are formed: one image shift per listed cell, all of
+// them zero or not, or the minimum-image rule
+enum { kNoShift = 0, kShift = 1, kMinImage = 2 };
+
+// one batch of 64 candidates (j, its position and support, in lane order)
+// past the wavefront's particles whose bits are set in run; returns how many
+// of them the lane's candidate is an extra of
+template <int P, int MODE>
+__device__ __forceinline__ uint32_t walk_batch(RunLds<P> &s, const double (&X)[P], const double (&Y)[P],
+                                               const double (&Z)[P], const double (&H2)[P], uint32_t (&at)[P],
+                                               int run, int32_t i0, int32_t j, const double4 &pj, double sx,
+                                               double sy, double sz, double L, double hL, int cap,
+                                               uint32_t *rows) {
+    const double hj2 = pj.w * pj.w;
+    uint32_t ne = 0;
+    // opaque copies, so that what follows from them per particle is formed
+    // anew in each batch: held across the batches it would push the
+    // particles' positions out of the scalar registers
+    asm volatile("" : "+s"(run), "+s"(cap), "+s"(i0));
+    // a batch that holds one of the wavefront's own particles
+    const uint64_t own = __builtin_amdgcn_ballot_w64((uint32_t)(j - i0) < (uint32_t)P);
+#pragma unroll
+    for (int p = 0; p < P; p++) {
+        if (!(run >> p & 1)) continue;   // uniform
+        double dx, dy, dz;
+        if (MODE == kMinImage) {
+            dx = min_image(X[p] - pj.x, L, hL);
+            dy = min_image(Y[p] - pj.y, L, hL);
+            dz = min_image(Z[p] - pj.z, L, hL);
+        } else {
+            dx = X[p] - pj.x;
+            dy = Y[p] - pj.y;
+            dz = Z[p] - pj.z;
+            if (MODE == kShift) {
+                dx += sx;
+                dy += sy;
+                dz += sz;
+            }
+        }
+        const double r2 = r2_exact(dx, dy, dz);
+        uint64_t hm = __builtin_amdgcn_ballot_w64(r2 < H2[p]);
+        if (own != 0) hm &= ~__builtin_amdgcn_ballot_w64(j == i0 + p);   // uniform
+        if (hm == 0) continue;                                          // uniform
+        const uint32_t end = at[p] + __popcll(hm);
+        if (__builtin_amdgcn_inverse_ballot_w64(hm)) {
+            const uint32_t e = r2 < hj2 ? 0u : 1u, w = (e << 31) | (uint32_t)j;
+            const uint32_t k = __builtin_amdgcn_mbcnt_hi((uint32_t)(hm >> 32),
+                                                         __builtin_amdgcn_mbcnt_lo((uint32_t)hm, at[p]));
+            if (end <= (uint32_t)kRowSlots<P>) {   // uniform
+                s.row[p][k] = w;
+            } else if (k < (uint32_t)kRowSlots<P>) {
+                s.row[p][k] = w;
+            } else if (k < (uint32_t)cap) {
+                rows[(uint32_t)(p * cap) + k] = w;
+            }
+            ne += e;
+        }
+        at[p] = end;
+    }
+    return ne;
+}
+
+// The candidates of the nr listed ranges (cum of them), 64 at a time; the
+// next batch's positions load while this one is tested. Loads, stores and
+// atomics of a wavefront complete in order, so a wait for the positions is a
+// wait for all that was issued before it: hits gather in LDS, and the extras
+// of a batch are counted only after the next positions have arrived.
+template <int P, int MODE>
+__device__ __forceinline__ void walk_list(const double4 *__restrict__ posH, RunLds<P> &s, int nr, int cum,
+                                          int lane, const double (&X)[P], const double (&Y)[P],
+                                          const double (&Z)[P], const double (&H2)[P], uint32_t (&at)[P],
+                                          int run, int32_t i0, double L, double hL, int cap,
+                                          uint32_t *rows, int32_t *rcnt, const double (*shifts)[3]) {
+    const int top = nr > 1 ? 1 << (31 - __builtin_clz(nr - 1)) : 0;   // largest power of two below nr
+    int before = -1;   // range of the candidate before the batch
+    auto fetch = [&](int f0, int32_t &j, double4 &pj, int &code) {
+        const int f = f0 + lane;
+        int r = 0;
+        if (f0 < 64 * kHeadWords) {
+            // the ranges that start at or before this lane's candidate
+            const uint64_t hd = s.head[f0 >> 6];
+            const uint32_t h0 = __builtin_amdgcn_readfirstlane((uint32_t)hd),
+                           h1 = __builtin_amdgcn_readfirstlane((uint32_t)(hd >> 32));
+            r = before + (int)(h0 & 1u) +
+                (int)__builtin_amdgcn_mbcnt_hi(h1 >> 1, __builtin_amdgcn_mbcnt_lo(h0 >> 1 | h1 << 31, 0u));
+            before += __popc(h0) + __popc(h1);
+        } else {
+            for (int t = top; t > 0; t >>= 1)
+                if (r + t < nr && s.c[r + t] <= f) r += t;
+        }
+        j = -1;
+        code = 0;
+        // past the end: at infinity, so no test hits
+        pj = make_double4(INFINITY, INFINITY, INFINITY, 0.0);
+        if (f < cum) {
+            j = s.b[r] + (f - s.c[r]);
+            if (MODE == kShift) code = s.code[r];
+            pj = posH[(uint32_t)j];
+        }
+    };
+    int32_t jn, jp = 0;
+    uint32_t ne = 0;
+    double4 pn;
+    int cn;
+    fetch(0, jn, pn, cn);
+    for (int f0 = 0; f0 < cum; f0 += 64) {
+        const int32_t j = jn;
+        const double4 pj = pn;
+        double sx = 0.0, sy = 0.0, sz = 0.0;
+        if (MODE == kShift) {
+            sx = shifts[cn][0];
+            sy = shifts[cn][1];
+            sz = shifts[cn][2];
+        }
+        __builtin_amdgcn_s_waitcnt(0x0F70);   // the positions are here
+        __builtin_amdgcn_sched_barrier(0);
+        if (ne) atomicAdd(&rcnt[jp], (int)ne);
+        if (f0 + 64 < cum) fetch(f0 + 64, jn, pn, cn);
+        ne = walk_batch<P, MODE>(s, X, Y, Z, H2, at, run, i0, j, pj, sx, sy, sz, L, hL, cap, rows);
+        jp = j;
+    }
+    if (ne) atomicAdd(&rcnt[jp], (int)ne);
+}
+
+template <int P>
+__global__ __launch_bounds__(kBlock, P == 8 ? 7 : 8) void k_walk(const double4 *__restrict__ posH, int64_t n, Levels v,
+                                                 const int32_t *__restrict__ cbeg,
+                                                 const int32_t *__restrict__ cend, int cap, uint32_t *scratch,
+                                                 int32_t *ng, int32_t *rcnt, int shift) {
+    static_assert(P <= 8, "the axis tables hold eight particles");
     __shared__ double s_shift[27][3];
+    __shared__ RunLds<P> s_run[kBlock / 64];
     fill_shifts(s_shift, v.L);
     __syncthreads();
-    // the first walk maps blocks to XCDs in contiguous runs of particles; the
-    // list of the second is short, so its blocks go round the XCDs in order
-    const int64_t gid = (DIRECT ? (int64_t)blockIdx.x : xcd_block(blockIdx.x, gridDim.x)) * kBlock + threadIdx.x;
-    const int l = (int)(gid % G);
-    if constexpr (!DIRECT) {
-        const int64_t i = gid / G;
-        if (i >= n) return;   // whole groups leave together (G divides the block)
-        const int32_t cg = walk_one<G, false>(posH, i, l, v, cbeg, cend, cap, scratch, rcnt, goff, gidx,
-                                              eoff, efill, etmp, shift, s_shift);
-        if (l == 0) ng[i] = cg;
-    } else {
-        const int64_t nl = longs[0];
-        const int64_t stride = (int64_t)gridDim.x * (kBlock / G);
-        for (int64_t t = gid / G; t < nl; t += stride) {
-            const int64_t i = longs[1 + t];
-            // a recorded step whose lists overflowed their capacities has
-            // its counts cleared: then nothing is written
-            if (ng[i] <= cap) continue;
-            walk_one<G, true>(posH, i, l, v, cbeg, cend, cap, scratch, rcnt, goff, gidx, eoff, efill, etmp,
-                              shift, s_shift);
+    const int lane = threadIdx.x & 63;
+    // the wavefront's number and all that follows from it in scalar registers
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t i0 = (xcd_block(blockIdx.x, gridDim.x) * (kBlock / 64) + wave) * (int64_t)P;
+    if (i0 >= n) return;   // whole waves leave together
+    RunLds<P> &s = s_run[wave];
+    const int np = (int)(n - i0 < P ? n - i0 : P);
+    // lane p holds particle p's walk (lanes past the last repeat it)
+    const int64_t il = i0 + (lane < np ? lane : np - 1);
+    const double4 pl = posH[il];
+    const int kl = level_for(pl.w * (double)(1 << shift), v);
+    const int bl = (int)(v.skey[il] >> (3 * v.bits));
+    // cells of the walk per axis, first + 1024 above the end + 1024; the level
+    // with the culling flag above it
+    uint32_t rg[3], kc_;
+    {
+        const int nck = 1 << (v.bits - kl);
+        const Grid g{v.L, v.hL, (double)nck / v.L, v.margin, nck};
+        int lo, cnt;
+        axis_range(pl.x, pl.w, g, lo, cnt);
+        rg[0] = (uint32_t)(lo + 1024) << 16 | (uint32_t)(lo + cnt + 1024);
+        axis_range(pl.y, pl.w, g, lo, cnt);
+        rg[1] = (uint32_t)(lo + 1024) << 16 | (uint32_t)(lo + cnt + 1024);
+        axis_range(pl.z, pl.w, g, lo, cnt);
+        rg[2] = (uint32_t)(lo + 1024) << 16 | (uint32_t)(lo + cnt + 1024);
+        // the support widened by twice the axis margin (far above any rounding)
+        kc_ = (uint32_t)kl | (2.0 * ((pl.w + 2.0 * v.margin) + v.L / (double)nck) < v.L ? 256u : 0u);
+    }
+    double X[P], Y[P], Z[P], H2[P];
+    uint32_t at[P];   // hits of each particle so far
+    const double hl2 = pl.w * pl.w;
+#pragma unroll
+    for (int p = 0; p < P; p++) {
+        const double4 q = posH[i0 + (p < np ? p : np - 1)];   // uniform: scalar loads
+        X[p] = q.x;
+        Y[p] = q.y;
+        Z[p] = q.z;
+        H2[p] = readlane_f64(hl2, p);
+        at[p] = 0;
+    }
+    // particle lane & 7 for the axis tables
+    const double px = __shfl(pl.x, lane & 7, 64), py = __shfl(pl.y, lane & 7, 64),
+                 pz = __shfl(pl.z, lane & 7, 64), ph = __shfl(pl.w, lane & 7, 64);
+    uint32_t *rows = scratch + (size_t)i0 * cap;
+    for (int p0 = 0; p0 < np;) {
+        // the run p0 .. p1-1: particles of one box and one level whose cells
+        // together stay a small block (a step of the sort along the curve can
+        // be long; the next run starts there). Without culling the wrapped
+        // range decides the order, so it has to be the same for all.
+        const uint32_t kc = __builtin_amdgcn_readlane(kc_, p0);
+        const int k = (int)(kc & 255u), cull = (int)(kc >> 8), bx = __builtin_amdgcn_readlane(bl, p0);
+        int ul[3], uh[3];
+#pragma unroll
+        for (int a = 0; a < 3; a++) {
+            const uint32_t r = __builtin_amdgcn_readlane(rg[a], p0);
+            ul[a] = (int)(r >> 16);
+            uh[a] = (int)(r & 0xffffu);
         }
+        int p1 = p0 + 1;
+        while (p1 < np) {
+            bool ok = __builtin_amdgcn_readlane(kc_, p1) == kc && __builtin_amdgcn_readlane(bl, p1) == bx;
+            int nl[3], nh[3], cells = 1;
+#pragma unroll
+            for (int a = 0; a < 3; a++) {
+                const uint32_t r = __builtin_amdgcn_readlane(rg[a], p1);
+                const int l1 = (int)(r >> 16), h1 = (int)(r & 0xffffu);
+                nl[a] = l1 < ul[a] ? l1 : ul[a];
+                nh[a] = h1 > uh[a] ? h1 : uh[a];
+                if (!cull) ok = ok && l1 == ul[a] && h1 == uh[a];
+                ok = ok && nh[a] - nl[a] <= kAxisCells;
+                cells *= nh[a] - nl[a];
+            }
+            if (!ok || cells > kRunCells) break;
+#pragma unroll
+            for (int a = 0; a < 3; a++) {
+                ul[a] = nl[a];
+                uh[a] = nh[a];
+            }
+            p1++;
+        }
+#pragma unroll
+        for (int a = 0; a < 3; a++) {
+            ul[a] -= 1024;
+            uh[a] -= 1024;
+        }
+        const int nck = 1 << (v.bits - k);
+        const double cs = v.L / (double)nck;
+        const int mx = uh[0] - ul[0], my = uh[1] - ul[1], mz = uh[2] - ul[2];
+        const int ncell = mx * my * mz;
+        // axis tables: Morton bits and image code of each cell along an axis;
+        // per particle of the run the gap to it, in FP32 with a margin far
+        // above its rounding (a cell is listed when it is in reach of any)
+        const double ics = (double)nck / v.L;
+        if (lane < 3 * kAxisCells) {
+            const int a = lane / kAxisCells, e = lane % kAxisCells;
+            const int kc = (a == 0 ? ul[0] : a == 1 ? ul[1] : ul[2]) + e;
+            const int code = !cull ? 0 : kc < 0 ? 1 : (kc >= nck ? 2 : 0);
+            s.id[a][e] = (spread3(wrapc(kc, nck)) << a) | ((uint32_t)code << 30);
+        }
+        {
+            const int e = lane >> 3, p = lane & 7;   // (lanes past P hold no particle)
+            const bool in = p >= p0 && p < p1;
+            float reach = in ? 1e30f : -1e30f;
+            if (cull && in) {
+                const float h = (float)((ph + 2.0 * v.margin) * ics);
+                reach = h * h * 1.00001f + 1e-5f;
+            }
+#pragma unroll
+            for (int a = 0; a < 3; a++) {
+                // the particle from the run's first cell, in cell sides
+                const float t = (float)((a == 0 ? px : a == 1 ? py : pz) * ics - (double)ul[a]);
+                const float g = fmaxf(0.0f, fmaxf((float)e - t, t - (float)(e + 1)));
+                if (p < P) s.g2[a][e][p] = (cull ? g * g : 0.0f) - (a == 0 ? reach : 0.0f);
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        const int32_t *cb = cbeg + (int64_t)bx * v.box_stride + v.off[k];
+        const int32_t *ce = cend + (int64_t)bx * v.box_stride + v.off[k];
+        const uint32_t dvx = div16(mx), dvy = div16(my);
+        const int run = (1 << p1) - (1 << p0);
+        for (int c0 = 0; c0 < ncell;) {
+            int nr = 0, cum = 0;
+            uint64_t shifted = 0;
+            if (lane < kHeadWords) s.head[lane] = 0;
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            while (c0 < ncell && nr + 64 <= kRunRanges) {
+                const int cidx = c0 + lane;
+                int jb = 0, len = 0, code = 0;
+                if (cidx < ncell) {
+                    const int t = (int)(((uint32_t)cidx * dvx) >> 16);
+                    const int e = cidx - t * mx;
+                    const int a = (int)(((uint32_t)t * dvy) >> 16);
+                    const int b = t - a * my;
+                    float near = INFINITY;
+#pragma unroll
+                    for (int p = 0; p < P; p++)
+                        near = fminf(near, (s.g2[2][a][p] + s.g2[1][b][p]) + s.g2[0][e][p]);
+                    if (near <= 0.0f) {
+                        const uint32_t ix = s.id[0][e], iy = s.id[1][b], iz = s.id[2][a];
+                        const uint32_t id = (ix | iy | iz) & 0x3fffffffu;
+                        code = (int)(ix >> 30) + 3 * (int)(iy >> 30) + 9 * (int)(iz >> 30);
+                        jb = cb[id];
+                        len = ce[id] - jb;
+                    }
+                }
+                const int inc = wave_incl_scan(len);
+                const uint64_t hmk = __builtin_amdgcn_ballot_w64(len > 0);
+                if (len > 0) {
+                    const int pos = nr + (int)__builtin_amdgcn_mbcnt_hi(
+                                             (uint32_t)(hmk >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)hmk, 0u));
+                    s.b[pos] = jb;
+                    s.c[pos] = cum + (inc - len);
+                    s.code[pos] = (uint8_t)code;
+                    const int f = cum + (inc - len);
+                    if (f < 64 * kHeadWords) atomicOr((uint32_t *)s.head + (f >> 5), 1u << (f & 31));
+                }
+                shifted |= __builtin_amdgcn_ballot_w64(len > 0 && code != 0);
+                nr += __popcll(hmk);
+                cum += __builtin_amdgcn_readlane(inc, 63);
+                c0 += 64;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            if (!cull)
+                walk_list<P, kMinImage>(posH, s, nr, cum, lane, X, Y, Z, H2, at, run, (int32_t)i0, v.L, v.hL,
+                                        cap, rows, rcnt, s_shift);
+            else if (shifted)
+                walk_list<P, kShift>(posH, s, nr, cum, lane, X, Y, Z, H2, at, run, (int32_t)i0, v.L, v.hL, cap,
+                                     rows, rcnt, s_shift);
+            else
+                walk_list<P, kNoShift>(posH, s, nr, cum, lane, X, Y, Z, H2, at, run, (int32_t)i0, v.L, v.hL,
+                                       cap, rows, rcnt, s_shift);
+            // the list is rewritten only after every lane read it
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        }
+        p0 = p1;
+    }
+    // the rows leave LDS 64 entries a store
+#pragma unroll
+    for (int p = 0; p < P; p++) {
+        uint32_t m = at[p] < (uint32_t)kRowSlots<P> ? at[p] : (uint32_t)kRowSlots<P>;
+        m = m < (uint32_t)cap ? m : (uint32_t)cap;
+        for (uint32_t k = lane; k < m; k += 64) rows[(uint32_t)(p * cap) + k] = s.row[p][k];
+    }
+    int cnt = 0;
+#pragma unroll
+    for (int p = 0; p < P; p++)
+        if (lane == p) cnt = (int)at[p];
+    if (lane < np) ng[i0 + lane] = cnt;
+}
+
+// The rows past the scratch rows' slots, walked again straight into place
+// (gather row and extras): a grid of any size whose groups of G lanes take the
+// particles that compaction listed in longs (longs[0] counts them, the list
+// follows) in turn, so it costs nothing when no row is long. The list is short,
+// so the blocks go round the XCDs in order.
+template <int G>
+__global__ __launch_bounds__(kBlock) void k_walk_long(const double4 *__restrict__ posH, Levels v,
+                                                      const int32_t *__restrict__ cbeg,
+                                                      const int32_t *__restrict__ cend, int cap,
+                                                      const int32_t *__restrict__ ng,
+                                                      const int64_t *__restrict__ goff, int32_t *gidx,
+                                                      int32_t *efill, int32_t *etmp, int shift,
+                                                      const int32_t *__restrict__ longs) {
+    // the shift table first: every wave of the block is still running
+    constexpr int NG = kBlock / G, NR = walk_ranges<G>();
+    __shared__ double s_shift[27][3];
+    __shared__ int32_t s_b[NG][NR], s_c[NG][NR + 1];
+    __shared__ uint8_t s_code[NG][NR];
+    __shared__ AxisTab s_ax[NG];
+    fill_shifts(s_shift, v.L);
+    __syncthreads();
+    const int l = threadIdx.x % G, grp = threadIdx.x / G;
+    const int gshift = (threadIdx.x & 63) - l;
+    const uint32_t below = l == 0 ? 0u : (1u << l) - 1u;
+    const int64_t nl = longs[0];
+    const int64_t stride = (int64_t)gridDim.x * NG;
+    for (int64_t t = (int64_t)blockIdx.x * NG + grp; t < nl; t += stride) {
+        const int64_t i = longs[1 + t];
+        // a recorded step whose lists overflowed their capacities has its
+        // counts cleared: then nothing is written
+        if (ng[i] <= cap) continue;
+        const double4 pi = posH[i];
+        const int k = level_for(pi.w * (double)(1 << shift), v);
+        const int nck = 1 << (v.bits - k);
+        const Grid g{v.L, v.hL, (double)nck / v.L, v.margin, nck};
+        int lx, ly, lz, mx, my, mz;
+        axis_range(pi.x, pi.w, g, lx, mx);
+        axis_range(pi.y, pi.w, g, ly, my);
+        axis_range(pi.z, pi.w, g, lz, mz);
+        const int64_t base = box_base(v, i) + v.off[k];
+        // the support widened by twice the axis margin (far above any rounding)
+        const double cs = v.L / (double)nck;
+        const double Hc = pi.w + 2.0 * v.margin;
+        if (2.0 * (Hc + cs) < v.L)
+            walk_row_flat<G, true>(posH, i, pi, l, gshift, below, v, cbeg + base, cend + base, nck, lx, ly, lz,
+                                   mx, my, mz, cs, Hc * Hc, goff[i], gidx, efill, etmp, s_b[grp], s_c[grp],
+                                   s_code[grp], s_ax[grp], s_shift);
+        else
+            walk_row_flat<G, false>(posH, i, pi, l, gshift, below, v, cbeg + base, cend + base, nck, lx, ly, lz,
+                                    mx, my, mz, cs, INFINITY, goff[i], gidx, efill, etmp, s_b[grp], s_c[grp],
+                                    s_code[grp], s_ax[grp], s_shift);
     }
 }
 
@@ -819,6 +1080,20 @@ Levels levels(const crk_ctx *c) {
     return v;
 }
 
+// Particles per wavefront of the walk. More of them share a listed cell and a
+// loaded candidate, fewer leave more wavefronts: the device holds 8192 at
+// eight per SIMD, and a wavefront of four particles is worth its half as many
+// once it fills that (32^3: 28 us with four, 32 with two and 37 with one;
+// 20^3: 57, 45 and 40), one of eight once there are 16 rounds of them, so that
+// the last round is a small part (128^3: 1.21 ms with eight, 1.25 with four;
+// 64^3: 0.19 and 0.18). The lanes per particle that were asked for bound it.
+static int walk_particles(int64_t n, int lanes) {
+    const int most = 64 / lanes < 8 ? 64 / lanes : 8;
+    int P = n >= (int64_t)8 * 16 * 8192 ? 8 : 4;
+    while (P > 1 && (P > most || (P < 8 && n < (int64_t)P * 8192))) P /= 2;
+    return P;
+}
+
 // Neighbour lists for the current posH / cell tables.
 static crk_status build_lists(crk_ctx *c) {
     int64_t n = c->n;
@@ -847,15 +1122,13 @@ static crk_status build_lists(crk_ctx *c) {
     k_fill_i32<<<1, kBlock, 0, c->stream>>>(longs, 1, 0);
     {
         KTimer kt_(c, "k_walk");
-        int G = c->G_walk;
-#define L_WALK(GG) k_walk_scratch<GG, false><<<(unsigned)((n * GG + kBlock - 1) / kBlock), kBlock, 0, c->stream>>>(posH, n, v, cbeg, cend, cap, scratch, ng, ecnt, nullptr, nullptr, nullptr, nullptr, nullptr, c->walk_shift, longs)
-        switch (G) {
+        const int P = walk_particles(n, c->G_walk);
+#define L_WALK(PP) k_walk<PP><<<(unsigned)(((n + PP - 1) / PP + kBlock / 64 - 1) / (kBlock / 64)), kBlock, 0, c->stream>>>(posH, n, v, cbeg, cend, cap, scratch, ng, ecnt, c->walk_shift)
+        switch (P) {
             case 1: L_WALK(1); break;
             case 2: L_WALK(2); break;
             case 4: L_WALK(4); break;
-            case 8: L_WALK(8); break;
-            case 16: L_WALK(16); break;
-            default: return set_err(c, CRK_ERR_INVALID_ARG, "walk lanes must be 1, 2, 4, 8 or 16");
+            default: L_WALK(8); break;
         }
 #undef L_WALK
     }
@@ -914,9 +1187,8 @@ static crk_status build_lists(crk_ctx *c) {
         KTimer kt_(c, "k_walk_long");
         constexpr int GL = 32;
         const unsigned nb = (unsigned)std::min<int64_t>((n * GL + kBlock - 1) / kBlock, 4096);
-        k_walk_scratch<GL, true><<<nb, kBlock, 0, c->stream>>>(
-            posH, n, v, cbeg, cend, cap, nullptr, ng, nullptr, goff, (int32_t *)c->gidx.p, eoff, efill,
-            etmp, c->walk_shift, longs);
+        k_walk_long<GL><<<nb, kBlock, 0, c->stream>>>(posH, v, cbeg, cend, cap, ng, goff,
+                                                      (int32_t *)c->gidx.p, efill, etmp, c->walk_shift, longs);
     }
     CRK_HIP(c, hipGetLastError());
     if (vol) {

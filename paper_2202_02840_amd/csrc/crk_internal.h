@@ -352,15 +352,14 @@ __device__ __forceinline__ uint32_t morton3(uint32_t x, uint32_t y, uint32_t z) 
 }
 
 // level whose cell side is at least R/2 (so at most five cells a side cover
-// the support), capped at the single-cell level
+// the support), capped at the single-cell level: the smallest k >= 0 with
+// c0 2^k >= R/2, from the exponents and one exact comparison
 __device__ __forceinline__ int level_for(double R, const Levels &v) {
-    int k = 0;
-    double c = v.c0;
-    while (k < v.bits && c < 0.5 * R) {
-        c *= 2.0;
-        k++;
-    }
-    return k;
+    const double h = 0.5 * R;
+    int k = __builtin_amdgcn_frexp_exp(h) - __builtin_amdgcn_frexp_exp(v.c0);
+    k = k < 0 ? 0 : k;
+    if (ldexp(v.c0, k) < h) k++;
+    return k < v.bits ? k : v.bits;
 }
 
 // scratch row slots for gather rows of g entries in all over n particles:
