@@ -151,6 +151,86 @@ __device__ __forceinline__ int64_t group_index(int G, int &lane) {
     return gid / G;
 }
 
+// Partner records on their way to registers. A lane that loads its partner's
+// record itself reads CH 16-byte pieces, each from a cache line that no other
+// lane of the load touches, and the vector L1 serves one line after another:
+// that path was busy 98% of the derivative pass. Here CH lanes fetch one
+// record together, whole lines at a time, for each of their CH records in
+// turn, straight into LDS (nothing passes through registers, so the next
+// records are on their way while this one is worked on), and every lane then
+// reads its own record from there. The records of the groups' lanes s lie
+// kStep bytes after those of their lanes s - 1: 1024 that one load fills and
+// 16 more, so that consecutive lanes read from different banks.
+//
+// Derivative pass, 128^3 lognormal, 1.70e8 pairs: 1.69 ms with a load of its
+// own for each piece (L1 accesses 1.67e9), 1.375 ms here (6.4e8), now bound by
+// vector instruction issue (about 90% of the time); in FP64 at 64^3 0.452 to
+// 0.399 ms; 268 neighbours at 45^3 0.335 to 0.245 ms. The compatible pass of
+// two kicks, 50^3 lattice: 0.110 to 0.092 ms (three wavefronts a SIMD: a
+// register bound for four spills, and a spill's reload waits for every record
+// on its way: 0.170 ms).
+template <int CH>
+struct Staged {
+    static constexpr int kStep = 1024 + 16;
+    __align__(16) char rec[CH * kStep];   // 64 records
+    __align__(16) int32_t j[64];
+};
+
+// start the loads of every lane's record j; wide: the records take 4 GiB or
+// more, so that an offset needs 64 bits
+template <int CH>
+__device__ __forceinline__ void stage_load(const void *__restrict__ rec, bool wide, Staged<CH> &st, int32_t j,
+                                           int lane) {
+    using Global = const __attribute__((address_space(1))) void *;
+    using Lds = __attribute__((address_space(3))) void *;
+    st.j[lane] = j;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    const int c = lane & (CH - 1);
+    const int32_t *js = st.j + (lane - c);
+    if (wide) {   // uniform
+#pragma unroll 1
+        for (int s = 0; s < CH; s++) {
+            const char *src = (const char *)rec + ((size_t)(uint32_t)js[s] * (CH * 16) + (size_t)(c << 4));
+            // the reads of the last records are done before a piece arrives
+            __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0)
+            __builtin_amdgcn_global_load_lds((Global)src, (Lds)(st.rec + s * Staged<CH>::kStep), 16, 0, 0);
+        }
+        return;
+    }
+    uint32_t off[CH];
+#pragma unroll
+    for (int s = 0; s < CH; s++) off[s] = (uint32_t)js[s] * (CH * 16) + (uint32_t)(c << 4);
+    // the reads of the last records and of the indices are done before the
+    // first piece arrives
+    __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0)
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int s = 0; s < CH; s++)
+        __builtin_amdgcn_global_load_lds((Global)((const char *)rec + off[s]), (Lds)(st.rec + s * Staged<CH>::kStep), 16, 0, 0);
+}
+
+// wait for the loads
+__device__ __forceinline__ void stage_wait() {
+    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// 16-byte piece k of this lane's record
+template <int CH>
+__device__ __forceinline__ float4 stage_piece(const Staged<CH> &st, int lane, int k) {
+    const int c = lane & (CH - 1);
+    return *(const float4 *)(st.rec + (c * Staged<CH>::kStep + (lane - c) * 16) + 16 * k);
+}
+
+__device__ __forceinline__ double4 as_double4(const float4 &a, const float4 &b) {
+    return make_double4(__hiloint2double(__float_as_int(a.y), __float_as_int(a.x)),
+                        __hiloint2double(__float_as_int(a.w), __float_as_int(a.z)),
+                        __hiloint2double(__float_as_int(b.y), __float_as_int(b.x)),
+                        __hiloint2double(__float_as_int(b.w), __float_as_int(b.z)));
+}
+
 // ------------------------------------------------------------- S2 volume
 template <typename T, int G>
 __global__ __launch_bounds__(kBlock) void k_volume(const double4 *__restrict__ posH,
@@ -546,9 +626,9 @@ __global__ __launch_bounds__(kBlock) void k_gradv(const double4 *__restrict__ po
 // differently.
 //
 // Packed per-particle record of the derivative and compatible passes, eight
-// 4-vectors of data and one of padding (a 144-byte stride for FP32: with
-// a power-of-two stride the partners' records of one step fall on few
-// memory channels, which measured 1.5x slower):
+// 4-vectors (128 bytes in FP32, 256 in FP64; whole cache lines, which the
+// passes move to LDS several lanes a record). The FP32 records are followed
+// by one 4-vector a particle with the positions in fixed point.
 //   0 {vx, vy, vz, Vs}      Vs = V a / sqrt(2), so Vs_i Vs_j = (a^2/2) V_i V_j
 //   1 {P, rho, Clcs, ih}    Clcs = C_l c_s; ih = 1/H, negated for an FP64 row
 //   2 {hA, he, Ag, B0}      hA = hh / a, he = hh^2 eps^2 (hh = H / n_h, eq. mu)
@@ -557,7 +637,7 @@ __global__ __launch_bounds__(kBlock) void k_gradv(const double4 *__restrict__ po
 //   5 {M10, M11, M12, M20}
 //   6 {M21, M22, S0, S1}    S = (g00, g11, g22, g01 + g10, g02 + g20, g12 + g21)
 //   7 {S2, S3, S4, S5}      of grad v (g_ab = dv_a/dx_b)
-constexpr int kRec = 9;   // 4-vectors per record (the last one padding)
+constexpr int kRec = 8;   // 4-vectors per record
 
 struct DerivPrm {
     double gamma, Cl, Cq, eps2, inv_nh, inv_a, adot, eta_c, inv_eta_f, vs_scale, inv_a5;
@@ -569,11 +649,16 @@ struct DerivPrm {
 template <typename T>
 struct Rec {
     T v[3], Vs, P, rho, Clcs, ih, hA, he, Ag, B[3], U[3], M[9], S[6];
-    // FP32 records: the position in fixed point (the record's ninth
-    // 4-vector): high parts q (q_i - q_j taken mod 2^32 is the minimum
-    // image) and the packed low parts qf
-    uint32_t q[3], qf;
 };
+
+// a position in fixed point: high parts q (q_i - q_j taken mod 2^32 is the
+// minimum image) and the packed low parts (in the slots of a float4)
+struct FixedPos {
+    uint32_t q[3], f;
+};
+__device__ __forceinline__ FixedPos fixed_pos(const float4 &v) {
+    return FixedPos{{__float_as_uint(v.x), __float_as_uint(v.y), __float_as_uint(v.z)}, __float_as_uint(v.w)};
+}
 
 // the record of one particle from FP64 state (P, rho, c_s given)
 __device__ __forceinline__ void make_rec(double H, double vx, double vy, double vz, double Vi, double P,
@@ -620,20 +705,13 @@ __device__ __forceinline__ void store_rec(V4 *o, const Rec<double> &r) {
     o[5] = V4{(T)r.M[3], (T)r.M[4], (T)r.M[5], (T)r.M[6]};
     o[6] = V4{(T)r.M[7], (T)r.M[8], (T)r.S[0], (T)r.S[1]};
     o[7] = V4{(T)r.S[2], (T)r.S[3], (T)r.S[4], (T)r.S[5]};
-    o[8] = V4{(T)0, (T)0, (T)0, (T)0};
 }
 
-template <typename V4, typename T>
-__device__ __forceinline__ void load_rec(const V4 *__restrict__ rec, int64_t j, Rec<T> &s) {
-    const V4 *o = rec + j * kRec;
-    const V4 r0 = o[0], r1 = o[1], r2 = o[2], r3 = o[3], r4 = o[4], r5 = o[5], r6 = o[6], r7 = o[7];
-    if constexpr (sizeof(T) == 4) {
-        const V4 r8 = o[8];
-        s.q[0] = __float_as_uint(r8.x);
-        s.q[1] = __float_as_uint(r8.y);
-        s.q[2] = __float_as_uint(r8.z);
-        s.qf = __float_as_uint(r8.w);
-    }
+// the record whose 4-vector k is get(k)
+template <typename T, typename Get>
+__device__ __forceinline__ void unpack_rec(Rec<T> &s, Get &&get) {
+    const auto r0 = get(0), r1 = get(1), r2 = get(2), r3 = get(3), r4 = get(4), r5 = get(5), r6 = get(6),
+               r7 = get(7);
     s.v[0] = r0.x; s.v[1] = r0.y; s.v[2] = r0.z; s.Vs = r0.w;
     s.P = r1.x; s.rho = r1.y; s.Clcs = r1.z; s.ih = r1.w;
     s.hA = r2.x; s.he = r2.y; s.Ag = r2.z; s.B[0] = r2.w;
@@ -695,7 +773,7 @@ __device__ __forceinline__ void pack8_one(int64_t i, int64_t n, const double4 *_
                                           const double *rho, const double *V, const double *A,
                                           const double *B, const double *gA, const double *gB,
                                           const double *gv, const DerivPrm &p, bool fp64row,
-                                          V4 *o, double4 *aux, int *bad) {
+                                          V4 *o, V4 *oq, double4 *aux, int *bad) {
     double r, P, cs;
     gas_state(i, v, m, u, rho, V, n, p.gamma, r, P, cs, bad);
     double B3[3], gA3[3], gB9[9], gv9[9];
@@ -716,8 +794,8 @@ __device__ __forceinline__ void pack8_one(int64_t i, int64_t n, const double4 *_
     if constexpr (sizeof(T) == 4) {
         const double4 x = posH[i];
         const Fixed fx = fixed_q(x.x, p.qinv), fy = fixed_q(x.y, p.qinv), fz = fixed_q(x.z, p.qinv);
-        o[8] = V4{__uint_as_float(fx.q), __uint_as_float(fy.q), __uint_as_float(fz.q),
-                  __uint_as_float(pack_f(fx, fy, fz))};
+        *oq = V4{__uint_as_float(fx.q), __uint_as_float(fy.q), __uint_as_float(fz.q),
+                 __uint_as_float(pack_f(fx, fy, fz))};
     }
     if (aux) aux[i] = make_double4(r, P, cs, 0.0);
 }
@@ -732,10 +810,12 @@ __global__ __launch_bounds__(kBlock) void k_pack8(int64_t n, const double4 *__re
                                                   int32_t *flag_out, int32_t *flist,
                                                   unsigned long long *nflag) {
     // FP32 records are assembled in LDS and leave as one contiguous run per
-    // block (consecutive lanes, consecutive 16 bytes) instead of nine
-    // 16-byte stores 144 bytes apart per lane
+    // block (consecutive lanes, consecutive 16 bytes) instead of eight
+    // 16-byte stores 128 bytes apart per lane (rows of nine 4-vectors there,
+    // so that the lanes' stores fall on different banks)
     constexpr bool STAGE = sizeof(T) == 4;
-    __shared__ V4 s_rec[STAGE ? kBlock * kRec : 1];
+    constexpr int S = kRec + 1;
+    __shared__ V4 s_rec[STAGE ? kBlock * S : 1];
     const int64_t b0 = (int64_t)blockIdx.x * kBlock;
     const int64_t i = b0 + threadIdx.x;
     // with flag_out the FP64 rows are decided here (as k_flag does), from
@@ -749,14 +829,14 @@ __global__ __launch_bounds__(kBlock) void k_pack8(int64_t n, const double4 *__re
             f = flag && flag[i] != 0;
         }
         pack8_one<V4, T>(i, n, posH, v, m, u, rho, V, A, B, gA, gB, gv, p, f != 0,
-                         STAGE ? s_rec + threadIdx.x * kRec : rec + i * kRec, aux, bad);
+                         STAGE ? s_rec + threadIdx.x * S : rec + i * kRec, rec + n * kRec + i, aux, bad);
     }
     if (flag_out) append_row(f != 0, i, flist, nflag);
     if constexpr (STAGE) {
         __syncthreads();
         const int cnt = (int)((n - b0 < kBlock ? n - b0 : kBlock) * kRec);
         V4 *dst = rec + b0 * kRec;
-        for (int k = threadIdx.x; k < cnt; k += kBlock) dst[k] = s_rec[k];
+        for (int k = threadIdx.x; k < cnt; k += kBlock) dst[k] = s_rec[k / kRec * S + k % kRec];
     }
 }
 
@@ -951,66 +1031,166 @@ __device__ __forceinline__ void group_scan_max(int lane, int key, T &x) {
     }
 }
 
+// lane_group with the number of particles a wave at run time, or, with
+// G > 0, groups of G lanes (a power of two) each
+__device__ __forceinline__ LaneGroup lane_group_rt(int P, int G, int64_t i0, int np, int lane,
+                                                   const int64_t *__restrict__ goff,
+                                                   const int32_t *__restrict__ eb,
+                                                   const int32_t *__restrict__ ee) {
+    LaneGroup lg;
+    if (G > 0) {
+        // lanes past the last particle make one more group, without work
+        const int p = lane / G;
+        lg.i = i0 + (p < np ? p : np - 1);
+        lg.first = p < np ? lane % G : INT32_MAX / 2;
+        lg.g = G;
+        lg.key = p;
+        lg.last = p < np && lane % G == G - 1;
+        return lg;
+    }
+    const int len = lane < np ? (int)(goff[i0 + lane + 1] - goff[i0 + lane]) + (ee[i0 + lane] - eb[i0 + lane]) : 0;
+    int cum = len;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int t = __shfl_up(cum, o, 64);
+        if (lane >= o) cum += t;
+    }
+    const int64_t S = __shfl(cum, 63, 64);
+    const int spare = 64 - np;
+    const int start = lane < np ? lane + (S > 0 ? (int)(((int64_t)spare * (cum - len)) / S) : 0) : 64;
+    // this lane's particle: the last p with start_p <= lane
+    int p = 0;
+    for (int q = 1; q < np; q++)
+        if (__builtin_amdgcn_readlane(start, q) <= lane) p = q;
+    const int sp = __shfl(start, p, 64);
+    const int sn = __shfl(start, p + 1 < np ? p + 1 : 63, 64);
+    const int end = p + 1 < np ? sn : 64;
+    lg.i = i0 + p;
+    lg.first = lane - sp;
+    lg.g = end - sp;
+    lg.key = p;
+    lg.last = lane == end - 1;
+    return lg;
+}
+
+template <typename T>
+struct RecIO;
+template <>
+struct RecIO<float> {
+    static constexpr int CH = 8;
+    static __device__ __forceinline__ float4 vec(const Staged<8> &st, int lane, int k) {
+        return stage_piece<8>(st, lane, k);
+    }
+};
+template <>
+struct RecIO<double> {
+    static constexpr int CH = 16;
+    static __device__ __forceinline__ double4 vec(const Staged<16> &st, int lane, int k) {
+        return as_double4(stage_piece<16>(st, lane, 2 * k), stage_piece<16>(st, lane, 2 * k + 1));
+    }
+};
+
+// One particle's pair row N_s(i) (gather row, then extras row) as this lane
+// walks it
+struct PairRow {
+    const int32_t *g, *e;   // the two parts
+    int ng, tot;
+    __device__ __forceinline__ int32_t at(int k) const { return k < ng ? g[k] : e[k - ng]; }
+};
+
+// Runs body(valid, d, record, position index) over this lane's pairs first,
+// first + G, ..., every lane of the wavefront taking part until the last has
+// done (valid false past the end of a row; the record is then i's own). The
+// separations come from the fixed-point positions (FP32) or the FP64 ones.
+template <typename T, typename V4, typename Load, typename Body>
+__device__ __forceinline__ void staged_pairs(const PairRow &row, const V4 *__restrict__ rec, int64_t n, int64_t i,
+                                             const double4 *__restrict__ posH, const Box &box, T qs, int first,
+                                             int G, int lane, Staged<RecIO<T>::CH> &st, Load &&load, Body &&body) {
+    constexpr int CH = RecIO<T>::CH;
+    constexpr bool F32 = sizeof(T) == 4;
+    using P4 = typename std::conditional<F32, float4, double4>::type;
+    const P4 *pos;
+    if constexpr (F32) pos = rec + n * kRec;
+    else pos = posH;
+    const int32_t self = (int32_t)i;
+    const P4 pi = pos[i];
+    int k = first;
+    int32_t jn = k < row.tot ? row.at(k) : self;
+    int32_t j1 = k < row.tot - G ? row.at(k + G) : self;
+    if (!__any(k < row.tot)) return;
+    const bool wide = (uint64_t)n * (CH * 16) >> 32 != 0;
+    stage_load<CH>(rec, wide, st, jn, lane);
+    P4 pn = pos[jn];
+    auto xn = load(jn);
+    for (;;) {
+        stage_wait();
+        Rec<T> sj;
+        unpack_rec<T>(sj, [&](int q) { return RecIO<T>::vec(st, lane, q); });
+        const P4 pj = pn;
+        const auto xj = xn;
+        const bool valid = k < row.tot;
+        k = valid ? k + G : k;
+        const bool more = __any(k < row.tot);
+        if (more) {
+            jn = j1;
+            stage_load<CH>(rec, wide, st, jn, lane);
+            pn = pos[jn];
+            xn = load(jn);
+            j1 = k < row.tot - G ? row.at(k + G) : self;
+        }
+        T d[3];
+        if constexpr (F32) {
+            const FixedPos a = fixed_pos(pi), b = fixed_pos(pj);
+#pragma unroll
+            for (int x = 0; x < 3; x++) d[x] = fixed_d(a.q[x], unpack_f(a.f, x), b.q[x], unpack_f(b.f, x), qs);
+        } else {
+            separation(pi, pj, box, d[0], d[1], d[2]);
+        }
+        body(valid, d, sj, xj);
+        if (!more) break;
+    }
+}
+
 // first particle of this wave when every wave takes P particles
 __device__ __forceinline__ int64_t wave_first(int P) {
     return (xcd_block(blockIdx.x, gridDim.x) * (kBlock / 64) + (threadIdx.x >> 6)) * (int64_t)P;
 }
 
-// Derivative pass, balanced lane groups (P particles per wave). Pairs with
-// an FP64-row flag on either side are left to k_deriv_fix.
-template <typename T, int P, bool TS>
-__global__ __launch_bounds__(kBlock) void k_deriv_bal(const double4 *__restrict__ posH,
-                                                      const int64_t *__restrict__ goff,
-                                                      const int32_t *__restrict__ gidx,
-                                                      const int32_t *__restrict__ eb,
-                                                      const int32_t *__restrict__ ee,
-                                                      const int32_t *__restrict__ eidx,
-                                                      const typename std::conditional<sizeof(T) == 4, float4, double4>::type *__restrict__ rec,
-                                                      const double *__restrict__ m, int64_t n, Box box,
-                                                      DerivPrm p, double *dpdt, double *dudt,
-                                                      double *ts_vs = nullptr, double *ts_qr = nullptr) {
+// Derivative pass: P particles a wave, in balanced lane groups or in groups
+// of G lanes (G > 0). Pairs with an FP64-row flag on either side are left to
+// k_deriv_fix.
+template <typename T, bool TS>
+__global__ __launch_bounds__(kBlock, sizeof(T) == 4 ? 4 : 2) void k_deriv(const double4 *__restrict__ posH,
+                                                  const int64_t *__restrict__ goff,
+                                                  const int32_t *__restrict__ gidx,
+                                                  const int32_t *__restrict__ eb,
+                                                  const int32_t *__restrict__ ee,
+                                                  const int32_t *__restrict__ eidx,
+                                                  const typename std::conditional<sizeof(T) == 4, float4, double4>::type *__restrict__ rec,
+                                                  const double *__restrict__ m, int64_t n, Box box, DerivPrm p,
+                                                  int P, int G, double *dpdt, double *dudt,
+                                                  double *ts_vs = nullptr, double *ts_qr = nullptr) {
+    __shared__ Staged<RecIO<T>::CH> s_st[kBlock / 64];
     const int64_t i0 = wave_first(P);
     if (i0 >= n) return;   // whole waves leave together
     const int lane = threadIdx.x & 63;
+    Staged<RecIO<T>::CH> &st = s_st[__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)];
     const int np = (int)(n - i0 < P ? n - i0 : P);
-    const LaneGroup lg = lane_group<P>(i0, np, lane, goff, eb, ee);
+    const LaneGroup lg = lane_group_rt(P, G, i0, np, lane, goff, eb, ee);
     const int64_t i = lg.i;
     double a[4] = {0.0, 0.0, 0.0, 0.0};
     T vs = (T)0, qr = (T)0;
     Rec<T> si;
-    load_rec(rec, i, si);
-    const double4 pi = posH[i];
+    unpack_rec<T>(si, [&](int k) { return rec[i * kRec + k]; });
     const PairK<T> pk = pair_k<T>(p);
     const int64_t gb = goff[i];
-    const int ngi = (int)(goff[i + 1] - gb);
-    const int ebi = eb[i];
-    const int tot = fp64_row(si) ? 0 : ngi + (ee[i] - ebi);
-    const int G = lg.g;
-    int kk = lg.first;
-    int32_t jn = kk < tot ? (kk < ngi ? gidx[gb + kk] : eidx[ebi + (kk - ngi)]) : 0;
-    for (; kk < tot; kk += G) {
-        const int32_t j = jn;
-        const int kn = kk + G;
-        if (kn < tot) jn = kn < ngi ? gidx[gb + kn] : eidx[ebi + (kn - ngi)];
-        // the partner's position and record are loaded together and the
-        // pair is evaluated before its FP64-row flag is looked at, so no
-        // load waits on another
-        Rec<T> sj;
-        load_rec(rec, j, sj);
-        T d[3];
-        if constexpr (sizeof(T) == 4) {
-            // FP32 pair terms: d from the fixed-point positions, whose
-            // 32-bit difference wraps to the minimum image (error at most
-            // L 2^-32 per component, then the FP32 rounding); the position
-            // rides in the record, so no separate position load
-#pragma unroll
-            for (int x = 0; x < 3; x++) d[x] = fixed_d(si.q[x], unpack_f(si.qf, x), sj.q[x], unpack_f(sj.qf, x), pk.qs);
-        } else {
-            separation(pi, posH[j], box, d[0], d[1], d[2]);
-        }
+    PairRow row{gidx + gb, eidx + eb[i], (int)(goff[i + 1] - gb), 0};
+    row.tot = fp64_row(si) ? 0 : row.ng + (ee[i] - eb[i]);
+    staged_pairs<T>(row, rec, n, i, posH, box, pk.qs, lg.first, lg.g, lane, st, [](int32_t) { return 0; },
+                    [&](bool valid, const T(&d)[3], const Rec<T> &sj, int) {
         T FD[3], EP, pvs, pqr;
         pair_deriv<T, TS>(si, sj, d, pk, FD, EP, pvs, pqr);
-        if (!fp64_row(sj)) {
+        if (valid && !fp64_row(sj)) {
             a[0] += (double)FD[0];
             a[1] += (double)FD[1];
             a[2] += (double)FD[2];
@@ -1020,7 +1200,7 @@ __global__ __launch_bounds__(kBlock) void k_deriv_bal(const double4 *__restrict_
                 qr = pqr > qr ? pqr : qr;
             }
         }
-    }
+    });
     group_scan<double, 4>(lane, lg.key, a);
     if constexpr (TS) {
         group_scan_max<T>(lane, lg.key, vs);
@@ -1246,80 +1426,6 @@ __global__ __launch_bounds__(kBlock) void k_gradv_bal(const double4 *__restrict_
         for (int q = 0; q < 9; q++) gradv[q * n + i] = a[q];
 }
 
-// Derivative pass, G lanes per particle striding over N_s(i) (the gather row,
-// then the extras row), compensated sums reduced across the group.
-template <typename T, int G, bool TS = false>
-__global__ __launch_bounds__(kBlock) void k_deriv(const double4 *__restrict__ posH,
-                                                  const int64_t *__restrict__ goff,
-                                                  const int32_t *__restrict__ gidx,
-                                                  const int32_t *__restrict__ eb,
-                                                  const int32_t *__restrict__ ee,
-                                                  const int32_t *__restrict__ eidx,
-                                                  const typename std::conditional<sizeof(T) == 4, float4, double4>::type *__restrict__ rec,
-                                                  const double *__restrict__ m, int64_t n, Box box,
-                                                  DerivPrm p, double *dpdt, double *dudt,
-                                                  double *ts_vs = nullptr, double *ts_qr = nullptr) {
-    int l;
-    int64_t i = group_index(G, l);
-    Acc<T> a[4];
-    T vs = (T)0, qr = (T)0;
-    T Vsi = (T)0;
-    if (i < n) {
-        const double4 pi = posH[i];
-        Rec<T> si;
-        load_rec(rec, i, si);
-        Vsi = si.Vs;
-        const PairK<T> pk = pair_k<T>(p);
-        const int64_t gb = goff[i];
-        const int ngi = (int)(goff[i + 1] - gb);
-        const int ebi = eb[i];
-        const int tot = fp64_row(si) ? 0 : ngi + (ee[i] - ebi);
-        int32_t jn = l < tot ? (l < ngi ? gidx[gb + l] : eidx[ebi + (l - ngi)]) : 0;
-        for (int kk = l; kk < tot; kk += G) {
-            const int32_t j = jn;
-            const int kn = kk + G;
-            if (kn < tot) jn = kn < ngi ? gidx[gb + kn] : eidx[ebi + (kn - ngi)];
-            const double4 pj = posH[j];
-            Rec<T> sj;
-            load_rec(rec, j, sj);
-            T d[3];
-            separation(pi, pj, box, d[0], d[1], d[2]);
-            T FD[3], EP, pvs, pqr;
-            pair_deriv<T, TS>(si, sj, d, pk, FD, EP, pvs, pqr);
-            if (!fp64_row(sj)) {
-                a[0].add(FD[0]);
-                a[1].add(FD[1]);
-                a[2].add(FD[2]);
-                a[3].add(EP);
-                if constexpr (TS) {
-                    vs = pvs > vs ? pvs : vs;
-                    qr = pqr > qr ? pqr : qr;
-                }
-            }
-        }
-    }
-    group_reduce<T, G, 4>(a);
-    if constexpr (TS) {
-#pragma unroll
-        for (int o = G / 2; o >= 1; o >>= 1) {
-            const T v2 = __shfl_xor(vs, o, G), q2 = __shfl_xor(qr, o, G);
-            vs = v2 > vs ? v2 : vs;
-            qr = q2 > qr ? q2 : qr;
-        }
-    }
-    if (i < n && l == 0) {
-        const double f = (double)Vsi / m[i];
-        dpdt[i] = a[0].value() * f;
-        dpdt[n + i] = a[1].value() * f;
-        dpdt[2 * n + i] = a[2].value() * f;
-        dudt[i] = a[3].value() * f * p.inv_a5;
-        if constexpr (TS) {
-            ts_vs[i] = (double)vs;
-            ts_qr[i] = (double)qr;
-        }
-    }
-}
-
 // FP64 rows of the adaptive mode: for each listed particle, every pair when
 // the particle itself is flagged, else only the pairs with a flagged
 // partner; the FP64 sums are added to the outputs of the FP32 launch.
@@ -1437,64 +1543,54 @@ __device__ __forceinline__ T compat_term(const V4 &ci, const V4 &cj, const T F[3
 // balanced lane groups. With NK = 2 a second kick (records ce2, output du2)
 // shares the pair forces. Pairs with an FP64-row flag on either side are
 // left to k_compat_fix.
-template <typename T, int P, int NK>
-__global__ __launch_bounds__(kBlock) void k_compat_bal(const double4 *__restrict__ posH,
-                                                       const int64_t *__restrict__ goff,
-                                                       const int32_t *__restrict__ gidx,
-                                                       const int32_t *__restrict__ eb,
-                                                       const int32_t *__restrict__ ee,
-                                                       const int32_t *__restrict__ eidx,
-                                                       const typename std::conditional<sizeof(T) == 4, float4, double4>::type *__restrict__ rec,
-                                                       const typename std::conditional<sizeof(T) == 4, float4, double4>::type *__restrict__ ce,
-                                                       const typename std::conditional<sizeof(T) == 4, float4, double4>::type *__restrict__ ce2,
-                                                       const double *__restrict__ m,
-                                                       const double *__restrict__ u, int64_t n, Box box,
-                                                       DerivPrm p, double scale, double cool, double *du,
-                                                       double *du2) {
+template <typename T, int NK>
+__global__ __launch_bounds__(kBlock, sizeof(T) == 4 ? 3 : 2) void k_compat(const double4 *__restrict__ posH,
+                                                   const int64_t *__restrict__ goff,
+                                                   const int32_t *__restrict__ gidx,
+                                                   const int32_t *__restrict__ eb,
+                                                   const int32_t *__restrict__ ee,
+                                                   const int32_t *__restrict__ eidx,
+                                                   const typename std::conditional<sizeof(T) == 4, float4, double4>::type *__restrict__ rec,
+                                                   const typename std::conditional<sizeof(T) == 4, float4, double4>::type *__restrict__ ce,
+                                                   const typename std::conditional<sizeof(T) == 4, float4, double4>::type *__restrict__ ce2,
+                                                   const double *__restrict__ m, const double *__restrict__ u,
+                                                   int64_t n, Box box, DerivPrm p, int P, double scale,
+                                                   double cool, double *du, double *du2) {
     using V4 = typename std::conditional<sizeof(T) == 4, float4, double4>::type;
+    __shared__ Staged<RecIO<T>::CH> s_st[kBlock / 64];
     const int64_t i0 = wave_first(P);
     if (i0 >= n) return;
     const int lane = threadIdx.x & 63;
+    Staged<RecIO<T>::CH> &st = s_st[__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)];
     const int np = (int)(n - i0 < P ? n - i0 : P);
-    const LaneGroup lg = lane_group<P>(i0, np, lane, goff, eb, ee);
+    const LaneGroup lg = lane_group_rt(P, 0, i0, np, lane, goff, eb, ee);
     const int64_t i = lg.i;
     double a[NK] = {};
     Rec<T> si;
-    load_rec(rec, i, si);
-    const double4 pi = posH[i];
-    const V4 cei = ce[i];
-    const V4 cei2 = NK == 2 ? ce2[i] : cei;
+    unpack_rec<T>(si, [&](int k) { return rec[i * kRec + k]; });
+    struct Kick {
+        V4 c[NK];
+    };
+    const auto kick = [&](int32_t j) {
+        Kick k;
+        k.c[0] = ce[j];
+        if constexpr (NK == 2) k.c[1] = ce2[j];
+        return k;
+    };
+    const Kick ki = kick((int32_t)i);
     const PairK<T> pk = pair_k<T>(p);
     const int64_t gb = goff[i];
-    const int ngi = (int)(goff[i + 1] - gb);
-    const int ebi = eb[i];
-    const int tot = fp64_row(si) ? 0 : ngi + (ee[i] - ebi);
-    const int G = lg.g;
-    int kk = lg.first;
-    int32_t jn = kk < tot ? (kk < ngi ? gidx[gb + kk] : eidx[ebi + (kk - ngi)]) : 0;
-    for (; kk < tot; kk += G) {
-        const int32_t j = jn;
-        const int kn = kk + G;
-        if (kn < tot) jn = kn < ngi ? gidx[gb + kn] : eidx[ebi + (kn - ngi)];
-        const V4 cej = ce[j];
-        const V4 cej2 = NK == 2 ? ce2[j] : cej;
-        Rec<T> sj;
-        load_rec(rec, j, sj);
-        T d[3];
-        if constexpr (sizeof(T) == 4) {
-            // as in the derivative pass: d from the records' fixed-point positions
-#pragma unroll
-            for (int x = 0; x < 3; x++) d[x] = fixed_d(si.q[x], unpack_f(si.qf, x), sj.q[x], unpack_f(sj.qf, x), pk.qs);
-        } else {
-            separation(pi, posH[j], box, d[0], d[1], d[2]);
-        }
+    PairRow row{gidx + gb, eidx + eb[i], (int)(goff[i + 1] - gb), 0};
+    row.tot = fp64_row(si) ? 0 : row.ng + (ee[i] - eb[i]);
+    staged_pairs<T>(row, rec, n, i, posH, box, pk.qs, lg.first, lg.g, lane, st, kick,
+                    [&](bool valid, const T(&d)[3], const Rec<T> &sj, const Kick &kj) {
         T FD[3], EP, vs, qr;
         pair_deriv<T, false>(si, sj, d, pk, FD, EP, vs, qr);
-        if (!fp64_row(sj)) {
-            a[0] += (double)compat_term<T>(cei, cej, FD);
-            if constexpr (NK == 2) a[1] += (double)compat_term<T>(cei2, cej2, FD);
+        if (valid && !fp64_row(sj)) {
+#pragma unroll
+            for (int q = 0; q < NK; q++) a[q] += (double)compat_term<T>(ki.c[q], kj.c[q], FD);
         }
-    }
+    });
     group_scan<double, NK>(lane, lg.key, a);
     if (lg.last) {
         const double f = (double)si.Vs * scale / m[i];
@@ -1504,7 +1600,7 @@ __global__ __launch_bounds__(kBlock) void k_compat_bal(const double4 *__restrict
 }
 
 // FP64 pairs of the adaptive mode (as k_deriv_fix): adds their share of
-// the sum to the output(s) of k_compat_bal.
+// the sum to the output(s) of k_compat.
 template <int G, int NK>
 __global__ __launch_bounds__(kBlock) void k_compat_fix(const double4 *__restrict__ posH,
                                                        const int64_t *__restrict__ goff,
@@ -1981,7 +2077,10 @@ crk_status crk_derivatives(crk_ctx *c, const crk_params *p, const double *v, con
     CRK_TRY(ensure(c, c->misc, 256));
     int *bad = (int *)c->misc.p + 2;
     CRK_TRY(zero_async(c, bad, 1));
-    int Gg = c->G_grad, Gd = c->G_der, Pd = c->P_der, Pg = c->P_grad;
+    // derivative pass: P_der particles a wave in balanced lane groups, or, at
+    // 0, groups of G_der lanes
+    const int Gg = c->G_grad, Gd = c->G_der, Pg = c->P_grad;
+    const int Gf = c->P_der > 0 ? 0 : Gd, Pd = c->P_der > 0 ? c->P_der : 64 / Gd;
 
     // adaptive mode: FP64 rows for ill-conditioned RK templates, flagged by
     // the record packing (which reads the corrections anyway) after the FP32
@@ -1994,7 +2093,7 @@ crk_status crk_derivatives(crk_ctx *c, const crk_params *p, const double *v, con
 
     if (f32) {
         CRK_TRY(ensure(c, c->rec6, (size_t)n * 2 * sizeof(float4)));
-        CRK_TRY(ensure(c, c->rec7, (size_t)n * kRec * sizeof(float4)));
+        CRK_TRY(ensure(c, c->rec7, (size_t)n * (kRec + 1) * sizeof(float4)));
         float4 *r6 = (float4 *)c->rec6.p, *r7 = (float4 *)c->rec7.p;
         double4 *r6d = nullptr, *aux = nullptr;
         if (adapt) {
@@ -2043,15 +2142,13 @@ crk_status crk_derivatives(crk_ctx *c, const crk_params *p, const double *v, con
         }
         {
             KTimer kt_(c, "k_deriv");
-            if (Pd > 0) {
-#define L_DER(PP) if (ts) k_deriv_bal<float, PP, true><<<pblocks(n, PP), kBlock, 0, c->stream>>>(posH, goff, gidx, eb, ee, eidx, r7, m, n, box, dp, dpdt, dudt, tvs, tqr); else k_deriv_bal<float, PP, false><<<pblocks(n, PP), kBlock, 0, c->stream>>>(posH, goff, gidx, eb, ee, eidx, r7, m, n, box, dp, dpdt, dudt)
-                CRK_DISPATCH_P(Pd, L_DER);
-#undef L_DER
-            } else {
-#define L_DER(GG) if (ts) k_deriv<float, GG, true><<<gblocks(n, GG), kBlock, 0, c->stream>>>(posH, goff, gidx, eb, ee, eidx, r7, m, n, box, dp, dpdt, dudt, tvs, tqr); else k_deriv<float, GG><<<gblocks(n, GG), kBlock, 0, c->stream>>>(posH, goff, gidx, eb, ee, eidx, r7, m, n, box, dp, dpdt, dudt)
-                CRK_DISPATCH_G(Gd, L_DER);
-#undef L_DER
-            }
+            const unsigned nb = pblocks(n, Pd);
+            if (ts)
+                k_deriv<float, true><<<nb, kBlock, 0, c->stream>>>(posH, goff, gidx, eb, ee, eidx, r7, m, n, box, dp, Pd,
+                                                                Gf, dpdt, dudt, tvs, tqr);
+            else
+                k_deriv<float, false><<<nb, kBlock, 0, c->stream>>>(posH, goff, gidx, eb, ee, eidx, r7, m, n, box, dp,
+                                                                 Pd, Gf, dpdt, dudt);
         }
         if (adapt && ntouch > 0) {
             Soa s{v, V, A, B, gA, gB, gradv, aux};
@@ -2086,15 +2183,13 @@ crk_status crk_derivatives(crk_ctx *c, const crk_params *p, const double *v, con
         }
         {
             KTimer kt_(c, "k_deriv");
-            if (Pd > 0) {
-#define L_DER(PP) if (ts) k_deriv_bal<double, PP, true><<<pblocks(n, PP), kBlock, 0, c->stream>>>(posH, goff, gidx, eb, ee, eidx, r7, m, n, box, dp, dpdt, dudt, tvs, tqr); else k_deriv_bal<double, PP, false><<<pblocks(n, PP), kBlock, 0, c->stream>>>(posH, goff, gidx, eb, ee, eidx, r7, m, n, box, dp, dpdt, dudt)
-                CRK_DISPATCH_P(Pd, L_DER);
-#undef L_DER
-            } else {
-#define L_DER(GG) if (ts) k_deriv<double, GG, true><<<gblocks(n, GG), kBlock, 0, c->stream>>>(posH, goff, gidx, eb, ee, eidx, r7, m, n, box, dp, dpdt, dudt, tvs, tqr); else k_deriv<double, GG><<<gblocks(n, GG), kBlock, 0, c->stream>>>(posH, goff, gidx, eb, ee, eidx, r7, m, n, box, dp, dpdt, dudt)
-                CRK_DISPATCH_G(Gd, L_DER);
-#undef L_DER
-            }
+            const unsigned nb = pblocks(n, Pd);
+            if (ts)
+                k_deriv<double, true><<<nb, kBlock, 0, c->stream>>>(posH, goff, gidx, eb, ee, eidx, r7, m, n, box, dp, Pd,
+                                                                Gf, dpdt, dudt, tvs, tqr);
+            else
+                k_deriv<double, false><<<nb, kBlock, 0, c->stream>>>(posH, goff, gidx, eb, ee, eidx, r7, m, n, box, dp,
+                                                                 Pd, Gf, dpdt, dudt);
         }
     }
     CRK_HIP(c, hipGetLastError());
@@ -2181,7 +2276,7 @@ crk_status crk::compat_pass(crk_ctx *c, const crk_params *p, const double *v, co
         }
     }
     if (f32) {
-        CRK_TRY(ensure(c, c->rec7, (size_t)n * kRec * sizeof(float4)));
+        CRK_TRY(ensure(c, c->rec7, (size_t)n * (kRec + 1) * sizeof(float4)));
         CRK_TRY(ensure(c, c->ce, (size_t)n * sizeof(float4) * (two ? 2 : 1)));
         float4 *r7 = (float4 *)c->rec7.p, *ce = (float4 *)c->ce.p;
         float4 *ce2 = two ? ce + n : nullptr;
@@ -2199,12 +2294,16 @@ crk_status crk::compat_pass(crk_ctx *c, const crk_params *p, const double *v, co
             k_pack_ce<float4, float><<<nblocks(n), kBlock, 0, c->stream>>>(n, v, pk, dpdt, m, u, rho, V, p->gamma, p->a, dt, ce, ced);
             if (two) k_pack_ce<float4, float><<<nblocks(n), kBlock, 0, c->stream>>>(n, v, pk2, dpdt, m, u, rho, V, p->gamma, p->a, dt, ce2, ced2);
         }
-#define L_CE(PP) if (two) k_compat_bal<float, PP, 2><<<pblocks(n, PP), kBlock, 0, c->stream>>>(posH, goff, gidx, eb, ee, eidx, r7, ce, ce2, m, u, n, box, dp, scale, cool, du, du2); else k_compat_bal<float, PP, 1><<<pblocks(n, PP), kBlock, 0, c->stream>>>(posH, goff, gidx, eb, ee, eidx, r7, ce, nullptr, m, u, n, box, dp, scale, cool, du, nullptr)
         {
             KTimer kt_(c, "k_compat");
-            CRK_DISPATCH_P(Pd, L_CE);
+            const unsigned nb = pblocks(n, Pd);
+            if (two)
+                k_compat<float, 2><<<nb, kBlock, 0, c->stream>>>(posH, goff, gidx, eb, ee, eidx, r7, ce, ce2, m, u, n, box,
+                                                              dp, Pd, scale, cool, du, du2);
+            else
+                k_compat<float, 1><<<nb, kBlock, 0, c->stream>>>(posH, goff, gidx, eb, ee, eidx, r7, ce, nullptr, m, u, n,
+                                                              box, dp, Pd, scale, cool, du, nullptr);
         }
-#undef L_CE
         if (adapt && ar.ntouch > 0) {
             Soa s{v, V, A, B, gA, gB, gradv, aux};
 #define L_CEF(GG) if (two) k_compat_fix<GG, 2><<<fix_blocks(ar.ntouch, GG, false), kBlock, 0, c->stream>>>(posH, goff, gidx, eb, ee, eidx, s, ced, ced2, ar.flag, ar.tlist, ar.ntouch, m, n, box, dp, scale, du, du2); else k_compat_fix<GG, 1><<<fix_blocks(ar.ntouch, GG, false), kBlock, 0, c->stream>>>(posH, goff, gidx, eb, ee, eidx, s, ced, nullptr, ar.flag, ar.tlist, ar.ntouch, m, n, box, dp, scale, du, nullptr)
@@ -2223,12 +2322,16 @@ crk_status crk::compat_pass(crk_ctx *c, const crk_params *p, const double *v, co
             k_pack_ce<double4, double><<<nblocks(n), kBlock, 0, c->stream>>>(n, v, pk, dpdt, m, u, rho, V, p->gamma, p->a, dt, ce, nullptr);
             if (two) k_pack_ce<double4, double><<<nblocks(n), kBlock, 0, c->stream>>>(n, v, pk2, dpdt, m, u, rho, V, p->gamma, p->a, dt, ce2, nullptr);
         }
-#define L_CE(PP) if (two) k_compat_bal<double, PP, 2><<<pblocks(n, PP), kBlock, 0, c->stream>>>(posH, goff, gidx, eb, ee, eidx, r7, ce, ce2, m, u, n, box, dp, scale, cool, du, du2); else k_compat_bal<double, PP, 1><<<pblocks(n, PP), kBlock, 0, c->stream>>>(posH, goff, gidx, eb, ee, eidx, r7, ce, nullptr, m, u, n, box, dp, scale, cool, du, nullptr)
         {
             KTimer kt_(c, "k_compat");
-            CRK_DISPATCH_P(Pd, L_CE);
+            const unsigned nb = pblocks(n, Pd);
+            if (two)
+                k_compat<double, 2><<<nb, kBlock, 0, c->stream>>>(posH, goff, gidx, eb, ee, eidx, r7, ce, ce2, m, u, n, box,
+                                                              dp, Pd, scale, cool, du, du2);
+            else
+                k_compat<double, 1><<<nb, kBlock, 0, c->stream>>>(posH, goff, gidx, eb, ee, eidx, r7, ce, nullptr, m, u, n,
+                                                              box, dp, Pd, scale, cool, du, nullptr);
         }
-#undef L_CE
     }
     CRK_HIP(c, hipGetLastError());
     int *pin = (int *)c->pinned.p + 32;
