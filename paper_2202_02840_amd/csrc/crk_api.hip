@@ -292,7 +292,7 @@ crk_status crk_workspace_estimate(const crk_ctx *c, int64_t n, int32_t nboxes,
     t += 2 * held(4.0 * ntab);
     t += held(4.0 * N) + held(8.0 * (N + 2.0)) + held(8.0 * (N + 1.0)) + 2 * held(4.0 * N);   // counts, offsets
     t += held(4.0 * N * walk_cap) + held(4.0 * (N + 1.0));                // walk rows, long rows
-    t += held(4.0 * P) + 2 * held(4.0 * 0.5 * P) + 2 * held(4.0 * N);    // N_g rows, extras (E <= P/2)
+    t += held(4.0 * P + 16.0) + 2 * held(4.0 * 0.5 * P) + 2 * held(4.0 * N);    // N_g rows, extras (E <= P/2)
     if (precision != CRK_MIXED) t += held(8.0 * N);                       // the build's FP64 volumes
     // passes
     const bool f64 = precision == CRK_FP64, adapt = precision == CRK_MIXED_ADAPT;
@@ -313,7 +313,7 @@ crk_status crk_workspace_estimate(const crk_ctx *c, int64_t n, int32_t nboxes,
     if (uses & CRK_WS_GRAPH) {
         t += held(24.0 * N) + 3 * held(8.0 * N) + held((nboxes + 1) * 8.0) + held(64.0);
         // list capacities of the recorded step: 1.25 P + 1024 (default headroom)
-        t += held(4.0 * (1.25 * P + 1024.0)) - held(4.0 * P);
+        t += held(4.0 * (1.25 * P + 1024.0) + 16.0) - held(4.0 * P + 16.0);
         t += 2 * (held(4.0 * (0.625 * P + 1024.0)) - held(2.0 * P));
     }
     if (uses & CRK_WS_LEAVES) {

@@ -1156,7 +1156,8 @@ static crk_status build_lists(crk_ctx *c) {
         longest = pin[2];
     }
     if (E > INT32_MAX - 1) return set_err(c, CRK_ERR_INVALID_ARG, "more than 2^31 extra pairs");
-    CRK_TRY(ensure(c, c->gidx, (size_t)(G > 0 ? G : 1) * sizeof(int32_t)));
+    // (four entries more: the passes read whole 16-byte pieces)
+    CRK_TRY(ensure(c, c->gidx, (size_t)(G + 4) * sizeof(int32_t)));
     CRK_TRY(ensure(c, c->etmp, (size_t)(E > 0 ? E : 1) * sizeof(int32_t)));
     CRK_TRY(ensure(c, c->eidx, (size_t)(E > 0 ? E : 1) * sizeof(int32_t)));
     CRK_TRY(ensure(c, c->eb, (size_t)n * sizeof(int32_t)));
@@ -1210,6 +1211,8 @@ static crk_status build_lists(crk_ctx *c) {
         c->ngather = c->nextra = c->npairs = -1;
     } else {
         c->ngather = G;
+        c->mean_row = (double)G / (double)n;
+        c->mean_pairs = (double)(G + E) / (double)n;
         c->nextra = E;
         c->npairs = G + E;
         c->walk_cap_auto = walk_cap_next((double)G, (double)n, longest);

@@ -120,6 +120,8 @@ struct crk_ctx {
 
     // per-pass tuning: lanes per particle (1..64)
     int G_vol = 4, G_mom = 1, G_grad = 4, G_der = 8;
+    // mean gather row and mean pair row of the last eager build
+    double mean_row = 0.0, mean_pairs = 0.0;
     // volume, moment, velocity-gradient, derivative (and compatible)
     // passes: particles per wavefront of the balanced lane-group mapping
     // (4, 8, 16 or 32); 0 = the G_* lanes per particle above

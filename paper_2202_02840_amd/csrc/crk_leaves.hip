@@ -702,7 +702,7 @@ crk_status crk_build_leaves(crk_ctx *c, int32_t nboxes, const int64_t *box_offse
         ovr = *(int *)(pin + 2);
     }
     if (E > INT32_MAX - 1) return set_err(c, CRK_ERR_INVALID_ARG, "more than 2^31 extra pairs");
-    CRK_TRY(ensure(c, c->gidx, (size_t)std::max<int64_t>(G, 1) * sizeof(int32_t)));
+    CRK_TRY(ensure(c, c->gidx, (size_t)(G + 4) * sizeof(int32_t)));
     CRK_TRY(ensure(c, c->eidx, (size_t)std::max<int64_t>(E, 1) * sizeof(int32_t)));
     CRK_TRY(ensure(c, c->eb, (size_t)n * sizeof(int32_t)));
     CRK_TRY(ensure(c, c->ee, (size_t)n * sizeof(int32_t)));
@@ -724,6 +724,8 @@ crk_status crk_build_leaves(crk_ctx *c, int32_t nboxes, const int64_t *box_offse
     }
     CRK_HIP(c, hipStreamSynchronize(c->stream));
     c->ngather = G;
+    c->mean_row = (double)G / (double)n;
+    c->mean_pairs = (double)(G + E) / (double)n;
     c->nextra = E;
     c->npairs = G + E;
     c->built = 1;

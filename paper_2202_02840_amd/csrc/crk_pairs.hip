@@ -224,6 +224,92 @@ __device__ __forceinline__ float4 stage_piece(const Staged<CH> &st, int lane, in
     return *(const float4 *)(st.rec + (c * Staged<CH>::kStep + (lane - c) * 16) + 16 * k);
 }
 
+// The entries l, l + G, ... below cnt of a row: term(load(k)) for each in
+// turn, the next D (1 or 2) partners' records loading meanwhile (load takes
+// any k).
+template <int G, int D, typename Load, typename Term>
+__device__ __forceinline__ void row_terms(int l, int cnt, Load &&load, Term &&term) {
+    auto r0 = load(l);
+    if constexpr (D == 1) {
+        for (int k = l; k < cnt; k += G) {
+            const auto a = r0;
+            r0 = load(k + G);
+            term(a);
+        }
+    } else {
+        auto r1 = load(l + G);
+        for (int k = l; k < cnt; k += 2 * G) {
+            const auto a = r0;
+            r0 = load(k + 2 * G);
+            term(a);
+            const auto b = r1;
+            r1 = load(k + 3 * G);
+            if (k + G < cnt) term(b);
+        }
+    }
+}
+
+// Tiles of the gather rows of a wavefront's 64 / G groups in LDS. Read from
+// memory as the loop goes, every step of many rows would meet the first line
+// of some row's next 32 entries, and a wavefront's loads complete in order,
+// so that each step would wait for HBM whatever is prefetched. One load
+// instruction brings the next 4 G entries of each row.
+template <int G>
+struct RowTile {
+    static constexpr int kLoads = G < 16 ? 8 : 128 / G;
+    static constexpr int kTile = 4 * G * kLoads - (G < 2 ? 4 : 2 * G);   // entries used: any alignment, whole steps
+    __align__(16) int32_t e[kLoads * 256];
+};
+
+// the tile from entry k0 (a multiple of four) of the row at gidx + b4 + al of
+// this lane's group, b4 a multiple of four; up to three entries past the row
+// are read
+template <int G>
+__device__ __forceinline__ void fetch_tile(RowTile<G> &t, const int32_t *__restrict__ gidx, int64_t b4, int end,
+                                           int k0, int l) {
+    const int32_t *p = gidx + b4 + k0 + 4 * l;
+    int o = k0 + 4 * l;
+#pragma unroll
+    for (int q = 0; q < RowTile<G>::kLoads; q++, p += 4 * G, o += 4 * G)
+        if (o < end)
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)p,
+                                             (__attribute__((address_space(3))) void *)(t.e + q * 256), 16, 0, 0);
+    stage_wait();
+}
+
+// word of the tile, from its group's first on, that holds entry x (counted from
+// its first, aligned, entry)
+template <int G>
+__device__ __forceinline__ uint32_t tile_word(uint32_t x) {
+    return x / (4 * G) * 256 + x % (4 * G);
+}
+
+// The sum over the row gidx[b .. b + cnt) of this lane's group: term(load(j))
+// over the lane's entries j, the next D (1 or 2) partners' records loading
+// meanwhile. self: any particle, loaded past the end.
+template <int G, int D, typename Load, typename Term>
+__device__ __forceinline__ void row_sum(RowTile<G> &t, const int32_t *__restrict__ gidx, int64_t b, int cnt,
+                                        int32_t self, int lane, Load &&load, Term &&term) {
+    const int al = (int)(b & 3), l = lane % G;
+    for (int k0 = 0; k0 < cnt; k0 += RowTile<G>::kTile) {
+        __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): the last tile's reads are done
+        __builtin_amdgcn_sched_barrier(0);
+        fetch_tile<G>(t, gidx, b - al, cnt + al, k0, l);
+        const int end = min(cnt - k0, RowTile<G>::kTile);
+        const int32_t *const e = t.e + (lane - l) * 4;
+        row_terms<G, D>(l, end, [&](int k) { return load(k < end ? e[tile_word<G>(k + al)] : self); }, term);
+    }
+}
+
+// a . b with its rounding spelled out: in a sum of products the compiler
+// picks which of them is rounded by itself, and may pick differently in two
+// copies of one loop's body
+template <typename T>
+__device__ __forceinline__ T dot3(const T (&a)[3], const T (&b)[3]) {
+    if constexpr (sizeof(T) == 4) return fmaf(a[2], b[2], fmaf(a[0], b[0], a[1] * b[1]));
+    else return fma(a[2], b[2], fma(a[0], b[0], a[1] * b[1]));
+}
+
 __device__ __forceinline__ double4 as_double4(const float4 &a, const float4 &b) {
     return make_double4(__hiloint2double(__float_as_int(a.y), __float_as_int(a.x)),
                         __hiloint2double(__float_as_int(a.w), __float_as_int(a.z)),
@@ -280,21 +366,27 @@ __global__ __launch_bounds__(kBlock) void k_volume(const double4 *__restrict__ p
 // with Q2_ag = sum u d_a d_g and Q3_abg = sum u d_a d_b d_g, both symmetric
 // in their indices (6 and 10 distinct sums), since d/dx_i (d_a W) = delta W +
 // d_a grad W. Same sums as the term-by-term form, grouped differently.
+// Bound by FP64 vector instructions (76 a pair) where the loads keep up:
+// 128^3, four lanes a row, 0.92 ms with the index rows read in the loop, 0.84
+// with them tiled through LDS and two records ahead; 64^3, one lane a row, 0.41
+// and 0.22 ms. Four wavefronts a SIMD: five would spill the 29 sums.
 // index of the symmetric pair (a, b) among (0,0),(0,1),(0,2),(1,1),(1,2),(2,2),
 // and of the sorted triple (a, b, c) among the ten triples in lexicographic order
 __device__ constexpr int kSym2[3][3] = {{0, 1, 2}, {1, 3, 4}, {2, 4, 5}};
 __device__ constexpr int kSym3[3][3][3] = {{{0, 1, 2}, {1, 3, 4}, {2, 4, 5}}, {{1, 3, 4}, {3, 6, 7}, {4, 7, 8}}, {{2, 4, 5}, {4, 7, 8}, {5, 8, 9}}};
 
 template <typename T, int G>
-__global__ __launch_bounds__(kBlock) void k_moments(const double4 *__restrict__ posH,
+__global__ __launch_bounds__(kBlock, 4) void k_moments(const double4 *__restrict__ posH,
                                                     const int64_t *__restrict__ goff,
                                                     const int32_t *__restrict__ gidx,
                                                     const double4 *__restrict__ posV, int64_t n, Box box,
                                                     double *m0, double *m1, double *m2, double *gm0,
                                                     double *gm1, double *gm2) {
     // sums: 0 m0 | 1-3 m1 | 4-9 m2 | 10-12 gm0 | 13-18 Q2 | 19-28 Q3
+    __shared__ RowTile<G> s_rows[kBlock / 64];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int l;
-    int64_t i = group_index(G, l);
+    const int64_t i = group_index(G, l);
     Acc<T> a[29];
     if (i < n) {
         double4 pi = posH[i];
@@ -303,17 +395,13 @@ __global__ __launch_bounds__(kBlock) void k_moments(const double4 *__restrict__ 
         T cw = (T)kW * invH2 * invH;
         T cg = (T)kG * invH2 * invH2 * invH;
         if (l == 0) a[0].add((T)posV[i].w * cw);   // self pair: d = 0, so m0 only
-        int64_t b = goff[i];
-        int cnt = (int)(goff[i + 1] - b);
-        int32_t jn = l < cnt ? gidx[b + l] : 0;
-        for (int k = l; k < cnt; k += G) {
-            const int32_t j = jn;
-            if (k + G < cnt) jn = gidx[b + k + G];
-            const double4 pj = posV[j];   // x, y, z and V
+        const int64_t b = goff[i];
+        const int cnt = (int)(goff[i + 1] - b);
+        const auto term = [&](const double4 &pj) {   // x, y, z and V
             T Vj = (T)pj.w;
             T d[3];
             separation(pi, pj, box, d[0], d[1], d[2]);
-            T q = Mth<T>::sqrt(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]) * invH;
+            T q = Mth<T>::sqrt(dot3(d, d)) * invH;
             T w, gf;
             kernel_wg(q, cw, cg, w, gf);
             const T t = Vj * w, u = Vj * gf;
@@ -337,7 +425,9 @@ __global__ __launch_bounds__(kBlock) void k_moments(const double4 *__restrict__ 
                 for (int y = x; y < 3; y++)
 #pragma unroll
                     for (int z = y; z < 3; z++) a[19 + kSym3[x][y][z]].add(u * dd[kSym2[x][y]] * d[z]);
-        }
+        };
+        row_sum<G, sizeof(T) == 8 ? 2 : 1>(s_rows[wave], gidx, b, cnt, (int32_t)i, lane,
+                                           [&](int32_t j) { return posV[j]; }, term);
     }
     group_reduce<T, G, 29>(a);
     if (i < n && l == 0) {
@@ -476,7 +566,9 @@ __device__ __forceinline__ void rk_grad(const Coef<T> &k, const T d[3], T w, T g
 }
 
 // i = list[g] when a list is given (the FP64 rows of the adaptive mode),
-// else i = g; rows with skip[i] set are left to another launch.
+// else i = g; rows with skip[i] set are left to another launch. Index rows as
+// in the moment pass: 128^3 FP32 rows 0.74 ms with 8 lanes a row and the
+// indices read in the loop, 0.62 with 4 lanes and tiles (0.71 with 8).
 template <typename T, int G>
 __global__ __launch_bounds__(kBlock) void k_gradv(const double4 *__restrict__ posH,
                                                   const int64_t *__restrict__ goff,
@@ -488,6 +580,8 @@ __global__ __launch_bounds__(kBlock) void k_gradv(const double4 *__restrict__ po
                                                   const int32_t *__restrict__ list, int64_t nlist,
                                                   const int64_t *__restrict__ nlist_dev,
                                                   const int32_t *__restrict__ skip, double *gradv) {
+    __shared__ RowTile<G> s_rows[kBlock / 64];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int l;
     int64_t g = group_index(G, l);
     if (nlist_dev) nlist = *nlist_dev;
@@ -512,6 +606,9 @@ __global__ __launch_bounds__(kBlock) void k_gradv(const double4 *__restrict__ po
         const T vi[3] = {ri.x, ri.y, ri.z};
         const int64_t b = goff[i];
         const int cnt = (int)(goff[i + 1] - b);
+        const auto sum = [&](auto &&load, auto &&term) {
+            row_sum<G, sizeof(T) == 4 ? 2 : 1>(s_rows[wave], gidx, b, cnt, (int32_t)i, lane, load, term);
+        };
         if constexpr (sizeof(T) == 8) {
             // eq. (gRK) term by term
             const T invH = (T)(1.0 / pi.w);
@@ -527,12 +624,11 @@ __global__ __launch_bounds__(kBlock) void k_gradv(const double4 *__restrict__ po
             }
 #pragma unroll
             for (int s = 0; s < 9; s++) k.gB[s] = (T)gB[s * n + i];
-            int32_t jn = l < cnt ? gidx[b + l] : 0;
-            for (int kk = l; kk < cnt; kk += G) {
-                const int32_t j = jn;
-                if (kk + G < cnt) jn = gidx[b + kk + G];
-                const double4 pj = posH[j];
-                auto rj = rec6[j];
+            struct Partner {
+                double4 p, r;
+            };
+            sum([&](int32_t j) { return Partner{posH[j], rec6[j]}; }, [&](const Partner &q_) {
+                const double4 &pj = q_.p, &rj = q_.r;
                 T d[3];
                 separation(pi, pj, box, d[0], d[1], d[2]);
                 const T q = Mth<T>::sqrt(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]) * invH;
@@ -545,7 +641,7 @@ __global__ __launch_bounds__(kBlock) void k_gradv(const double4 *__restrict__ po
                 for (int x = 0; x < 3; x++)
 #pragma unroll
                     for (int y = 0; y < 3; y++) a[x * 3 + y].add(-dv[x] * G3[y]);
-            }
+            });
         } else {
             // the regrouped template: grad W^R_ij = pw (U + M d) + Ag c pg d
             const double ihd = 1.0 / pi.w, cwd = kW * ihd * ihd * ihd;
@@ -556,14 +652,14 @@ __global__ __launch_bounds__(kBlock) void k_gradv(const double4 *__restrict__ po
                 Bd[x] = B[x * n + i];
                 gAd[x] = gA[x * n + i];
             }
-            T U[3], M[9], Bt[3];
+            T U[3], M[3][3], Bt[3];
 #pragma unroll
             for (int g = 0; g < 3; g++) {
                 Bt[g] = (T)Bd[g];
                 U[g] = (T)(cwd * (gAd[g] + Ad * Bd[g]));
 #pragma unroll
                 for (int c = 0; c < 3; c++)
-                    M[g * 3 + c] = (T)(cwd * (gAd[g] * Bd[c] + Ad * gB[(c * 3 + g) * n + i]));
+                    M[g][c] = (T)(cwd * (gAd[g] * Bd[c] + Ad * gB[(c * 3 + g) * n + i]));
             }
             const T Ag = (T)(Ad * kG * ihd * ihd * ihd * ihd * ihd);
             const T ih = (T)ihd;
@@ -571,26 +667,23 @@ __global__ __launch_bounds__(kBlock) void k_gradv(const double4 *__restrict__ po
             const uint32_t qi[3] = {__float_as_uint(qv.x), __float_as_uint(qv.y), __float_as_uint(qv.z)};
             const uint32_t fi = __float_as_uint(qv.w);
             const T qs = (T)(box.L * 2.3283064365386962890625e-10);
-            int32_t jn = l < cnt ? gidx[b + l] : 0;
-            for (int kk = l; kk < cnt; kk += G) {
-                const int32_t j = jn;
-                if (kk + G < cnt) jn = gidx[b + kk + G];
-                auto rj = rec6[S6 * j];
-                const auto qj = rec6[S6 * j + 1];
+            struct Partner {
+                float4 r, q;
+            };
+            sum([&](int32_t j) { return Partner{rec6[S6 * (int64_t)j], rec6[S6 * (int64_t)j + 1]}; },
+                [&](const Partner &q_) {
+                const float4 &rj = q_.r, &qj = q_.q;
                 T d[3];
                 // d from the fixed-point positions (as in the derivative pass)
                 d[0] = fixed_d(qi[0], unpack_f(fi, 0), __float_as_uint(qj.x), unpack_f(__float_as_uint(qj.w), 0), qs);
                 d[1] = fixed_d(qi[1], unpack_f(fi, 1), __float_as_uint(qj.y), unpack_f(__float_as_uint(qj.w), 1), qs);
                 d[2] = fixed_d(qi[2], unpack_f(fi, 2), __float_as_uint(qj.z), unpack_f(__float_as_uint(qj.w), 2), qs);
-                const T r = Mth<T>::sqrt(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]);
                 T pw, pg;
-                kfac(r * ih, pw, pg);
-                const T kc = Ag * ((T)1 + (Bt[0] * d[0] + Bt[1] * d[1] + Bt[2] * d[2])) * pg;
+                kfac(Mth<T>::sqrt(dot3(d, d)) * ih, pw, pg);
+                const T kc = Ag * ((T)1 + dot3(d, Bt)) * pg;
                 T G3[3];
 #pragma unroll
-                for (int g = 0; g < 3; g++)
-                    G3[g] = pw * (U[g] + (M[g * 3 + 0] * d[0] + M[g * 3 + 1] * d[1] + M[g * 3 + 2] * d[2])) +
-                            kc * d[g];
+                for (int g = 0; g < 3; g++) G3[g] = fmaf(kc, d[g], pw * (U[g] + dot3(d, M[g])));
                 // -V_j (v_i - v_j) (x) grad W^R_ij
                 const T w[3] = {((T)rj.x - vi[0]) * (T)rj.w, ((T)rj.y - vi[1]) * (T)rj.w,
                                 ((T)rj.z - vi[2]) * (T)rj.w};
@@ -598,7 +691,7 @@ __global__ __launch_bounds__(kBlock) void k_gradv(const double4 *__restrict__ po
                 for (int x = 0; x < 3; x++)
 #pragma unroll
                     for (int y = 0; y < 3; y++) a[x * 3 + y].add((double)(w[x] * G3[y]));
-            }
+            });
         }
     }
     group_reduce<double, G, 9>(a);
@@ -1055,9 +1148,15 @@ __device__ __forceinline__ LaneGroup lane_group_rt(int P, int G, int64_t i0, int
         const int t = __shfl_up(cum, o, 64);
         if (lane >= o) cum += t;
     }
-    const int64_t S = __shfl(cum, 63, 64);
+    const int S = __builtin_amdgcn_readlane(cum, 63);
     const int spare = 64 - np;
-    const int start = lane < np ? lane + (S > 0 ? (int)(((int64_t)spare * (cum - len)) / S) : 0) : 64;
+    // floor(spare * prefix / S): from FP32, at most one off, and put right
+    // (a division of 64 bits costs a hundred instructions)
+    const int64_t part = (int64_t)spare * (cum - len);
+    int off = S > 0 ? (int)((float)(cum - len) * ((float)spare / (float)S)) : 0;
+    if ((int64_t)off * S > part) off--;
+    else if (S > 0 && (int64_t)(off + 1) * S <= part) off++;
+    const int start = lane < np ? lane + off : 64;
     // this lane's particle: the last p with start_p <= lane
     int p = 0;
     for (int q = 1; q < np; q++)
@@ -1803,6 +1902,38 @@ inline unsigned pblocks(int64_t n, int P) {
     return (unsigned)(((n + P - 1) / P + kBlock / 64 - 1) / (kBlock / 64));
 }
 
+// Lanes per row of the FP64 moment pass and of the velocity gradient, from the
+// lanes asked for up to 16: at most 28 entries of a mean row a lane, and 4096
+// wavefronts, half of what the device holds, so that the last ones end
+// together (45^3 with 268 neighbours: moments 0.313 ms with 4 lanes, 0.152
+// with 16; gradient 0.302 and 0.122. 40^3, 1000 wavefronts at one lane: 0.122
+// with 1, 0.045 with 4, 0.042 with 8). More lanes than that cost more in the
+// reduction at a row's end (128^3: 0.84, 0.98 and 1.45 ms with 4, 8 and 16).
+int row_lanes(const crk_ctx *c, int G) {
+    while (G < 16 && (c->n * G < (int64_t)64 * 4096 || c->mean_row > 28.0 * G)) G *= 2;
+    return G;
+}
+
+// Particles per wavefront of the derivative and compatible passes in balanced
+// groups, from P down to 2: fewer where there would be under 2048 wavefronts
+// (20^3: 0.022 ms with 8, 0.017 with 4; 12^3: 0.020 and 0.014), and 4 instead
+// of 8 where rows are long and the wavefronts few, so that the last ones end
+// together (45^3 with 268 neighbours: 0.246 and 0.222 ms; 40^3 with 64: 0.117
+// and 0.123).
+int deriv_particles(const crk_ctx *c, int P) {
+    while (P > 2 && c->n < (int64_t)P * 2048) P /= 2;
+    if (P == 8 && c->n < (int64_t)P * 16384 && c->mean_pairs >= 160.0) P = 4;
+    return P;
+}
+
+// lanes per listed row of the FP64 fixes: a list is short, so its rows are
+// spread wide (20^3: 0.024 ms with 8 lanes, 0.012 with 32; 128^3: 0.108, 0.105
+// with 16, 0.124 with 32)
+int fix_lanes(const crk_ctx *c, int G) {
+    const int least = c->n < (int64_t)1 << 18 ? 32 : 16;
+    return G > least ? G : least;
+}
+
 // volume then (optionally) moment pass in type T, with the lane mapping of
 // the context (balanced groups of P particles per wave, or G lanes each)
 // n_i and V_i of the volumes the build summed (vnsum, posV.w) into the
@@ -1817,10 +1948,18 @@ __global__ __launch_bounds__(kBlock) void k_volume_out(int64_t n, const double *
 }
 
 template <typename T>
-crk_status volume_moments(crk_ctx *c, const double4 *posH, const int64_t *goff, const int32_t *gidx,
+crk_status volume_moments(crk_ctx *c, int prec, const double4 *posH, const int64_t *goff, const int32_t *gidx,
                           int64_t n, Box box, double *nsum, double *V, T *rv, bool want_m, double *m0,
                           double *m1, double *m2, double *gm0, double *gm1, double *gm2) {
-    const int Gv = c->G_vol, Gm = c->G_mom, Pv = c->P_vol, Pm = c->P_mom;
+    const int Gv = c->G_vol, Pv = c->P_vol, Pm = c->P_mom;
+    // (FP32 sums depend on the lanes at the rounding of a term: they keep the
+    // lanes asked for. So do FP64 ones of large sets, which have particles
+    // whose corrections hang on the last bits of the moments, and those that
+    // FP32 passes go on from, where another order of the sums moves a rounding
+    // of the corrections to FP32; long rows and small sets have most to gain
+    // and least of either)
+    const bool by_rule = sizeof(T) == 8 && (n <= (int64_t)1 << (prec == CRK_FP64 ? 16 : 14) || c->mean_row > 112.0);
+    const int Gm = by_rule ? row_lanes(c, c->G_mom) : c->G_mom;
     CRK_TRY(ensure(c, c->posV, (size_t)n * sizeof(double4)));
     double4 *posV = (double4 *)c->posV.p;
     if (sizeof(T) == 8 && c->vol_ready) {
@@ -1923,10 +2062,10 @@ crk_status crk_moments(crk_ctx *c, const crk_params *p, double *nsum, double *V,
     CRK_TRY(ensure(c, c->recV, (size_t)n * (f32 ? 4 : 8)));
     if (f32) {
         float *rv = (float *)c->recV.p;
-        CRK_TRY(volume_moments<float>(c, posH, goff, gidx, n, box, nsum, V, rv, want_m, m0, m1, m2, gm0, gm1, gm2));
+        CRK_TRY(volume_moments<float>(c, p->precision, posH, goff, gidx, n, box, nsum, V, rv, want_m, m0, m1, m2, gm0, gm1, gm2));
     } else {
         double *rv = (double *)c->recV.p;
-        CRK_TRY(volume_moments<double>(c, posH, goff, gidx, n, box, nsum, V, rv, want_m, m0, m1, m2, gm0, gm1, gm2));
+        CRK_TRY(volume_moments<double>(c, p->precision, posH, goff, gidx, n, box, nsum, V, rv, want_m, m0, m1, m2, gm0, gm1, gm2));
     }
     CRK_HIP(c, hipGetLastError());
     c->have_V = 1;
@@ -2079,8 +2218,9 @@ crk_status crk_derivatives(crk_ctx *c, const crk_params *p, const double *v, con
     CRK_TRY(zero_async(c, bad, 1));
     // derivative pass: P_der particles a wave in balanced lane groups, or, at
     // 0, groups of G_der lanes
-    const int Gg = c->G_grad, Gd = c->G_der, Pg = c->P_grad;
-    const int Gf = c->P_der > 0 ? 0 : Gd, Pd = c->P_der > 0 ? c->P_der : 64 / Gd;
+    const int Gg = row_lanes(c, c->G_grad), Gd = fix_lanes(c, c->G_der), Pg = c->P_grad;
+    const int Gf = c->P_der > 0 ? 0 : c->G_der;
+    const int Pd = c->P_der > 0 ? deriv_particles(c, c->P_der) : 64 / c->G_der;
 
     // adaptive mode: FP64 rows for ill-conditioned RK templates, flagged by
     // the record packing (which reads the corrections anyway) after the FP32
@@ -2137,7 +2277,7 @@ crk_status crk_derivatives(crk_ctx *c, const crk_params *p, const double *v, con
         if (adapt && nflag > 0) {
 #define L_GV(GG) k_gradv<double, GG><<<fix_blocks(nflag, GG, gm), kBlock, 0, c->stream>>>(posH, goff, gidx, r6d, A, B, gA, gB, n, box, flist, nflag, nflag_dev, nullptr, gradv)
             KTimer kt_(c, "k_gradv_fix");
-            CRK_DISPATCH_G(Gg, L_GV);
+            CRK_DISPATCH_G(Gd, L_GV);
 #undef L_GV
         }
         {
@@ -2261,7 +2401,7 @@ crk_status crk::compat_pass(crk_ctx *c, const crk_params *p, const double *v, co
     CRK_TRY(ensure(c, c->misc, 256));
     int *bad = (int *)c->misc.p + 2;
     CRK_TRY(zero_async(c, bad, 1));
-    const int Gd = c->G_der, Pd = c->P_der > 0 ? c->P_der : 8;
+    const int Gd = fix_lanes(c, c->G_der), Pd = deriv_particles(c, c->P_der > 0 ? c->P_der : 8);
     AdaptRows ar;
     // the records, FP64-row flags and lists of the derivative call just made
     // on this same state are reused when the caller says so (eager only)
