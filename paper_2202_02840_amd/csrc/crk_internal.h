@@ -372,11 +372,16 @@ __host__ __device__ inline int walk_cap_for(double g, double n) {
     return (int)(c < 1024.0 ? c : 1024.0);
 }
 
-// The most slots per scratch row that still fit 2^33 slots (32 GiB) for n
-// particles, a multiple of 64 and at most 1024.
+// The most slots per scratch row for n particles, a multiple of 64: as many as
+// fit 2^33 slots (32 GiB) up to 1024, or 2^29 slots (2 GiB) up to 4096 (45^3
+// with 268 neighbours has 109 rows of 1024 to 3300 entries: walking them again
+// and summing them apart took 0.32 ms of its step's 2.4).
 inline int walk_cap_limit(double n) {
-    const double c = n > 0.0 ? 64.0 * std::floor(8589934592.0 / n / 64.0) : 1024.0;
-    return (int)(c < 1024.0 ? c : 1024.0);
+    const auto fit = [n](double slots, double most) {
+        const double c = n > 0.0 ? 64.0 * std::floor(slots / n / 64.0) : most;
+        return (int)(c < most ? c : most);
+    };
+    return std::max(fit(8589934592.0, 1024.0), fit(536870912.0, 4096.0));
 }
 
 // Slots of the next walk's scratch rows after a build with g gather pairs
