@@ -14,6 +14,7 @@
 #include <mutex>
 
 #include "crk_internal.h"
+#include "crk_rows.h"
 
 namespace crk {
 namespace {
@@ -28,8 +29,20 @@ __device__ __forceinline__ float gelu_d(float x) {
     return 0.5f * (1.0f + erff(x * 0.70710678118654752f)) + x * 0.39894228040143268f * __expf(-0.5f * x * x);
 }
 
+// (all loads before the first store: one wait for memory, not one a step)
 __device__ __forceinline__ void load_theta(const float *__restrict__ th, float *s) {
-    for (int e = threadIdx.x; e < kNP; e += blockDim.x) s[e] = th[e];
+    constexpr int N = (kNP + kBlock - 1) / kBlock;
+    float t[N];
+#pragma unroll
+    for (int k = 0; k < N; k++) {
+        const int e = threadIdx.x + k * kBlock;
+        t[k] = th[e < kNP ? e : kNP - 1];
+    }
+#pragma unroll
+    for (int k = 0; k < N; k++) {
+        const int e = threadIdx.x + k * kBlock;
+        if (e < kNP) s[e] = t[k];
+    }
     __syncthreads();
 }
 
@@ -122,191 +135,228 @@ __device__ __forceinline__ float row_sum16(float x) {
     return x;
 }
 
-// Gradient on the matrix cores: a wavefront takes a tile of 16 samples (the
+// Gradient on the matrix cores: a block takes a tile of 16 samples (the
 // columns; lane c = l % 16 is a sample, g = l / 16 picks four hidden units
-// per register tile) and writes one partial gradient row. Forward as in
-// k_hnet_fwd. Backward: dZ2 = dy w3 gelu'(z2) in the same layout; dA1 =
-// W2^T dZ2 on the matrix cores with the permuted k order of the forward;
-// dZ1 = dA1 gelu'(z1). Weight gradients are sums over the tile's samples,
-// so the sample index becomes the k of the product: dZ2, A1 and dZ1 are
-// transposed through LDS (row stride 17), and dW2 = dZ2 A1^T, db2 (a column
-// of ones), dW1 = dZ1 F^T and db1 (F padded with a row of ones) run on the
-// matrix cores; dw3 and db3 are row sums over the 16 sample lanes.
-constexpr int kTS = 17;   // LDS row stride of the transposed 64 x 16 tiles
+// per register tile), its wavefront w the hidden units 16 w .. 16 w + 15 of
+// each layer, and writes one partial gradient row. Forward as in k_hnet_fwd.
+// Backward: dZ2 = dy w3 gelu'(z2) in the same layout; dA1 = W2^T dZ2 on the
+// matrix cores with the permuted k order of the forward; dZ1 = dA1 gelu'(z1).
+// What the other wavefronts' units are needed for passes through LDS (row
+// stride 17). Weight gradients are sums over the tile's samples, so the sample
+// index becomes the k of the product: dW2 = dZ2 A1^T, db2 (a column of ones),
+// dW1 = dZ1 F^T and db1 (F padded with a row of ones) run on the matrix cores
+// from the transposed tiles; dw3 and db3 are row sums over the 16 sample
+// lanes. Bound by the latency of this chain (8192 samples are two tiles a CU):
+// a wavefront per tile, four tiles a block, took 31 us of them, this 16.
+constexpr int kTS = 17;   // LDS row stride of the 64 x 16 tiles
 __global__ __launch_bounds__(kBlock) void k_hnet_grad(const float *__restrict__ theta,
                                                       const float *__restrict__ feat,
                                                       const float *__restrict__ target, int64_t nb,
                                                       float inv_b, float *partial, float *ploss) {
+    static_assert(kBlock == 256, "a wavefront per 16 of 64 hidden units");
     __shared__ float s[kNP];
-    __shared__ float tr[kBlock / 64][3][kHid * kTS];
-    load_theta(theta, s);
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    __shared__ float Ta1[kHid * kTS], Tg2[kHid * kTS], Tdz2[kHid * kTS], Tdz1[kHid * kTS];
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int c = lane & 15, g = lane >> 4;
-    const int64_t tile = (int64_t)blockIdx.x * (kBlock / 64) + wv;
-    if (tile * 16 >= nb) return;   // the whole wavefront: no samples left
+    const int64_t tile = blockIdx.x;
     const int64_t smp = tile * 16 + c;
     const bool act = smp < nb;
-    float *Ta1 = tr[wv][0], *Tdz2 = tr[wv][1], *Tdz1 = tr[wv][2];
-    // forward
-    f4v z1[4], z2[4];
+    const float tgt = act ? target[smp] : 0.0f;
+    float bf[2], fb[4];   // F, and B of dW1: F[c][s] for c < 8, ones for c == 8 (db1), else 0
 #pragma unroll
-    for (int mt = 0; mt < 4; mt++) z1[mt] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-    for (int ks = 0; ks < 2; ks++) {
-        const float bf = act ? feat[(int64_t)(4 * ks + g) * nb + smp] : 0.0f;
-#pragma unroll
-        for (int mt = 0; mt < 4; mt++) z1[mt] = mfma4(s[oW1 + (16 * mt + c) * kIn + 4 * ks + g], bf, z1[mt]);
-    }
-    float a1[4][4];
-#pragma unroll
-    for (int mt = 0; mt < 4; mt++)
-#pragma unroll
-        for (int r = 0; r < 4; r++) {
-            z1[mt][r] += s[ob1 + 16 * mt + 4 * g + r];
-            a1[mt][r] = gelu(z1[mt][r]);
-        }
-#pragma unroll
-    for (int m2 = 0; m2 < 4; m2++) z2[m2] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-    for (int mt = 0; mt < 4; mt++)
-#pragma unroll
-        for (int r = 0; r < 4; r++)
-#pragma unroll
-            for (int m2 = 0; m2 < 4; m2++)
-                z2[m2] = mfma4(s[oW2 + (16 * m2 + c) * kHid + 16 * mt + 4 * g + r], a1[mt][r], z2[m2]);
-    float part = 0.0f;
-#pragma unroll
-    for (int m2 = 0; m2 < 4; m2++)
-#pragma unroll
-        for (int r = 0; r < 4; r++) {
-            z2[m2][r] += s[ob2 + 16 * m2 + 4 * g + r];
-            part += s[ow3 + 16 * m2 + 4 * g + r] * gelu(z2[m2][r]);
-        }
-    part += __shfl_xor(part, 16);
-    part += __shfl_xor(part, 32);
-    const float res = act ? part + s[ob3] - target[smp] : 0.0f;
-    const float dy = 2.0f * res * inv_b;
-    float *out = partial + tile * kNP;
-    // loss and db3: sums over the tile's samples
-    const float lsum = row_sum16(res * res), dysum = row_sum16(dy);
-    if (lane == 0) {
-        ploss[tile] = lsum;
-        out[ob3] = dysum;
-    }
-    // dZ2 (and dw3 from the same registers)
-    float dz2[4][4];
-#pragma unroll
-    for (int m2 = 0; m2 < 4; m2++)
-#pragma unroll
-        for (int r = 0; r < 4; r++) {
-            const int h = 16 * m2 + 4 * g + r;
-            dz2[m2][r] = dy * s[ow3 + h] * gelu_d(z2[m2][r]);
-            const float dw3 = row_sum16(dy * gelu(z2[m2][r]));
-            if (c == 0) out[ow3 + h] = dw3;
-            Tdz2[h * kTS + c] = dz2[m2][r];
-        }
-    // dA1 = W2^T dZ2, then dZ1
-    f4v da1[4];
-#pragma unroll
-    for (int mt = 0; mt < 4; mt++) {
-        da1[mt] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-        for (int m2 = 0; m2 < 4; m2++)
-#pragma unroll
-            for (int r = 0; r < 4; r++)
-                da1[mt] = mfma4(s[oW2 + (16 * m2 + 4 * g + r) * kHid + 16 * mt + c], dz2[m2][r], da1[mt]);
-    }
-#pragma unroll
-    for (int mt = 0; mt < 4; mt++)
-#pragma unroll
-        for (int r = 0; r < 4; r++) {
-            const int h = 16 * mt + 4 * g + r;
-            Ta1[h * kTS + c] = a1[mt][r];
-            Tdz1[h * kTS + c] = da1[mt][r] * gelu_d(z1[mt][r]);
-        }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    // dW2 and db2: k = the tile's samples
-    float fb[4];   // B of dW1: F[c][s] for c < 8, ones for c == 8 (db1), else 0
+    for (int ks = 0; ks < 2; ks++) bf[ks] = act ? feat[(int64_t)(4 * ks + g) * nb + smp] : 0.0f;
 #pragma unroll
     for (int ks = 0; ks < 4; ks++) {
         const int64_t sk = tile * 16 + 4 * ks + g;
         fb[ks] = c < kIn ? (sk < nb ? feat[(int64_t)c * nb + sk] : 0.0f) : (c == kIn ? 1.0f : 0.0f);
     }
+    load_theta(theta, s);
+    const int h0 = 16 * w + 4 * g;   // this lane's units h0 .. h0 + 3
+    // forward
+    f4v z1 = f4v{0.0f, 0.0f, 0.0f, 0.0f}, z2 = z1, da1 = z1;
 #pragma unroll
-    for (int m2 = 0; m2 < 4; m2++) {
-        float av[4];
+    for (int ks = 0; ks < 2; ks++) z1 = mfma4(s[oW1 + (16 * w + c) * kIn + 4 * ks + g], bf[ks], z1);
 #pragma unroll
-        for (int ks = 0; ks < 4; ks++) av[ks] = Tdz2[(16 * m2 + c) * kTS + 4 * ks + g];
-#pragma unroll
-        for (int mt = 0; mt < 4; mt++) {
-            f4v acc = f4v{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-            for (int ks = 0; ks < 4; ks++) acc = mfma4(av[ks], Ta1[(16 * mt + c) * kTS + 4 * ks + g], acc);
-#pragma unroll
-            for (int r = 0; r < 4; r++) out[oW2 + (16 * m2 + 4 * g + r) * kHid + 16 * mt + c] = acc[r];
-        }
-        f4v acc = f4v{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-        for (int ks = 0; ks < 4; ks++) acc = mfma4(av[ks], c == 0 ? 1.0f : 0.0f, acc);
-        if (c == 0)
-#pragma unroll
-            for (int r = 0; r < 4; r++) out[ob2 + 16 * m2 + 4 * g + r] = acc[r];
+    for (int r = 0; r < 4; r++) {
+        z1[r] += s[ob1 + h0 + r];
+        Ta1[(h0 + r) * kTS + c] = gelu(z1[r]);
     }
-    // dW1 (columns 0..7) and db1 (column 8)
+    __syncthreads();
+#pragma unroll
+    for (int mt = 0; mt < 4; mt++)
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+            const int h = 16 * mt + 4 * g + r;
+            z2 = mfma4(s[oW2 + (16 * w + c) * kHid + h], Ta1[h * kTS + c], z2);
+        }
+    float g2[4];
+#pragma unroll
+    for (int r = 0; r < 4; r++) {
+        z2[r] += s[ob2 + h0 + r];
+        g2[r] = gelu(z2[r]);
+        Tg2[(h0 + r) * kTS + c] = g2[r];
+    }
+    __syncthreads();
+    float part = 0.0f;
+#pragma unroll
+    for (int m2 = 0; m2 < 4; m2++)
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+            const int h = 16 * m2 + 4 * g + r;
+            part += s[ow3 + h] * Tg2[h * kTS + c];
+        }
+    part += __shfl_xor(part, 16);
+    part += __shfl_xor(part, 32);
+    const float res = act ? part + s[ob3] - tgt : 0.0f;
+    const float dy = 2.0f * res * inv_b;
+    float *out = partial + tile * kNP;
+    // loss and db3: sums over the tile's samples
+    const float lsum = row_sum16(res * res), dysum = row_sum16(dy);
+    if (threadIdx.x == 0) {
+        ploss[tile] = lsum;
+        out[ob3] = dysum;
+    }
+    // dZ2 (and dw3 from the same registers)
+#pragma unroll
+    for (int r = 0; r < 4; r++) {
+        const int h = h0 + r;
+        Tdz2[h * kTS + c] = dy * s[ow3 + h] * gelu_d(z2[r]);
+        const float dw3 = row_sum16(dy * g2[r]);
+        if (c == 0) out[ow3 + h] = dw3;
+    }
+    __syncthreads();
+    // dA1 = W2^T dZ2, then dZ1
+#pragma unroll
+    for (int m2 = 0; m2 < 4; m2++)
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+            const int h = 16 * m2 + 4 * g + r;
+            da1 = mfma4(s[oW2 + h * kHid + 16 * w + c], Tdz2[h * kTS + c], da1);
+        }
+#pragma unroll
+    for (int r = 0; r < 4; r++) Tdz1[(h0 + r) * kTS + c] = da1[r] * gelu_d(z1[r]);
+    // (the tiles below are this wavefront's own rows, but A1, which is there)
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    // dW2 and db2: k = the tile's samples
+    float av[4];
+#pragma unroll
+    for (int ks = 0; ks < 4; ks++) av[ks] = Tdz2[(16 * w + c) * kTS + 4 * ks + g];
 #pragma unroll
     for (int mt = 0; mt < 4; mt++) {
         f4v acc = f4v{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int ks = 0; ks < 4; ks++) acc = mfma4(Tdz1[(16 * mt + c) * kTS + 4 * ks + g], fb[ks], acc);
+        for (int ks = 0; ks < 4; ks++) acc = mfma4(av[ks], Ta1[(16 * mt + c) * kTS + 4 * ks + g], acc);
 #pragma unroll
-        for (int r = 0; r < 4; r++) {
-            const int h = 16 * mt + 4 * g + r;
-            if (c < kIn) out[oW1 + h * kIn + c] = acc[r];
-            else if (c == kIn) out[ob1 + h] = acc[r];
-        }
+        for (int r = 0; r < 4; r++) out[oW2 + (h0 + r) * kHid + 16 * mt + c] = acc[r];
+    }
+    f4v acc = f4v{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int ks = 0; ks < 4; ks++) acc = mfma4(av[ks], c == 0 ? 1.0f : 0.0f, acc);
+    if (c == 0)
+#pragma unroll
+        for (int r = 0; r < 4; r++) out[ob2 + h0 + r] = acc[r];
+    // dW1 (columns 0..7) and db1 (column 8)
+    acc = f4v{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int ks = 0; ks < 4; ks++) acc = mfma4(Tdz1[(16 * w + c) * kTS + 4 * ks + g], fb[ks], acc);
+#pragma unroll
+    for (int r = 0; r < 4; r++) {
+        const int h = h0 + r;
+        if (c < kIn) out[oW1 + h * kIn + c] = acc[r];
+        else if (c == kIn) out[ob1 + h] = acc[r];
     }
 }
 
-// fixed-order sum of the block partials (kAdamLanes lanes per parameter,
-// lane c takes blocks c, c + kAdamLanes, ...; the lanes combine in a fixed
-// butterfly), then one Adam step per parameter (bias-corrected, beta1 0.9,
-// beta2 0.999, eps 1e-8)
-__global__ __launch_bounds__(kBlock) void k_hnet_adam(const float *__restrict__ partial, int64_t nblk,
+// Fixed-order sum of the partial rows, then one Adam step per parameter
+// (bias-corrected, beta1 0.9, beta2 0.999, eps 1e-8). kAdamLanes running sums a
+// parameter, sum c over the rows c, c + kAdamLanes, ..., added up as a binary
+// tree. A block takes kAdamPar parameters, so that a row is read 64 bytes at a
+// time (a lane per sum and row read a line of which it used four). One more
+// block sums the loss in the order of the tiles, beside the others.
+constexpr int kAdamPar = 16, kAdamBlocks = (kNP + kAdamPar - 1) / kAdamPar;
+__global__ __launch_bounds__(kBlock) void k_hnet_adam(const float *__restrict__ partial,
+                                                      const float *__restrict__ ploss, int64_t nblk,
                                                       float *theta, float *m, float *v, float lr,
-                                                      float bc1, float bc2, float *grad_out) {
-    const int t = blockIdx.x * kBlock + threadIdx.x;
-    const int e = t / kAdamLanes, c = t % kAdamLanes;
-    if (e >= kNP) return;   // whole lane groups leave together
-    float g = 0.0f;
-    for (int64_t b = c; b < nblk; b += kAdamLanes) g += partial[b * kNP + e];
+                                                      float bc1, float bc2, float *grad_out, float inv_b,
+                                                      float *loss) {
+    constexpr int kGroups = kBlock / kAdamPar, kSums = kAdamLanes / kGroups;
+    __shared__ __align__(16) float s[1024];
+    static_assert(kAdamLanes * kAdamPar <= 1024, "the running sums fit");
+    if (blockIdx.x == kAdamBlocks) {
+        float L = 0.0f;
+        for (int64_t b0 = 0; b0 < nblk; b0 += 1024) {
+            __syncthreads();
 #pragma unroll
-    for (int o = 1; o < kAdamLanes; o <<= 1) g += __shfl_xor(g, o, kAdamLanes);
-    if (c != 0) return;
-    if (grad_out) grad_out[e] = g;
+            for (int k = 0; k < 1024; k += kBlock)
+                s[k + threadIdx.x] = b0 + k + threadIdx.x < nblk ? ploss[b0 + k + threadIdx.x] : 0.0f;
+            __syncthreads();
+            // (zeros follow the last tile)
+            const int q = nblk - b0 < 1024 ? (int)(nblk - b0) : 1024;
+            if (threadIdx.x == 0)
+                for (int k = 0; k < q; k += 64)
+#pragma unroll
+                    for (int u = 0; u < 64; u++) L += s[k + u];
+        }
+        if (threadIdx.x == 0) loss[0] = L * inv_b;
+        return;
+    }
+    const int p = threadIdx.x % kAdamPar, c0 = threadIdx.x / kAdamPar;
+    const int e = blockIdx.x * kAdamPar + p;
+    float g[kSums];
+#pragma unroll
+    for (int q = 0; q < kSums; q++) g[q] = 0.0f;
+    // eight rows of a running sum in flight at a time
+    const float *pe = partial + (e < kNP ? e : 0);
+    for (int64_t b = c0; b < nblk; b += 8 * kAdamLanes) {
+        float x[8][kSums];
+#pragma unroll
+        for (int u = 0; u < 8; u++)
+#pragma unroll
+            for (int q = 0; q < kSums; q++) {
+                const int64_t r = b + u * kAdamLanes + q * kGroups;
+                x[u][q] = pe[(r < nblk ? r : nblk - 1) * kNP];
+            }
+#pragma unroll
+        for (int u = 0; u < 8; u++)
+#pragma unroll
+            for (int q = 0; q < kSums; q++)
+                if (b + u * kAdamLanes + q * kGroups < nblk) g[q] += x[u][q];
+    }
+#pragma unroll
+    for (int q = 0; q < kSums; q++) s[(c0 + q * kGroups) * kAdamPar + p] = g[q];
+    __syncthreads();
+    if (threadIdx.x >= kAdamPar || e >= kNP) return;
+    float t[kAdamLanes];
+#pragma unroll
+    for (int q = 0; q < kAdamLanes; q++) t[q] = s[q * kAdamPar + p];
+#pragma unroll
+    for (int o = 1; o < kAdamLanes; o <<= 1)
+#pragma unroll
+        for (int q = 0; q < kAdamLanes; q += 2 * o) t[q] += t[q + o];
+    const float gs = t[0];
+    if (grad_out) grad_out[e] = gs;
     if (!theta) return;
-    float mm = 0.9f * m[e] + 0.1f * g;
-    float vv = 0.999f * v[e] + 0.001f * g * g;
+    float mm = 0.9f * m[e] + 0.1f * gs;
+    float vv = 0.999f * v[e] + 0.001f * gs * gs;
     m[e] = mm;
     v[e] = vv;
     theta[e] -= lr * (mm / bc1) / (sqrtf(vv / bc2) + 1e-8f);
 }
 
-__global__ void k_hnet_loss(const float *__restrict__ ploss, int64_t nblk, float inv_b, float *out) {
-    if (threadIdx.x != 0) return;
-    float L = 0.0f;
-    for (int64_t b = 0; b < nblk; b++) L += ploss[b];
-    out[0] = L * inv_b;
-}
-
 // Features at radius H: kernel-weighted counts N_w(h) = (4 pi/3) h^3 sum
 // W(r, h) at h = H, H/2, H/4 and raw counts within H and H/2 (self
 // included), see crk.h for the eight definitions. G lanes per particle
-// share the candidates and combine their five sums at the end. When the
-// last build's gather rows are given and the particle's H is the support
-// they were built with, the row is the candidate set (it holds every j with
-// r < H, self aside); otherwise a flattened walk of the support.
+// share the candidates and combine their five sums at the end, and each forms
+// one of the features (one logarithm a lane, where the first lane's six kept
+// the others waiting). When the
+// last build's gather rows are given and the H of a wavefront's particles are
+// the supports they were built with, the rows are the candidate sets (they
+// hold every j with r < H, self aside); otherwise a flattened walk of each
+// support. With the rows
+// tiled through LDS and two partners loading ahead, 64^3 takes 133 us, 212
+// with the entries read one by one.
 template <int G>
 __global__ __launch_bounds__(kBlock) void k_hnet_features(const double4 *__restrict__ posH,
                                                           const int32_t *__restrict__ cbeg,
@@ -323,39 +373,54 @@ __global__ __launch_bounds__(kBlock) void k_hnet_features(const double4 *__restr
     const double h = H[i];
     double s1 = 0.0, s2 = 0.0, s4 = 0.0, c1 = 0.0, c2 = 0.0;
     const double h2 = h * h, ih = 1.0 / h;
-    auto add = [&](double r2) {
-        if (r2 < h2) {
-            double q = sqrt(r2) * ih;
-            double w1 = 1.0 - q, w1_2 = w1 * w1;
-            s1 += w1_2 * w1_2 * w1_2 * (1.0 + q * (6.0 + q * (35.0 / 3.0)));
-            c1 += 1.0;
-            if (r2 < 0.25 * h2) {
-                double q2 = 2.0 * q, w2 = 1.0 - q2, w2_2 = w2 * w2;
-                s2 += w2_2 * w2_2 * w2_2 * (1.0 + q2 * (6.0 + q2 * (35.0 / 3.0)));
-                c2 += 1.0;
-                if (r2 < 0.0625 * h2) {
-                    double q4 = 4.0 * q, w4 = 1.0 - q4, w4_2 = w4 * w4;
-                    s4 += w4_2 * w4_2 * w4_2 * (1.0 + q4 * (6.0 + q4 * (35.0 / 3.0)));
-                }
-            }
+    const auto weight = [](double q) {
+        const double w = 1.0 - q, w2 = w * w;
+        return w2 * w2 * w2 * (1.0 + q * (6.0 + q * (35.0 / 3.0)));
+    };
+    // a partner within h at distance h q
+    const auto add = [&](double r2, double q) {
+        s1 += weight(q);
+        if (r2 < 0.25 * h2) {
+            s2 += weight(2.0 * q);
+            c2 += 1.0;
+            if (r2 < 0.0625 * h2) s4 += weight(4.0 * q);
         }
     };
-    constexpr int NR = flat_ranges<G>();
-    __shared__ int32_t s_b[kBlock / G][NR], s_c[kBlock / G][NR + 1];
-    __shared__ double s_x[kBlock / G][3 * NR];
-    __shared__ AxisTab s_ax[kBlock / G];
-    if (goff && h == pi.w) {
-        if (l == 0) add(0.0);   // self
-        for (int64_t k = goff[i] + l; k < goff[i + 1]; k += G) {
-            const double4 pj = posH[gidx[k]];
-            add(r2_exact(min_image(pi.x - pj.x, v.L, v.hL), min_image(pi.y - pj.y, v.L, v.hL),
-                         min_image(pi.z - pj.z, v.L, v.hL)));
-        }
+    static_assert(G == 8, "a lane per feature");
+    // a wavefront's rows, or the tables of its walks: one or the other, so
+    // that five blocks fit a CU
+    constexpr int NR = flat_ranges<G>(), NG = 64 / G;
+    struct Walks {
+        int32_t b[NG][NR], c[NG][NR + 1];
+        double x[NG][3 * NR];
+        AxisTab ax[NG];
+    };
+    __shared__ union {
+        Walks walks;
+        RowTile<G, 4> rows;
+    } s_w[kBlock / 64];
+    auto &sw = s_w[threadIdx.x >> 6];
+    if (!__any(!goff || h != pi.w)) {
+        if (l == 0) add(0.0, 0.0);   // self
+        const int64_t b = goff[i];
+        const int cnt = (int)(goff[i + 1] - b);
+        const Box box{v.L, 1.0 / v.L};
+        if (l == 0) c1 = (double)(cnt + 1);
+        row_sum<G, 2>(sw.rows, gidx, b, cnt, (int32_t)i, threadIdx.x & 63, [&](int32_t j) { return posH[j]; },
+                      [&](const double4 &pj) {
+            const double r2 = r2_exact(pair_image(pi.x - pj.x, box), pair_image(pi.y - pj.y, box),
+                                       pair_image(pi.z - pj.z, box));
+            add(r2, sqrt_dist(r2) * ih);
+        });
     } else {
-        const int grp = threadIdx.x / G;
-        flat_candidates<G, NR>(posH, cbeg, cend, v, i, pi, h, l, s_b[grp], s_c[grp], s_x[grp], s_ax[grp],
+        const int grp = (threadIdx.x & 63) / G;
+        flat_candidates<G, NR>(posH, cbeg, cend, v, i, pi, h, l, sw.walks.b[grp], sw.walks.c[grp], sw.walks.x[grp],
+                               sw.walks.ax[grp],
                                [&](bool valid, double r2) {
-                                   if (valid) add(r2);
+                                   if (valid && r2 < h2) {
+                                       add(r2, sqrt(r2) * ih);
+                                       c1 += 1.0;
+                                   }
                                    return false;
                                });
     }
@@ -367,18 +432,20 @@ __global__ __launch_bounds__(kBlock) void k_hnet_features(const double4 *__restr
         c1 += __shfl_xor(c1, m, G);
         c2 += __shfl_xor(c2, m, G);
     }
-    if (l != 0) return;
     // (4 pi/3) h^3 * kW h^-3 sum = (4 pi/3) kW sum, the same at every radius
     const double c = 4.0 / 3.0 * kPi * kW;
-    double N1 = c * s1, N2 = c * s2, N4 = c * s4;
-    feat[0 * n + i] = (float)log(N1 / Nres);
-    feat[1 * n + i] = (float)(cbrt(Nres / N1) - 1.0);
-    feat[2 * n + i] = (float)log(8.0 * N2 / Nres);
-    feat[3 * n + i] = (float)log(64.0 * N4 / Nres);
-    feat[4 * n + i] = (float)log(c1 / Nres);
-    feat[5 * n + i] = (float)log(8.0 * c2 / Nres);
-    feat[6 * n + i] = (float)log(h * cbrt((double)n) / v.L);
-    feat[7 * n + i] = 1.0f;
+    const double N1 = c * s1, N2 = c * s2, N4 = c * s4;
+    // lane l forms feature l
+    const double cb = cbrt(l == 6 ? (double)n : Nres / N1);
+    double num = N1;
+    if (l == 2) num = 8.0 * N2;
+    if (l == 3) num = 64.0 * N4;
+    if (l == 4) num = c1;
+    if (l == 5) num = 8.0 * c2;
+    if (l == 6) num = h * cb;
+    float f = l == 1 ? (float)(cb - 1.0) : (float)log(num / (l == 6 ? v.L : Nres));
+    if (l == 7) f = 1.0f;
+    feat[l * n + i] = f;
 }
 
 // seed = H_prev exp(y), clamped to [H_prev / 8, 8 H_prev] and below L/2;
@@ -502,22 +569,18 @@ crk_status crk_hnet_train_step(crk_ctx *c, float *theta, float *adam_m, float *a
     if (!theta) return set_err(c, CRK_ERR_INVALID_ARG, "theta is NULL");
     {
         KTimer kt_(c, "k_hnet_grad");
-        k_hnet_grad<<<(unsigned)((nblk + kBlock / 64 - 1) / (kBlock / 64)), kBlock, 0, c->stream>>>(th_in, feat, target, nb, 1.0f / (float)nb,
-                                                                   part, ploss);
+        k_hnet_grad<<<(unsigned)nblk, kBlock, 0, c->stream>>>(th_in, feat, target, nb, 1.0f / (float)nb, part, ploss);
     }
+    // (the loss goes straight to host memory)
+    float *pin = (float *)c->pinned.p + 256;
     float bc1 = 1.0f - powf(0.9f, (float)step), bc2 = 1.0f - powf(0.999f, (float)step);
     {
         KTimer kt_(c, "k_hnet_adam");
-        k_hnet_adam<<<(kNP * kAdamLanes + kBlock - 1) / kBlock, kBlock, 0, c->stream>>>(
-            part, nblk, lr > 0.0f ? theta : nullptr, adam_m, adam_v, lr, bc1, bc2, grad);
+        k_hnet_adam<<<kAdamBlocks + (loss ? 1 : 0), kBlock, 0, c->stream>>>(
+            part, ploss, nblk, lr > 0.0f ? theta : nullptr, adam_m, adam_v, lr, bc1, bc2, grad, 1.0f / (float)nb, pin);
     }
     CRK_HIP(c, hipGetLastError());
     if (loss) {
-        CRK_TRY(ensure(c, c->misc, 256));
-        float *dl = (float *)c->misc.p + 48;
-        k_hnet_loss<<<1, 64, 0, c->stream>>>(ploss, nblk, 1.0f / (float)nb, dl);
-        float *pin = (float *)c->pinned.p + 256;
-        CRK_HIP(c, hipMemcpyAsync(pin, dl, sizeof(float), hipMemcpyDeviceToHost, c->stream));
         CRK_HIP(c, hipStreamSynchronize(c->stream));
         *loss = pin[0];
     }
@@ -543,16 +606,14 @@ crk_status crk_hnet_train_step_noalloc(crk_ctx *c, float *theta, float *adam_m, 
     float *ploss = part + nblk * kNP;
     {
         KTimer kt_(c, "k_hnet_grad");
-        k_hnet_grad<<<(unsigned)((nblk + kBlock / 64 - 1) / (kBlock / 64)), kBlock, 0, c->stream>>>(
-            theta, feat, target, nb, 1.0f / (float)nb, part, ploss);
+        k_hnet_grad<<<(unsigned)nblk, kBlock, 0, c->stream>>>(theta, feat, target, nb, 1.0f / (float)nb, part, ploss);
     }
     const float bc1 = 1.0f - powf(0.9f, (float)step), bc2 = 1.0f - powf(0.999f, (float)step);
     {
         KTimer kt_(c, "k_hnet_adam");
-        k_hnet_adam<<<(kNP * kAdamLanes + kBlock - 1) / kBlock, kBlock, 0, c->stream>>>(
-            part, nblk, lr > 0.0f ? theta : nullptr, adam_m, adam_v, lr, bc1, bc2, grad);
+        k_hnet_adam<<<kAdamBlocks + (loss ? 1 : 0), kBlock, 0, c->stream>>>(
+            part, ploss, nblk, lr > 0.0f ? theta : nullptr, adam_m, adam_v, lr, bc1, bc2, grad, 1.0f / (float)nb, loss);
     }
-    if (loss) k_hnet_loss<<<1, 64, 0, c->stream>>>(ploss, nblk, 1.0f / (float)nb, loss);
     CRK_HIP(c, hipGetLastError());
     return CRK_OK;
 }

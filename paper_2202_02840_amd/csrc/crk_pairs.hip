@@ -22,6 +22,7 @@
 #include <type_traits>
 
 #include "crk_internal.h"
+#include "crk_rows.h"
 
 namespace crk {
 namespace {
@@ -211,94 +212,11 @@ __device__ __forceinline__ void stage_load(const void *__restrict__ rec, bool wi
         __builtin_amdgcn_global_load_lds((Global)((const char *)rec + off[s]), (Lds)(st.rec + s * Staged<CH>::kStep), 16, 0, 0);
 }
 
-// wait for the loads
-__device__ __forceinline__ void stage_wait() {
-    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
-    __builtin_amdgcn_sched_barrier(0);
-}
-
 // 16-byte piece k of this lane's record
 template <int CH>
 __device__ __forceinline__ float4 stage_piece(const Staged<CH> &st, int lane, int k) {
     const int c = lane & (CH - 1);
     return *(const float4 *)(st.rec + (c * Staged<CH>::kStep + (lane - c) * 16) + 16 * k);
-}
-
-// The entries l, l + G, ... below cnt of a row: term(load(k)) for each in
-// turn, the next D (1 or 2) partners' records loading meanwhile (load takes
-// any k).
-template <int G, int D, typename Load, typename Term>
-__device__ __forceinline__ void row_terms(int l, int cnt, Load &&load, Term &&term) {
-    auto r0 = load(l);
-    if constexpr (D == 1) {
-        for (int k = l; k < cnt; k += G) {
-            const auto a = r0;
-            r0 = load(k + G);
-            term(a);
-        }
-    } else {
-        auto r1 = load(l + G);
-        for (int k = l; k < cnt; k += 2 * G) {
-            const auto a = r0;
-            r0 = load(k + 2 * G);
-            term(a);
-            const auto b = r1;
-            r1 = load(k + 3 * G);
-            if (k + G < cnt) term(b);
-        }
-    }
-}
-
-// Tiles of the gather rows of a wavefront's 64 / G groups in LDS. Read from
-// memory as the loop goes, every step of many rows would meet the first line
-// of some row's next 32 entries, and a wavefront's loads complete in order,
-// so that each step would wait for HBM whatever is prefetched. One load
-// instruction brings the next 4 G entries of each row.
-template <int G>
-struct RowTile {
-    static constexpr int kLoads = G < 16 ? 8 : 128 / G;
-    static constexpr int kTile = 4 * G * kLoads - (G < 2 ? 4 : 2 * G);   // entries used: any alignment, whole steps
-    __align__(16) int32_t e[kLoads * 256];
-};
-
-// the tile from entry k0 (a multiple of four) of the row at gidx + b4 + al of
-// this lane's group, b4 a multiple of four; up to three entries past the row
-// are read
-template <int G>
-__device__ __forceinline__ void fetch_tile(RowTile<G> &t, const int32_t *__restrict__ gidx, int64_t b4, int end,
-                                           int k0, int l) {
-    const int32_t *p = gidx + b4 + k0 + 4 * l;
-    int o = k0 + 4 * l;
-#pragma unroll
-    for (int q = 0; q < RowTile<G>::kLoads; q++, p += 4 * G, o += 4 * G)
-        if (o < end)
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)p,
-                                             (__attribute__((address_space(3))) void *)(t.e + q * 256), 16, 0, 0);
-    stage_wait();
-}
-
-// word of the tile, from its group's first on, that holds entry x (counted from
-// its first, aligned, entry)
-template <int G>
-__device__ __forceinline__ uint32_t tile_word(uint32_t x) {
-    return x / (4 * G) * 256 + x % (4 * G);
-}
-
-// The sum over the row gidx[b .. b + cnt) of this lane's group: term(load(j))
-// over the lane's entries j, the next D (1 or 2) partners' records loading
-// meanwhile. self: any particle, loaded past the end.
-template <int G, int D, typename Load, typename Term>
-__device__ __forceinline__ void row_sum(RowTile<G> &t, const int32_t *__restrict__ gidx, int64_t b, int cnt,
-                                        int32_t self, int lane, Load &&load, Term &&term) {
-    const int al = (int)(b & 3), l = lane % G;
-    for (int k0 = 0; k0 < cnt; k0 += RowTile<G>::kTile) {
-        __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): the last tile's reads are done
-        __builtin_amdgcn_sched_barrier(0);
-        fetch_tile<G>(t, gidx, b - al, cnt + al, k0, l);
-        const int end = min(cnt - k0, RowTile<G>::kTile);
-        const int32_t *const e = t.e + (lane - l) * 4;
-        row_terms<G, D>(l, end, [&](int k) { return load(k < end ? e[tile_word<G>(k + al)] : self); }, term);
-    }
 }
 
 // a . b with its rounding spelled out: in a sum of products the compiler
