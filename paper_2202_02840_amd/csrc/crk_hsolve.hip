@@ -24,7 +24,19 @@ constexpr int kPoolCap = 4096;
 constexpr int kRegSlots8 = 40;
 constexpr int kRegSlots16 = 20;
 
-// n_i(H) by a group of G lanes: the group walks i's cells together, lanes
+// (4 pi / 3) H^3 n_i(H), the neighbour count of eq. (hi), of an unnormalised sum
+// of weights: the H^3 of the kernel's normalisation cancels
+__device__ __forceinline__ double count_of(double s) { return (4.0 * kPi / 3.0) * kW * s; }
+
+// 1 / x to FP64 rounding for x well inside the range: a hardware seed and two
+// Newton steps (a division tests for what cannot be here)
+__device__ __forceinline__ double recip(double x) {
+    double y = __builtin_amdgcn_rcp(x);
+    y = fma(fma(-x, y, 1.0), y, y);
+    return fma(fma(-x, y, 1.0), y, y);
+}
+
+// The count at H by a group of G lanes: the group walks i's cells together, lanes
 // take a cell's particles G at a time, and the partial sums are combined
 // with cross-lane shuffles (every lane ends with the same total).
 template <int G>
@@ -32,7 +44,7 @@ __device__ __forceinline__ double nsum_group(const double4 *__restrict__ posH,
                                              const int32_t *__restrict__ cbeg,
                                              const int32_t *__restrict__ cend, const Levels &v,
                                              int64_t i, const double4 &pi, double H, int l) {
-    const double H2 = H * H, invH = 1.0 / H;
+    const double H2 = H * H, invH = recip(H);
     double s = 0.0;
     int k = level_for(H, v);
     int nck = 1 << (v.bits - k);
@@ -67,7 +79,7 @@ __device__ __forceinline__ double nsum_group(const double4 *__restrict__ posH,
     }
 #pragma unroll
     for (int m = G / 2; m >= 1; m >>= 1) s += __shfl_xor(s, m, G);
-    return kW * invH * invH * invH * s;
+    return count_of(s);
 }
 
 // Candidate row of particle i: the distance r of every j within R (self
@@ -129,6 +141,14 @@ __device__ __forceinline__ int build_row(const double4 *__restrict__ posH,
     return c;
 }
 
+// LDS of one group's flattened walk
+template <int G>
+struct FlatLists {
+    double x[3 * flat_ranges<G>()];
+    AxisTab ax;
+    int32_t b[flat_ranges<G>()], c[flat_ranges<G>() + 1];
+};
+
 // The same row by the flattened walk (flat_candidates): the loads of
 // different cells overlap. Candidate order differs from build_row; the rows
 // hold the same set.
@@ -137,14 +157,13 @@ __device__ __forceinline__ int build_row_flat(const double4 *__restrict__ posH,
                                               const int32_t *__restrict__ cbeg,
                                               const int32_t *__restrict__ cend, const Levels &v,
                                               int64_t i, const double4 &pi, double R, int cap,
-                                              double *row, int l, int32_t *sb, int32_t *sc,
-                                              double *sx, AxisTab &tab) {
+                                              double *row, int l, FlatLists<G> &fl) {
     const double R2 = R * R;
     const int gshift = (threadIdx.x & 63) - l;
-    const uint64_t gmask = ((uint64_t)1 << G) - 1;
+    const uint64_t gmask = G == 64 ? ~0ull : ((uint64_t)1 << (G & 63)) - 1;
     const uint64_t below = ((uint64_t)1 << l) - 1;
     int c = 0;
-    flat_candidates<G, flat_ranges<G>()>(posH, cbeg, cend, v, i, pi, R, l, sb, sc, sx, tab,
+    flat_candidates<G, flat_ranges<G>()>(posH, cbeg, cend, v, i, pi, R, l, fl.b, fl.c, fl.x, fl.ax,
                                          [&](bool valid, double r2) {
         const bool hit = valid && r2 < R2;
         const uint64_t hm = (__ballot(hit) >> gshift) & gmask;
@@ -165,11 +184,11 @@ __device__ __forceinline__ double w_c4(double q) {
     return t2 * t2 * t2 * (1.0 + q * (6.0 + q * (35.0 / 3.0)));
 }
 
-// n_i(H) from a candidate row of distances (valid while H <= the row's
+// The count at H from a candidate row of distances (valid while H <= the row's
 // radius); rows that are not a multiple of 4G long finish one slot at a time
 template <int G>
 __device__ __forceinline__ double nsum_row(const double *__restrict__ row, int c, double H, int l) {
-    const double invH = 1.0 / H;
+    const double invH = recip(H);
     double s = 0.0;
     int k = l;
     for (; k + 3 * G < c; k += 4 * G) {
@@ -179,7 +198,7 @@ __device__ __forceinline__ double nsum_row(const double *__restrict__ row, int c
     for (; k < c; k += G) s += w_c4(row[k] * invH);
 #pragma unroll
     for (int m = G / 2; m >= 1; m >>= 1) s += __shfl_xor(s, m, G);
-    return kW * invH * invH * invH * s;
+    return count_of(s);
 }
 
 // Delta = x^(1/3) for x > 0 (x = Nres / N lies between ~1e-6 and ~3): an FP32
@@ -207,15 +226,15 @@ struct HsArgs {
 
 // Takes updates of eq. (thacker) from H until stop or R updates; returns the
 // state (0 running, 1 converged, 2 hit max_iter, 3 support reached L/2).
-// NS(H) gives n_i(H) and is the only part that differs between passes.
-template <typename NSum>
+// count(H) gives the neighbour count and is the only part that differs between
+// passes.
+template <typename Count>
 __device__ __forceinline__ int thacker_updates(const HsArgs &a, double &H, int &it, int R,
-                                               double Rmax, bool stop_outside, NSum &&NS) {
+                                               double Rmax, bool stop_outside, Count &&count) {
     for (int r = 0; r < R; r++) {
         if (stop_outside && !(H <= Rmax)) return 0;   // a new row next round
-        const double ns = NS(H);
-        const double N = (4.0 * kPi / 3.0) * H * H * H * ns;
-        const double x = a.Nres / N;   // Delta^3
+        const double N = count(H);
+        const double x = a.Nres * recip(N);   // Delta^3
         const double D = cube_root(x);
         const double lam = D < 1.0 ? 0.2 * (1.0 + D * D) : 0.2 * (1.0 + N * a.inv_Nres);
         const double Hn = H * (1.0 - lam + lam * D);
@@ -232,18 +251,15 @@ __device__ __forceinline__ int thacker_updates(const HsArgs &a, double &H, int &
 // A row at f H for particle i (which then serves every update with H <= f H
 // without a cell walk); when f H holds more candidates than the row, a row
 // just past H is tried (it still serves the updates that shrink H).
-// (FLAT: the flattened walk, with the group's LDS lists sb, sc, sx and axis
-// tables)
-template <int G, bool FLAT = false>
+// (with fl the flattened walk)
+template <int G>
 __device__ __forceinline__ int make_row(const HsArgs &a, int64_t i, const double4 &pi, double H,
                                         int rcap, double *row, double &Rmax, int l,
-                                        int32_t *sb = nullptr, int32_t *sc = nullptr,
-                                        double *sx = nullptr, AxisTab *tab = nullptr) {
+                                        FlatLists<G> *fl = nullptr) {
     auto build = [&](double R) {
-        if constexpr (FLAT)
-            return build_row_flat<G>(a.posH, a.cbeg, a.cend, a.v, i, pi, R, rcap, row, l, sb, sc, sx, *tab);
-        else
-            return build_row<G>(a.posH, a.cbeg, a.cend, a.v, i, pi, R, rcap, row, l);
+        if constexpr (G >= 4)
+            if (fl) return build_row_flat<G>(a.posH, a.cbeg, a.cend, a.v, i, pi, R, rcap, row, l, *fl);
+        return build_row<G>(a.posH, a.cbeg, a.cend, a.v, i, pi, R, rcap, row, l);
     };
     Rmax = a.f * H;
     int c = build(Rmax);
@@ -324,26 +340,59 @@ __device__ __forceinline__ double dpp_f64(double x) {
     return __hiloint2double(hi, lo);
 }
 
-// Sum over an aligned group of G = 8 or 16 lanes; every lane ends with the
+// Sum over an aligned group of G = 8, 16 or 64 lanes; every lane ends with the
 // same total (each step adds commuting pairs): swap neighbours, swap pairs,
-// mirror the 8-lane halves, mirror the 16-lane row
+// mirror the 8-lane halves, mirror the 16-lane row, then the rows
 template <int G>
 __device__ __forceinline__ double group_sum(double s) {
-    static_assert(G == 8 || G == 16, "DPP group sum covers 8 or 16 lanes");
+    static_assert(G == 8 || G == 16 || G == 64, "group sum covers 8, 16 or 64 lanes");
     s += dpp_f64<0xB1>(s);   // quad_perm(1,0,3,2)
     s += dpp_f64<0x4E>(s);   // quad_perm(2,3,0,1)
     s += dpp_f64<0x141>(s);  // row_half_mirror
-    if constexpr (G == 16) s += dpp_f64<0x140>(s);  // row_mirror
+    if constexpr (G >= 16) s += dpp_f64<0x140>(s);  // row_mirror
+    if constexpr (G == 64) {
+        s += __shfl_xor(s, 16, 64);
+        s += __shfl_xor(s, 32, 64);
+    }
     return s;
 }
 
-// Narrow pass with the row held in registers: the round loads each
-// particle's row once (slot s of lane l holds candidate s G + l, empty slots
-// a distance of 2 Rmax, whose weight is zero) and every update sums from
-// registers; the same hand-over rules as the narrow pass of round_body.
+// A row into registers: slot s of lane l holds candidate s G + l, empty slots a
+// distance of 2 Rmax, whose weight is zero (c above S G loads nothing).
+// Returns the slots of the longest row of the wavefront's groups (of those
+// here: some may be elsewhere).
+template <int G, int S>
+__device__ __forceinline__ int load_row(const double *__restrict__ row, int c, double Rmax, int l, double (&r)[S]) {
+    const double pad = 2.0 * Rmax;
+    if (c > S * G) c = 0;
+#pragma unroll
+    for (int s = 0; s < S; s++) {
+        const int q = s * G + l;
+        r[s] = q < c ? row[q] : pad;
+    }
+    int most = 0;
+    for (uint64_t left = __ballot(l == 0); left; left &= left - 1)
+        most = max(most, __builtin_amdgcn_readlane(c, __ffsll((unsigned long long)left) - 1));
+    return (most + G - 1) / G;
+}
+
+// the count at h from it
+template <int G, int S>
+__device__ __forceinline__ double count_row(const double (&r)[S], int most, double h) {
+    const double invH = recip(h);
+    double acc = 0.0;
+#pragma unroll
+    for (int s = 0; s < S; s++)
+        if (s < most) acc += w_c4(r[s] * invH);   // (uniform; a break would make this a loop over memory)
+    return count_of(group_sum<G>(acc));
+}
+
+// Narrow pass with the row held in registers: the round loads each particle's
+// row once and every update sums from registers; the same hand-over rules as
+// the narrow pass of round_body.
 template <int G, int S>
 __device__ __forceinline__ void narrow_body(const HsArgs &a, const int32_t *__restrict__ list,
-                                            int64_t k, int l, int R) {
+                                            int64_t k, int l, int R, FlatLists<G> &fl) {
     const int64_t i = list[k];
     const double4 pi = a.posH[i];
     double H = a.H[i];
@@ -352,12 +401,7 @@ __device__ __forceinline__ void narrow_body(const HsArgs &a, const int32_t *__re
     double Rmax = a.Rlist[i];
     double *row = a.rows + (size_t)i * a.cap;
     if (!(c <= a.cap && H <= Rmax)) {
-        constexpr int NR = flat_ranges<G>();
-        __shared__ int32_t s_b[kBlock / G][NR], s_c[kBlock / G][NR + 1];
-        __shared__ double s_x[kBlock / G][3 * NR];
-        __shared__ AxisTab s_ax[kBlock / G];
-        const int grp = (threadIdx.x & (kBlock - 1)) / G;
-        c = make_row<G, true>(a, i, pi, H, a.cap, row, Rmax, l, s_b[grp], s_c[grp], s_x[grp], &s_ax[grp]);
+        c = make_row<G>(a, i, pi, H, a.cap, row, Rmax, l, &fl);
         if (l == 0) {
             a.rcnt[i] = c;
             a.Rlist[i] = Rmax;
@@ -368,22 +412,36 @@ __device__ __forceinline__ void narrow_body(const HsArgs &a, const int32_t *__re
         return;
     }
     double rr[S];
-    const double pad = 2.0 * Rmax;
-#pragma unroll
-    for (int s = 0; s < S; s++) {
-        const int q = s * G + l;
-        rr[s] = q < c ? row[q] : pad;
+    const int most = load_row<G>(row, c, Rmax, l, rr);
+    const int st = thacker_updates(a, H, it, R, Rmax, true, [&](double h) { return count_row<G>(rr, most, h); });
+    if (l == 0) {
+        a.H[i] = H;
+        a.iters[i] = it;
+        a.state[i] = st;
     }
-    const int st = thacker_updates(a, H, it, R, Rmax, true, [&](double h) {
-        const double invH = 1.0 / h;
-        double acc = 0.0;
-#pragma unroll
-        for (int s = 0; s < S; s++) {
-            if (!__any(s * G < c)) break;
-            acc += w_c4(rr[s] * invH);
-        }
-        return kW * invH * invH * invH * group_sum<G>(acc);
+}
+
+// Wide pass, a wavefront a particle: as round_body with the pool, the row by
+// the flattened walk, and in registers where they hold it. A round lasts as
+// long as its slowest particle: cell after cell and the row from memory, the
+// twelve wide particles of a late round took 76 us.
+template <int S>
+__device__ __forceinline__ void wide_body(const HsArgs &a, const int32_t *__restrict__ list, int64_t k, int l,
+                                          int R, double *pool, int pcap, FlatLists<64> &fl) {
+    const int64_t i = list[k];
+    const double4 pi = a.posH[i];
+    double H = a.H[i];
+    int it = a.iters[i];
+    double *row = pool + (size_t)k * pcap;
+    double Rmax;
+    const int c = make_row<64>(a, i, pi, H, pcap, row, Rmax, l, &fl);
+    double rr[S];
+    const int most = load_row<64>(row, c, Rmax, l, rr);
+    int st = thacker_updates(a, H, it, R, Rmax, false, [&](double h) {
+        if (c > pcap || !(h <= Rmax)) return nsum_group<64>(a.posH, a.cbeg, a.cend, a.v, i, pi, h, l);
+        return c <= 64 * S ? count_row<64>(rr, most, h) : nsum_row<64>(row, c, h, l);
     });
+    if (st == 0 && c > a.cap) st = 4;   // (a row that fits goes back to the narrow pass)
     if (l == 0) {
         a.H[i] = H;
         a.iters[i] = it;
@@ -401,7 +459,8 @@ __global__ __launch_bounds__(kBlock) void k_hsolve_round(HsArgs a, const int32_t
     round_body<G>(a, list, k, (int)(gid % G), R, pool, pcap, defer);
 }
 
-// One launch for both passes: the first nbw blocks (a multiple of 8, so the
+// One launch for both passes. Bound by latency and FP64 issue: 48^3, a round
+// of 12 updates for all 110592 particles in 240 us. The first nbw blocks (a multiple of 8, so the
 // XCD of a narrow block is the one xcd_block assumes) take the wide list with
 // a wavefront per particle and are dispatched first, since their particles
 // are the slow ones; the other blocks take the narrow list with register
@@ -411,58 +470,100 @@ __global__ __launch_bounds__(kBlock) void k_hsolve_both(HsArgs a, const int32_t 
                                                         int64_t mn, int Rn, const int32_t *__restrict__ lw,
                                                         int64_t mw, int Rw, int64_t nbw, double *pool,
                                                         int pcap) {
+    __shared__ union {
+        FlatLists<G> narrow[kBlock / G];
+        FlatLists<64> wide[kBlock / 64];
+    } s_fl;
     if ((int64_t)blockIdx.x < nbw) {
         const int64_t gid = (int64_t)blockIdx.x * kBlock + threadIdx.x;
         const int64_t k = gid / 64;
         if (k >= mw) return;
-        round_body<64>(a, lw, k, (int)(gid % 64), Rw, pool, pcap, 0);
+        wide_body<kRegSlots16>(a, lw, k, (int)(gid % 64), Rw, pool, pcap, s_fl.wide[threadIdx.x / 64]);
         return;
     }
     const int64_t gid = xcd_block(blockIdx.x - nbw, gridDim.x - nbw) * kBlock + threadIdx.x;
     const int64_t k = gid / G;
     if (k >= mn) return;
-    narrow_body<G, S>(a, ln, k, (int)(gid % G), Rn);
+    narrow_body<G, S>(a, ln, k, (int)(gid % G), Rn, s_fl.narrow[threadIdx.x / G]);
 }
 
-__global__ __launch_bounds__(kBlock) void k_hs_init(int64_t n, int32_t *list, int32_t *iters, int32_t *state,
-                                                    int32_t *rcnt, int cap) {
+// before the first round: everyone in the narrow list, no row; stopped: none
+__global__ __launch_bounds__(kBlock) void k_hs_init(int64_t n, int32_t *list, int32_t *iters, int32_t *rcnt, int cap,
+                                                    int32_t *stopped) {
     int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (i < 2) stopped[i] = 0;
     if (i >= n) return;
     list[i] = (int32_t)i;
     iters[i] = 0;
-    state[i] = 0;
     if (rcnt) rcnt[i] = cap + 1;   // no candidate row yet
 }
 
-// run[k]: 1 when list[k] runs on in the narrow pass, 1 << 32 when it runs on
-// in the wide pass (one scan then counts both classes)
-__global__ __launch_bounds__(kBlock) void k_hs_running(const int32_t *__restrict__ list, int64_t m,
-                                                       const int32_t *__restrict__ state, int64_t *run) {
-    int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (k < m) {
-        const int s = state[list[k]];
-        run[k] = s == 0 ? 1 : (s == 4 ? ((int64_t)1 << 32) : 0);
+// After a round, the particles of the list that run on, counted for every
+// kHsBlock of them: the narrow pass in the low half, the wide pass in the high
+// half. stopped[0] and [1] gain those at max_iter and those whose support
+// reached L/2.
+constexpr int kHsBlock = 1024;
+__global__ __launch_bounds__(kHsBlock) void k_hs_sums(const int32_t *__restrict__ list, int64_t m,
+                                                      const int32_t *__restrict__ state, int64_t *sums,
+                                                      int32_t *stopped) {
+    __shared__ int64_t s[kHsBlock / 64];
+    const int64_t k = (int64_t)blockIdx.x * kHsBlock + threadIdx.x;
+    const int st = k < m ? state[list[k]] : 1;
+    if (st == 2 || st == 3) atomicAdd(&stopped[st - 2], 1);   // few
+    const int64_t w = __popcll(__ballot(st == 0)) + ((int64_t)__popcll(__ballot(st == 4)) << 32);
+    if ((threadIdx.x & 63) == 0) s[threadIdx.x >> 6] = w;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int64_t t = 0;
+        for (int q = 0; q < kHsBlock / 64; q++) t += s[q];
+        sums[blockIdx.x] = t;
     }
-    if (k == m) run[m] = 0;
 }
 
-// running particles to out: the narrow ones first, then the wide ones
-__global__ __launch_bounds__(kBlock) void k_hs_compact(const int32_t *__restrict__ list, int64_t m,
-                                                       const int64_t *__restrict__ pos, int32_t *out) {
-    int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (k >= m) return;
-    const int64_t d = pos[k + 1] - pos[k];
-    if (d == 1) out[pos[k] & 0xffffffff] = list[k];
-    else if (d != 0) out[(pos[m] & 0xffffffff) + (pos[k] >> 32)] = list[k];
-}
-
-__global__ __launch_bounds__(kBlock) void k_hs_count(const int32_t *__restrict__ state, int64_t n,
-                                                     unsigned long long *cnt) {
-    int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i >= n) return;
-    int s = state[i];
-    if (s == 2) atomicAdd(&cnt[0], 1ull);
-    if (s == 3) atomicAdd(&cnt[1], 1ull);
+// Those particles to out, the narrow ones first, in the order of the list;
+// every block adds up the counts before its own. host: both totals, then
+// stopped[0] and [1], for the host to read once the stream is done.
+__global__ __launch_bounds__(kHsBlock) void k_hs_compact(const int32_t *__restrict__ list, int64_t m,
+                                                         const int32_t *__restrict__ state,
+                                                         const int64_t *__restrict__ sums, int32_t *out,
+                                                         const int32_t *__restrict__ stopped, int64_t *host) {
+    constexpr int W = kHsBlock / 64;
+    __shared__ int64_t s_all[W], s_before[W], s_here[W];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t k = (int64_t)blockIdx.x * kHsBlock + threadIdx.x;
+    int64_t all = 0, before = 0;
+    for (int64_t b = threadIdx.x; b < gridDim.x; b += kHsBlock) {
+        const int64_t t = sums[b];
+        all += t;
+        if (b < blockIdx.x) before += t;
+    }
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) {
+        all += __shfl_xor(all, o, 64);
+        before += __shfl_xor(before, o, 64);
+    }
+    const int32_t i = k < m ? list[k] : 0;
+    const int st = k < m ? state[i] : 1;
+    const uint64_t mn = __ballot(st == 0), mw = __ballot(st == 4);
+    if (lane == 0) {
+        s_all[wave] = all;
+        s_before[wave] = before;
+        s_here[wave] = __popcll(mn) + ((int64_t)__popcll(mw) << 32);
+    }
+    __syncthreads();
+    int64_t total = 0, at = 0;
+    for (int q = 0; q < W; q++) {
+        total += s_all[q];
+        at += s_before[q] + (q < wave ? s_here[q] : 0);
+    }
+    const uint64_t below = ((uint64_t)1 << lane) - 1;
+    if (st == 0) out[(at & 0xffffffff) + __popcll(mn & below)] = i;
+    else if (st == 4) out[(total & 0xffffffff) + (at >> 32) + __popcll(mw & below)] = i;
+    if (k == 0) {
+        host[0] = total;
+        host[1] = stopped[0];
+        host[2] = stopped[1];
+    }
 }
 
 __global__ __launch_bounds__(kBlock) void k_set_H2(double4 *posH, const double *H, int64_t n) {
@@ -523,12 +624,14 @@ crk_status crk_hsolve(crk_ctx *c, double Nres, double tol, int32_t max_iter, dou
     Levels v = levels(c);
     CRK_TRY(ensure(c, c->hs_list, (size_t)2 * n * sizeof(int32_t)));
     CRK_TRY(ensure(c, c->hs_state, (size_t)n * sizeof(int32_t)));
-    CRK_TRY(ensure(c, c->hs_pos, (size_t)(n + 1) * sizeof(int64_t)));
+    // the blocks' counts of running particles, then the two counts of stopped ones
+    const int64_t nsums = (n + kHsBlock - 1) / kHsBlock;
+    CRK_TRY(ensure(c, c->hs_pos, (size_t)(nsums + 1) * sizeof(int64_t)));
     CRK_TRY(ensure(c, c->hs_iters, (size_t)n * sizeof(int32_t)));
     int32_t *la = (int32_t *)c->hs_list.p, *lb = la + n;
-    int32_t *state = (int32_t *)c->hs_state.p;
     int32_t *it = iters ? iters : (int32_t *)c->hs_iters.p;
-    int64_t *pos = (int64_t *)c->hs_pos.p;
+    int64_t *sums = (int64_t *)c->hs_pos.p;
+    int32_t *state = (int32_t *)c->hs_state.p, *stopped = (int32_t *)(sums + nsums);
     const unsigned nb = (unsigned)((n + kBlock - 1) / kBlock);
     // candidate rows (positions do not move during the iteration); each
     // particle's first round builds its row
@@ -544,7 +647,7 @@ crk_status crk_hsolve(crk_ctx *c, double Nres, double tol, int32_t max_iter, dou
         rcnt = (int32_t *)c->hs_rcnt.p;
         Rl = (double *)c->hs_R.p;
     }
-    k_hs_init<<<nb, kBlock, 0, c->stream>>>(n, la, it, state, rcnt, cap);
+    k_hs_init<<<nb, kBlock, 0, c->stream>>>(n, la, it, rcnt, cap, stopped);
     CRK_HIP(c, hipGetLastError());
     int64_t mn = n, mw = 0;   // narrow and wide particles still running
     const int pcap = kPoolCap < 8 * cap ? 8 * cap : kPoolCap;
@@ -557,38 +660,42 @@ crk_status crk_hsolve(crk_ctx *c, double Nres, double tol, int32_t max_iter, dou
     {
         KTimer kt_(c, "k_hsolve");
         while (mn + mw > 0) {
-            // few particles left (the slowly contracting tail): give each one
-            // more lanes so the device stays busy, and run longer rounds
+            const int32_t *lw = la + mn;   // the wide list
+            // few particles left (the slowly contracting tail): longer rounds,
+            // and, where rows are not in registers, more lanes for each. A
+            // register row answers an update in 1.7 us whatever the number of
+            // particles (48^3: the 32k, 1300 and 24 of the last rounds took 320,
+            // 530 and 42 us with 32 and 64 lanes and rows from memory, where a
+            // support that has left its row walks the cells at every update, and
+            // 136, 93 and 82 with 16)
+            const bool reg = rows && ((G == 8 && cap <= 8 * kRegSlots8) || (G == 16 && cap <= 16 * kRegSlots16));
             int Gr = G;
-            while (Gr < 64 && mn * Gr < (int64_t)1 << 19) Gr *= 2;
-            const int Rn = Gr > G ? 4 * c->hs_round : c->hs_round;
+            while (!reg && Gr < 64 && mn * Gr < (int64_t)1 << 19) Gr *= 2;
+            const int Rn = mn * G < (int64_t)1 << 19 ? 4 * c->hs_round : c->hs_round;
             // the wide pass runs longer rounds: its particles are few and slow
             const int Rw = 4 * c->hs_round;
             const int64_t mw0 = mw < prow ? mw : prow;   // wide particles in the first launch
             if (mw0 > 0) CRK_TRY(ensure(c, c->hs_pool, (size_t)mw0 * pcap * sizeof(double)));
             double *pool = (double *)c->hs_pool.p;
-            const bool reg8 = rows && Gr == 8 && cap <= 8 * kRegSlots8;
-            const bool reg16 = rows && Gr == 16 && cap <= 16 * kRegSlots16;
-            if (mn > 0 && reg8)
-                CRK_TRY((hsolve_both<8, kRegSlots8>(c, a, la, mn, Rn, la + mn, mw0, Rw, pool, pcap)));
-            else if (mn > 0 && reg16)
-                CRK_TRY((hsolve_both<16, kRegSlots16>(c, a, la, mn, Rn, la + mn, mw0, Rw, pool, pcap)));
+            const bool reg8 = reg && G == 8, reg16 = reg && G == 16;
+            if (reg8)
+                CRK_TRY((hsolve_both<8, kRegSlots8>(c, a, la, mn, Rn, lw, mw0, Rw, pool, pcap)));
+            else if (reg16)
+                CRK_TRY((hsolve_both<16, kRegSlots16>(c, a, la, mn, Rn, lw, mw0, Rw, pool, pcap)));
             else {
                 if (mn > 0) CRK_TRY(hsolve_round(c, a, Gr, la, mn, Rn, nullptr, 0, rows && Gr < 64));
-                if (mw0 > 0) CRK_TRY(hsolve_round(c, a, 64, la + mn, mw0, Rw, pool, pcap, 0));
+                if (mw0 > 0) CRK_TRY(hsolve_round(c, a, 64, lw, mw0, Rw, pool, pcap, 0));
             }
             // wide particles beyond the pool: further launches reusing it
             for (int64_t w0 = mw0; w0 < mw; w0 += prow) {
                 const int64_t mc = mw - w0 < prow ? mw - w0 : prow;
-                CRK_TRY(hsolve_round(c, a, 64, la + mn + w0, mc, Rw, pool, pcap, 0));
+                CRK_TRY(hsolve_round(c, a, 64, lw + w0, mc, Rw, pool, pcap, 0));
             }
             const int64_t m = mn + mw;
-            const unsigned mb = (unsigned)((m + 1 + kBlock - 1) / kBlock);
-            k_hs_running<<<mb, kBlock, 0, c->stream>>>(la, m, state, pos);
-            CRK_TRY(scan_exclusive_i64(c, pos, pos, m + 1));
-            k_hs_compact<<<mb, kBlock, 0, c->stream>>>(la, m, pos, lb);
+            const unsigned mb = (unsigned)((m + kHsBlock - 1) / kHsBlock);
+            k_hs_sums<<<mb, kHsBlock, 0, c->stream>>>(la, m, state, sums, stopped);
+            k_hs_compact<<<mb, kHsBlock, 0, c->stream>>>(la, m, state, sums, lb, stopped, pin);
             CRK_HIP(c, hipGetLastError());
-            CRK_HIP(c, hipMemcpyAsync(pin, pos + m, sizeof(int64_t), hipMemcpyDeviceToHost, c->stream));
             CRK_HIP(c, hipStreamSynchronize(c->stream));
             mn = pin[0] & 0xffffffff;
             mw = pin[0] >> 32;
@@ -597,22 +704,16 @@ crk_status crk_hsolve(crk_ctx *c, double Nres, double tol, int32_t max_iter, dou
             lb = t;
         }
     }
-    CRK_TRY(ensure(c, c->misc, 256));
-    unsigned long long *cnt = (unsigned long long *)c->misc.p + 6;
-    CRK_TRY(zero_async(c, cnt, 4));
-    k_hs_count<<<nb, kBlock, 0, c->stream>>>(state, n, cnt);
-    unsigned long long *pc = (unsigned long long *)c->pinned.p + 16;
-    CRK_HIP(c, hipMemcpyAsync(pc, cnt, 2 * sizeof(unsigned long long), hipMemcpyDeviceToHost, c->stream));
-    CRK_HIP(c, hipStreamSynchronize(c->stream));
-    if (n_unconverged) *n_unconverged = (int64_t)pc[0];
-    if (pc[1]) return set_err(c, CRK_ERR_SUPPORT, "%llu supports reached L/2", pc[1]);
+    const int64_t at_max = pin[1], at_half = pin[2];
+    if (n_unconverged) *n_unconverged = at_max;
+    if (at_half) return set_err(c, CRK_ERR_SUPPORT, "%lld supports reached L/2", (long long)at_half);
     // the lists no longer match the support radii
     c->built = 0;
     c->have_V = 0;
     c->vol_ready = 0;
     k_set_H2<<<nb, kBlock, 0, c->stream>>>((double4 *)c->posH.p, H_inout, n);
     CRK_HIP(c, hipGetLastError());
-    if (pc[0]) return CRK_WARN_NOT_CONVERGED;
+    if (at_max) return CRK_WARN_NOT_CONVERGED;
     return CRK_OK;
 }
 

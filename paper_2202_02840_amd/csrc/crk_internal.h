@@ -303,7 +303,7 @@ __device__ __forceinline__ double cell_gap(double p, int k, double cs) {
 constexpr int kRanges = 32;
 template <int G>
 __host__ __device__ constexpr int flat_ranges() {
-    return 2 * G < 8 ? 8 : (2 * G > kRanges ? kRanges : 2 * G);
+    return 2 * G < 8 ? 8 : (G > kRanges ? G : 2 * G > kRanges ? kRanges : 2 * G);
 }
 
 // exclusive prefix sum of x over a group of G lanes (total to every lane)
@@ -477,7 +477,7 @@ __device__ __forceinline__ void flat_candidates(const double4 *__restrict__ posH
                                                 Visit &&visit) {
     static_assert(G >= 4 && G <= NR, "the flattened walk needs 4..NR lanes");
     const int gshift = (threadIdx.x & 63) - l;
-    const uint64_t gmask = ((uint64_t)1 << G) - 1;
+    const uint64_t gmask = G == 64 ? ~0ull : ((uint64_t)1 << (G & 63)) - 1;
     const uint64_t below = ((uint64_t)1 << l) - 1;
     const int k = level_for(R, v);
     const int nck = 1 << (v.bits - k);
