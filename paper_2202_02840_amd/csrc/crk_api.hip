@@ -281,7 +281,7 @@ crk_status crk_workspace_estimate(const crk_ctx *c, int64_t n, int32_t nboxes,
     double t = 0.0;
     // build (crk_build_cells, any use): checks, sort, tables, lists
     const double nblk = std::min(std::ceil(N / 256.0), 1024.0);
-    t += held(nblk * 24.0 + 64.0) + held(256.0) + held((nboxes + 1) * 8.0);
+    t += held(nblk * 28.0 + 64.0) + held(256.0) + held((nboxes + 1) * 8.0);
     t += 2 * held(4.0 * N) + 2 * held(4.0 * N) + held(std::ceil(N / 2048.0) * 256.0 * 8.0);
     t += held(std::max(scan_bytes(N + 1.0), 24.0 * N));   // scans; crk_update_support's copies
     t += held(32.0 * N);
@@ -290,7 +290,7 @@ crk_status crk_workspace_estimate(const crk_ctx *c, int64_t n, int32_t nboxes,
     while (bits < 8 && (double)nboxes * std::pow(8.0, bits + 1) * 8.0 / 7.0 <= (double)(1 << 26)) bits++;
     const double ntab = (std::pow(8.0, bits + 1) - 1.0) / 7.0 * nboxes;
     t += 2 * held(4.0 * ntab);
-    t += held(4.0 * N) + held(8.0 * (N + 2.0)) + held(8.0 * (N + 1.0)) + 2 * held(4.0 * N);   // counts, offsets
+    t += held(4.0 * N) + 2 * held(8.0 * (N + 1.0)) + 2 * held(4.0 * N);   // counts, offsets
     t += held(4.0 * N * walk_cap) + held(4.0 * (N + 1.0));                // walk rows, long rows
     t += held(4.0 * P + 16.0) + 2 * held(4.0 * 0.5 * P) + 2 * held(4.0 * N);    // N_g rows, extras (E <= P/2)
     if (precision != CRK_MIXED) t += held(8.0 * N);                       // the build's FP64 volumes
@@ -302,7 +302,7 @@ crk_status crk_workspace_estimate(const crk_ctx *c, int64_t n, int32_t nboxes,
     if (uses & CRK_WS_TIMESTEP) t += 2 * held(8.0 * N);
     if (uses & CRK_WS_COMPAT) t += held(32.0 * N * (f64 ? 2 : 1)) + (adapt ? held(64.0 * N) : 0.0);
     if (uses & CRK_WS_HSOLVE) {
-        t += held(8.0 * N) + 2 * held(4.0 * N) + held(8.0 * (N + 1.0)) + held(8.0 * N * hs_cap) +
+        t += held(8.0 * N) + 2 * held(4.0 * N) + held(8.0 * (N / 1024.0 + 2.0)) + held(8.0 * N * hs_cap) +
              held(4.0 * N) + held(8.0 * N);
         // rows of the particles whose candidates pass the cap: at most 8 GiB
         const double pcap = std::max(4096.0, 8.0 * hs_cap);

@@ -27,7 +27,8 @@ namespace {
 __global__ __launch_bounds__(kBlock) void k_validate(const double *x, const double *y,
                                                      const double *z, const double *H, int64_t n,
                                                      double L, double *part /* [nblk][3] */,
-                                                     int *flags /* [3] */) {
+                                                     int *flags /* [nblk]: bits as in k_validate_final */) {
+    __shared__ int sflags;
     __shared__ double smax[kBlock], smin[kBlock], ssum[kBlock];
     double hmax = 0.0, hmin = INFINITY, hsum = 0.0;
     int nf = 0, rg = 0, bh = 0;
@@ -47,7 +48,9 @@ __global__ __launch_bounds__(kBlock) void k_validate(const double *x, const doub
     smax[threadIdx.x] = hmax;
     smin[threadIdx.x] = hmin;
     ssum[threadIdx.x] = hsum;
+    if (threadIdx.x == 0) sflags = 0;
     __syncthreads();
+    if (nf | rg | bh) atomicOr(&sflags, nf | rg << 1 | bh << 2);
     for (int s = kBlock / 2; s > 0; s >>= 1) {
         if ((int)threadIdx.x < s) {
             smax[threadIdx.x] = fmax(smax[threadIdx.x], smax[threadIdx.x + s]);
@@ -60,21 +63,32 @@ __global__ __launch_bounds__(kBlock) void k_validate(const double *x, const doub
         part[blockIdx.x * 3 + 0] = smax[0];
         part[blockIdx.x * 3 + 1] = smin[0];
         part[blockIdx.x * 3 + 2] = ssum[0];
+        flags[blockIdx.x] = sflags;
     }
-    if (nf) atomicOr(&flags[0], 1);
-    if (rg) atomicOr(&flags[1], 1);
-    if (bh) atomicOr(&flags[2], 1);
 }
 
-// final reduction of the (at most 1024) block partials by one block, in a
-// fixed tree order
-__global__ __launch_bounds__(1024) void k_validate_final(const double *part, int nblk, double *out) {
+// what k_validate_final finds: extrema and sum of H, and the flags
+// (bit 0 non-finite input, bit 1 position outside [0, L), bit 2 H <= 0)
+struct Checks {
+    double hmax, hmin, hsum;
+    int flags;
+};
+
+// Final reduction of the (at most 1024) block partials by one block, in a
+// fixed tree order: to host (pinned memory, read once the stream is done), or
+// as the status of a graph-mode step in st (its bits as in Checks, bit 3
+// H >= L/2). boff: the offsets 0, n of a single box.
+__global__ __launch_bounds__(1024) void k_validate_final(const double *part, const int *flags, int nblk, double L,
+                                                         int64_t *boff, int64_t n, Checks *host, GraphStat *st) {
     __shared__ double smax[1024], smin[1024], ssum[1024];
+    __shared__ int sflags;
     const int t = threadIdx.x;
     smax[t] = t < nblk ? part[t * 3 + 0] : 0.0;
     smin[t] = t < nblk ? part[t * 3 + 1] : INFINITY;
     ssum[t] = t < nblk ? part[t * 3 + 2] : 0.0;
+    if (t == 0) sflags = 0;
     __syncthreads();
+    if (t < nblk && flags[t]) atomicOr(&sflags, flags[t]);
     for (int s = 512; s > 0; s >>= 1) {
         if (t < s) {
             smax[t] = fmax(smax[t], smax[t + s]);
@@ -83,10 +97,18 @@ __global__ __launch_bounds__(1024) void k_validate_final(const double *part, int
         }
         __syncthreads();
     }
-    if (t == 0) {
-        out[0] = smax[0];
-        out[1] = smin[0];
-        out[2] = ssum[0];
+    if (t != 0) return;
+    if (boff) {
+        boff[0] = 0;
+        boff[1] = n;
+    }
+    if (host) *host = Checks{smax[0], smin[0], ssum[0], sflags};
+    if (st) {
+        int e = sflags | (!(smin[0] > 0.0) ? 4 : 0);
+        if (!(sflags & 1) && !(smax[0] < 0.5 * L)) e |= 8;
+        st->input_error = e;
+        st->overflow = 0;
+        st->clear = 0;
     }
 }
 
@@ -136,66 +158,58 @@ __global__ __launch_bounds__(kBlock) void k_keys(const double *x, const double *
     val[i] = (int32_t)i;
 }
 
+// sorted particles, the permutation for the caller, and the ntot entries of
+// both cell tables cleared (16-byte aligned, four entries a thread; the
+// launch covers both)
 __global__ __launch_bounds__(kBlock) void k_gather_sorted(const double *x, const double *y,
                                                           const double *z, const double *H,
                                                           const int32_t *perm, int64_t n,
-                                                          int stand_ins, double L, double4 *posH) {
+                                                          int stand_ins, double L, double4 *posH,
+                                                          int32_t *perm_out, int32_t *cbeg, int32_t *cend,
+                                                          int64_t ntot) {
     int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const int4 zero = make_int4(0, 0, 0, 0);
+    if (4 * k + 4 <= ntot) {
+        ((int4 *)cbeg)[k] = zero;
+        ((int4 *)cend)[k] = zero;
+    } else {
+        for (int64_t e = 4 * k; e < ntot; e++) cbeg[e] = cend[e] = 0;
+    }
     if (k >= n) return;
     int32_t i = perm[k];
+    perm_out[k] = i;
     double4 p = make_double4(x[i], y[i], z[i], H[i]);
     if (stand_ins && invalid_particle(p.x, p.y, p.z, p.w, L)) p = stand_in(i, L);
     posH[k] = p;
 }
 
-// graph mode: the input checks of the eager build, as a status word
-// (bit 0 non-finite, bit 1 outside [0, L), bit 2 H <= 0, bit 3 H >= L/2)
-__global__ void k_graph_inputs(const double *res, const int *flags, double L, GraphStat *st) {
-    int e = (flags[0] ? 1 : 0) | (flags[1] ? 2 : 0) | (flags[2] || !(res[1] > 0.0) ? 4 : 0);
-    if (!flags[0] && !(res[0] < 0.5 * L)) e |= 8;
-    st->input_error = e;
-    st->overflow = 0;
-    st->clear = 0;
-}
-
-// graph mode: lists longer than the recorded capacity empty every row (so
-// that the fills below stay in bounds) and raise the overflow flag
-__global__ void k_graph_cap(const int64_t *goff, const int64_t *eoff, int64_t n, int64_t gcap,
-                            int64_t ecap, GraphStat *st) {
-    int64_t G = goff[n], E = eoff[n];
-    int o = (G > gcap || E > ecap) ? 1 : 0;
-    st->overflow = o;
-    st->clear = o;
-    st->n_gather = o ? 0 : G;
-    st->n_extra = o ? 0 : E;
-}
-
-__global__ __launch_bounds__(kBlock) void k_graph_clear(const GraphStat *st, int64_t n, int64_t *goff,
-                                                        int64_t *eoff, int32_t *ng) {
-    int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i > n || !st->clear) return;
+// graph mode: lists longer than the recorded capacity (tot: their lengths)
+// empty every row (so that the fills below stay in bounds) and raise the
+// overflow flag
+__global__ __launch_bounds__(kBlock) void k_graph_cap(const int64_t *tot, int64_t gcap, int64_t ecap, GraphStat *st,
+                                                      int64_t n, int64_t *goff, int64_t *eoff, int32_t *ng) {
+    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x, G = tot[0], E = tot[1];
+    const int o = (G > gcap || E > ecap) ? 1 : 0;
+    if (i == 0) {
+        st->overflow = o;
+        st->clear = o;
+        st->n_gather = o ? 0 : G;
+        st->n_extra = o ? 0 : E;
+    }
+    if (i > n || !o) return;
     goff[i] = 0;
     eoff[i] = 0;
     if (i < n) ng[i] = 0;
 }
 
-__global__ __launch_bounds__(kBlock) void k_fill_i32(int32_t *a, int64_t n, int32_t v) {
-    int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i < n) a[i] = v;
-}
-
-// zeros into two int32 arrays of n entries (16-byte aligned; b may be
-// null), four entries per store, one launch for both
-__global__ __launch_bounds__(kBlock) void k_zero2_i32(int32_t *a, int32_t *b, int64_t n) {
-    const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x, n4 = n >> 2;
-    const int4 z = make_int4(0, 0, 0, 0);
-    if (t < n4) {
-        ((int4 *)a)[t] = z;
-        if (b) ((int4 *)b)[t] = z;
-    } else if (t < n4 + (n & 3)) {
-        a[4 * n4 + (t - n4)] = 0;
-        if (b) b[4 * n4 + (t - n4)] = 0;
-    }
+// the extras' counts and the number of long rows before a walk (16-byte
+// aligned, four entries a thread)
+__global__ __launch_bounds__(kBlock) void k_zero_counts(int32_t *ecnt, int64_t n, int32_t *longs) {
+    const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (t == 0) longs[0] = 0;
+    if (4 * t + 4 <= n) ((int4 *)ecnt)[t] = make_int4(0, 0, 0, 0);
+    else
+        for (int64_t e = 4 * t; e < n; e++) ecnt[e] = 0;
 }
 
 // sorted-index range of every cell of every level (a level-k cell is the set
@@ -1039,6 +1053,23 @@ __global__ __launch_bounds__(kBlock) void k_permute(const int32_t *perm, const d
     }
 }
 
+// a step's gas state in sorted order, one launch for all of it (rho and its
+// destination may be null)
+__global__ __launch_bounds__(kBlock) void k_permute_state(const int32_t *perm, int64_t n, const double *v,
+                                                          const double *m, const double *u, const double *rho,
+                                                          double *sv, double *sm, double *su, double *srho) {
+    int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (k >= n) return;
+    int64_t o = perm[k];
+    const double a = v[o], b = v[n + o], c = v[2 * n + o], d = m[o], e = u[o], r = rho ? rho[o] : 0.0;
+    sv[k] = a;
+    sv[n + k] = b;
+    sv[2 * n + k] = c;
+    sm[k] = d;
+    su[k] = e;
+    if (rho) srho[k] = r;
+}
+
 // row lengths of the exported sets: which 0 -> N_g (self + gather row),
 // which 1 -> N_s (gather row + extras row)
 __global__ __launch_bounds__(kBlock) void k_export_len(const int64_t *goff, const int32_t *eb,
@@ -1066,35 +1097,35 @@ inline unsigned nblocks(int64_t n) { return (unsigned)((n + kBlock - 1) / kBlock
 
 }  // namespace
 
-// the reduced input checks of k_validate / k_validate_final, on the host
-static crk_status read_checks(crk_ctx *c, const double *res, const int *flags, double *hmax,
-                              double *hmin) {
-    double *pin = (double *)c->pinned.p;
-    CRK_HIP(c, hipMemcpyAsync(pin, res, 3 * sizeof(double), hipMemcpyDeviceToHost, c->stream));
-    CRK_HIP(c, hipMemcpyAsync(pin + 3, flags, 3 * sizeof(int), hipMemcpyDeviceToHost, c->stream));
-    CRK_HIP(c, hipStreamSynchronize(c->stream));
-    *hmax = pin[0];
-    *hmin = pin[1];
-    int *hf = (int *)(pin + 3);
-    if (hf[0]) return set_err(c, CRK_ERR_NONFINITE, "non-finite position or H");
-    if (hf[1]) return set_err(c, CRK_ERR_INVALID_ARG, "position outside [0, L)");
-    if (hf[2] || !(*hmin > 0.0)) return set_err(c, CRK_ERR_SUPPORT, "H must be positive");
+// The input checks: launched, and in an eager build read once they are done.
+// boff as in k_validate_final; st in graph mode.
+static crk_status launch_checks(crk_ctx *c, const double *x, const double *y, const double *z, const double *H,
+                                int64_t n, double L, int64_t *boff, GraphStat *st) {
+    const int nblk = (int)std::min<int64_t>((n + kBlock - 1) / kBlock, 1024);
+    CRK_TRY(ensure(c, c->red, (size_t)nblk * 3 * sizeof(double) + 64 + (size_t)nblk * sizeof(int)));
+    double *part = (double *)c->red.p;
+    int *flags = (int *)(part + (size_t)nblk * 3);
+    k_validate<<<nblk, kBlock, 0, c->stream>>>(x, y, z, H, n, L, part, flags);
+    k_validate_final<<<1, 1024, 0, c->stream>>>(part, flags, nblk, L, boff, n, st ? nullptr : (Checks *)c->pinned.p, st);
+    CRK_HIP(c, hipGetLastError());
+    if (!st) CRK_HIP(c, hipStreamSynchronize(c->stream));
+    return CRK_OK;
+}
+
+static crk_status read_checks(crk_ctx *c, double *hmax, double *hmin) {
+    const Checks k = *(const Checks *)c->pinned.p;
+    *hmax = k.hmax;
+    *hmin = k.hmin;
+    if (k.flags & 1) return set_err(c, CRK_ERR_NONFINITE, "non-finite position or H");
+    if (k.flags & 2) return set_err(c, CRK_ERR_INVALID_ARG, "position outside [0, L)");
+    if ((k.flags & 4) || !(*hmin > 0.0)) return set_err(c, CRK_ERR_SUPPORT, "H must be positive");
     return CRK_OK;
 }
 
 crk_status validate_inputs(crk_ctx *c, const double *x, const double *y, const double *z,
                            const double *H, int64_t n, double L, double *hmax, double *hmin) {
-    int nblk = (int)std::min<int64_t>((n + kBlock - 1) / kBlock, 1024);
-    CRK_TRY(ensure(c, c->red, (size_t)nblk * 3 * sizeof(double) + 64));
-    double *part = (double *)c->red.p;
-    int *flags = (int *)(part + (size_t)nblk * 3);
-    CRK_TRY(ensure(c, c->misc, 256));
-    double *res = (double *)c->misc.p;
-    k_fill_i32<<<1, kBlock, 0, c->stream>>>(flags, 3, 0);
-    k_validate<<<nblk, kBlock, 0, c->stream>>>(x, y, z, H, n, L, part, flags);
-    k_validate_final<<<1, 1024, 0, c->stream>>>(part, nblk, res);
-    CRK_HIP(c, hipGetLastError());
-    return read_checks(c, res, flags, hmax, hmin);
+    CRK_TRY(launch_checks(c, x, y, z, H, n, L, nullptr, nullptr));
+    return read_checks(c, hmax, hmin);
 }
 
 Levels levels(const crk_ctx *c) {
@@ -1129,8 +1160,7 @@ static crk_status build_lists(crk_ctx *c) {
     int64_t n = c->n;
     Levels v = levels(c);
     CRK_TRY(ensure(c, c->ng, (size_t)n * sizeof(int32_t)));
-    // goff[n + 1]: the longest gather row, for the next build's scratch rows
-    CRK_TRY(ensure(c, c->goff, (size_t)(n + 2) * sizeof(int64_t)));
+    CRK_TRY(ensure(c, c->goff, (size_t)(n + 1) * sizeof(int64_t)));
     CRK_TRY(ensure(c, c->ecnt, (size_t)n * sizeof(int32_t)));
     CRK_TRY(ensure(c, c->efill, (size_t)n * sizeof(int32_t)));
     CRK_TRY(ensure(c, c->eoff, (size_t)(n + 1) * sizeof(int64_t)));
@@ -1148,8 +1178,7 @@ static crk_status build_lists(crk_ctx *c) {
     // long rows: longs[0] counts them, their particles follow
     CRK_TRY(ensure(c, c->longs, (size_t)(n + 1) * sizeof(int32_t)));
     int32_t *longs = (int32_t *)c->longs.p;
-    k_zero2_i32<<<nblocks((n >> 2) + (n & 3)), kBlock, 0, c->stream>>>(ecnt, nullptr, n);
-    k_fill_i32<<<1, kBlock, 0, c->stream>>>(longs, 1, 0);
+    k_zero_counts<<<nblocks(n / 4 + 1), kBlock, 0, c->stream>>>(ecnt, n, longs);
     {
         KTimer kt_(c, "k_walk");
         const int P = walk_particles(n, c->G_walk);
@@ -1165,25 +1194,25 @@ static crk_status build_lists(crk_ctx *c) {
     CRK_HIP(c, hipGetLastError());
     // efill[j] = eoff[j]: the slot counters of the extras rows start at
     // their rows' offsets
-    CRK_TRY(scan_counts2(c, ng, ecnt, n, goff, eoff, goff + n + 1, efill));
-    int64_t G, E, longest = 0;
+    // tot: gather pairs, extra pairs and the longest gather row (for the next
+    // build's scratch rows), in graph mode on the device
+    CRK_TRY(ensure(c, c->misc, 256));
+    int64_t *tot = c->graph_mode ? (int64_t *)c->misc.p + 16 : (int64_t *)c->pinned.p;
+    CRK_TRY(scan_counts2(c, ng, ecnt, n, goff, eoff, tot, efill));
+    int64_t G, E, longest;
     GraphStat *gst = (GraphStat *)c->gstat.p;
     if (c->graph_mode) {
         // fixed capacities; the counts stay on the device
         G = c->gcap;
         E = c->ecap;
-        k_graph_cap<<<1, 1, 0, c->stream>>>(goff, eoff, n, G, E, gst);
-        k_graph_clear<<<nblocks(n + 1), kBlock, 0, c->stream>>>(gst, n, goff, eoff, ng);
+        longest = INT64_MAX;
+        k_graph_cap<<<nblocks(n + 1), kBlock, 0, c->stream>>>(tot, G, E, gst, n, goff, eoff, ng);
         CRK_HIP(c, hipGetLastError());
     } else {
-        int64_t *pin = (int64_t *)c->pinned.p;
-        CRK_HIP(c, hipMemcpyAsync(pin, goff + n, sizeof(int64_t), hipMemcpyDeviceToHost, c->stream));
-        CRK_HIP(c, hipMemcpyAsync(pin + 1, eoff + n, sizeof(int64_t), hipMemcpyDeviceToHost, c->stream));
-        CRK_HIP(c, hipMemcpyAsync(pin + 2, goff + n + 1, sizeof(int64_t), hipMemcpyDeviceToHost, c->stream));
         CRK_HIP(c, hipStreamSynchronize(c->stream));
-        G = pin[0];
-        E = pin[1];
-        longest = pin[2];
+        G = tot[0];
+        E = tot[1];
+        longest = tot[2];
     }
     if (E > INT32_MAX - 1) return set_err(c, CRK_ERR_INVALID_ARG, "more than 2^31 extra pairs");
     // (four entries more: the passes read whole 16-byte pieces)
@@ -1212,7 +1241,7 @@ static crk_status build_lists(crk_ctx *c) {
         k_compact_rows<GC, UC><<<(unsigned)((n * GC + kBlock - 1) / kBlock), kBlock, 0, c->stream>>>(
             scratch, cap, n, ng, goff, (int32_t *)c->gidx.p, efill, etmp, longs, posH, box, vnsum, posV);
     }
-    {
+    if (longest > cap) {
         // the rows over the cap are few and long: 32 lanes each (the row is
         // the same list for any lane count), over the list the compaction made
         KTimer kt_(c, "k_walk_long");
@@ -1222,7 +1251,7 @@ static crk_status build_lists(crk_ctx *c) {
                                                       (int32_t *)c->gidx.p, efill, etmp, c->walk_shift, longs);
     }
     CRK_HIP(c, hipGetLastError());
-    if (vol) {
+    if (vol && longest > cap) {
         const unsigned nb = (unsigned)std::min<int64_t>((n * GC + kBlock - 1) / kBlock, 1024);
         k_volume_longs<GC><<<nb, kBlock, 0, c->stream>>>(longs, ng, cap, goff, (const int32_t *)c->gidx.p,
                                                           posH, box, vnsum, posV);
@@ -1268,30 +1297,39 @@ crk_status build_sorted(crk_ctx *c, const double *x, const double *y, const doub
     CRK_TRY(ensure(c, c->perm, (size_t)n * sizeof(int32_t)));
     uint32_t *key = (uint32_t *)c->keyA.p;
     int32_t *pm = (int32_t *)c->perm.p;
+    uint32_t *key_in;
+    int32_t *pm_in;
+    CRK_TRY(radix_input(c, key, pm, n, 3 * bits + boxbits, &key_in, &pm_in));
     k_keys<<<nblocks(n), kBlock, 0, c->stream>>>(x, y, z, n, 1.0 / c->cell, c->nc, bits,
                                                   (const int64_t *)(c->graph_mode ? c->gboff.p : c->boff.p),
-                                                  nboxes, stand_ins ? H : nullptr, c->L, key, pm);
+                                                  nboxes, stand_ins ? H : nullptr, c->L, key_in, pm_in);
     CRK_HIP(c, hipGetLastError());
     {
         KTimer kt_(c, "sort");
-        CRK_TRY(radix_sort_pairs(c, key, pm, n, 3 * bits + boxbits));
+        CRK_TRY(radix_sort_pairs(c, key, pm, n, 3 * bits + boxbits, true));
     }
     // 3. sorted particles and the cell tables of every level of every box
     CRK_TRY(ensure(c, c->posH, (size_t)n * sizeof(double4)));
     CRK_TRY(ensure(c, c->cbeg, (size_t)ntot * sizeof(int32_t)));
     CRK_TRY(ensure(c, c->cend, (size_t)ntot * sizeof(int32_t)));
-    k_gather_sorted<<<nblocks(n), kBlock, 0, c->stream>>>(x, y, z, H, pm, n, stand_ins ? 1 : 0, c->L,
-                                                           (double4 *)c->posH.p);
-    k_zero2_i32<<<nblocks((ntot >> 2) + (ntot & 3)), kBlock, 0, c->stream>>>((int32_t *)c->cbeg.p,
-                                                                             (int32_t *)c->cend.p, ntot);
+    k_gather_sorted<<<nblocks(std::max(n, ntot / 4 + 1)), kBlock, 0, c->stream>>>(
+        x, y, z, H, pm, n, stand_ins ? 1 : 0, c->L, (double4 *)c->posH.p, perm, (int32_t *)c->cbeg.p,
+        (int32_t *)c->cend.p, ntot);
     k_tables<<<nblocks(n), kBlock, 0, c->stream>>>(key, n, levels(c), (int32_t *)c->cbeg.p,
                                                     (int32_t *)c->cend.p);
     CRK_HIP(c, hipGetLastError());
-    CRK_HIP(c, hipMemcpyAsync(perm, pm, (size_t)n * sizeof(int32_t), hipMemcpyDeviceToDevice, c->stream));
     // 4. neighbour lists
     CRK_TRY(build_lists(c));
     if (n_pairs) *n_pairs = c->npairs;
     if (n_cells) *n_cells = c->nc;
+    return CRK_OK;
+}
+
+crk_status permute_state(crk_ctx *c, const double *v, const double *m, const double *u, const double *rho, double *sv,
+                         double *sm, double *su, double *srho) {
+    k_permute_state<<<nblocks(c->n), kBlock, 0, c->stream>>>((const int32_t *)c->perm.p, c->n, v, m, u, rho, sv, sm, su,
+                                                             srho);
+    CRK_HIP(c, hipGetLastError());
     return CRK_OK;
 }
 
@@ -1333,24 +1371,15 @@ crk_status crk_build_cells_batch(crk_ctx *c, int32_t nboxes, const int64_t *box_
     // for (its volume pass sums in FP32)
     c->vol_in_build = p->precision != CRK_MIXED;
     // 1. validate and reduce H
-    int nblk = (int)std::min<int64_t>((n + kBlock - 1) / kBlock, 1024);
-    CRK_TRY(ensure(c, c->red, (size_t)nblk * 3 * sizeof(double) + 64));
-    double *part = (double *)c->red.p;
-    int *flags = (int *)(part + (size_t)nblk * 3);
-    CRK_TRY(ensure(c, c->misc, 256));
-    double *res = (double *)c->misc.p;
-    k_fill_i32<<<1, kBlock, 0, c->stream>>>(flags, 3, 0);
-    k_validate<<<nblk, kBlock, 0, c->stream>>>(x, y, z, H, n, p->L, part, flags);
-    k_validate_final<<<1, 1024, 0, c->stream>>>(part, nblk, res);
-    CRK_HIP(c, hipGetLastError());
     if (gm) {
         CRK_TRY(ensure(c, c->gstat, sizeof(GraphStat)));
-        k_graph_inputs<<<1, 1, 0, c->stream>>>(res, flags, p->L, (GraphStat *)c->gstat.p);
-        CRK_HIP(c, hipGetLastError());
+        CRK_TRY(launch_checks(c, x, y, z, H, n, p->L, nullptr, (GraphStat *)c->gstat.p));
         return build_sorted(c, x, y, z, H, perm, true, n_pairs, n_cells);
     }
+    CRK_TRY(ensure(c, c->boff, (size_t)(nboxes + 1) * sizeof(int64_t)));
+    CRK_TRY(launch_checks(c, x, y, z, H, n, p->L, nboxes == 1 ? (int64_t *)c->boff.p : nullptr, nullptr));
     double hmax = 0.0, hmin = 0.0;
-    CRK_TRY(read_checks(c, res, flags, &hmax, &hmin));
+    CRK_TRY(read_checks(c, &hmax, &hmin));
     if (!(hmax < 0.5 * p->L)) return set_err(c, CRK_ERR_SUPPORT, "max H %g >= L/2", hmax);
     // 2. Morton cell hierarchy: finest side near half the smallest support
     //    (or the requested side), at most 256 cells a side and at most about
@@ -1373,9 +1402,9 @@ crk_status crk_build_cells_batch(crk_ctx *c, int32_t nboxes, const int64_t *box_
         off += m * m * m;
     }
     c->ntab = off;
-    CRK_TRY(ensure(c, c->boff, (size_t)(nboxes + 1) * sizeof(int64_t)));
-    CRK_HIP(c, hipMemcpyAsync(c->boff.p, box_offsets, (size_t)(nboxes + 1) * sizeof(int64_t),
-                              hipMemcpyHostToDevice, c->stream));
+    if (nboxes > 1)
+        CRK_HIP(c, hipMemcpyAsync(c->boff.p, box_offsets, (size_t)(nboxes + 1) * sizeof(int64_t),
+                                  hipMemcpyHostToDevice, c->stream));
     return build_sorted(c, x, y, z, H, perm, false, n_pairs, n_cells);
 }
 
@@ -1396,22 +1425,11 @@ crk_status crk_update_support(crk_ctx *c, const double *H_sorted, int64_t *n_pai
     double *xs = (double *)c->scanTmp.p;
     k_get_xyz<<<nblocks(n), kBlock, 0, c->stream>>>((const double4 *)c->posH.p, n, xs, xs + n,
                                                      xs + 2 * n);
-    int nblk = (int)std::min<int64_t>((n + kBlock - 1) / kBlock, 1024);
-    CRK_TRY(ensure(c, c->red, (size_t)nblk * 3 * sizeof(double) + 64));
-    double *part = (double *)c->red.p;
-    int *flags = (int *)(part + (size_t)nblk * 3);
-    double *res = (double *)c->misc.p;
-    k_fill_i32<<<1, kBlock, 0, c->stream>>>(flags, 3, 0);
-    k_validate<<<nblk, kBlock, 0, c->stream>>>(xs, xs + n, xs + 2 * n, H_sorted, n, c->L, part, flags);
-    k_validate_final<<<1, 1024, 0, c->stream>>>(part, nblk, res);
-    double *pin = (double *)c->pinned.p;
-    CRK_HIP(c, hipMemcpyAsync(pin, res, 3 * sizeof(double), hipMemcpyDeviceToHost, c->stream));
-    CRK_HIP(c, hipMemcpyAsync(pin + 3, flags, 3 * sizeof(int), hipMemcpyDeviceToHost, c->stream));
-    CRK_HIP(c, hipStreamSynchronize(c->stream));
-    int *hf = (int *)(pin + 3);
-    if (hf[0]) return set_err(c, CRK_ERR_NONFINITE, "non-finite H");
-    if (hf[2] || !(pin[1] > 0.0)) return set_err(c, CRK_ERR_SUPPORT, "H must be positive");
-    if (!(pin[0] < 0.5 * c->L)) return set_err(c, CRK_ERR_SUPPORT, "max H %g >= L/2", pin[0]);
+    CRK_TRY(launch_checks(c, xs, xs + n, xs + 2 * n, H_sorted, n, c->L, nullptr, nullptr));
+    const Checks k = *(const Checks *)c->pinned.p;
+    if (k.flags & 1) return set_err(c, CRK_ERR_NONFINITE, "non-finite H");
+    if ((k.flags & 4) || !(k.hmin > 0.0)) return set_err(c, CRK_ERR_SUPPORT, "H must be positive");
+    if (!(k.hmax < 0.5 * c->L)) return set_err(c, CRK_ERR_SUPPORT, "max H %g >= L/2", k.hmax);
     k_set_H<<<nblocks(n), kBlock, 0, c->stream>>>((double4 *)c->posH.p, H_sorted, n);
     CRK_TRY(build_lists(c));
     if (n_pairs) *n_pairs = c->npairs;

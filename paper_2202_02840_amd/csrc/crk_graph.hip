@@ -42,24 +42,25 @@ crk_status step_run(crk_ctx *c, int32_t nboxes, const int64_t *box_offsets, int6
     CRK_TRY(crk_build_cells_batch(c, nboxes, box_offsets, n, io->x, io->y, io->z, io->H, p, cell_size,
                                   io->perm, n_pairs, nullptr));
     CRK_TRY(crk_moments(c, p, nullptr, io->V, io->m0, io->m1, io->m2, io->gm0, io->gm1, io->gm2));
-    crk_status sc = crk_corrections(c, n, io->m0, io->m1, io->m2, io->gm0, io->gm1, io->gm2, io->A,
-                                    io->B, io->gA, io->gB, gm ? nullptr : n_singular);
-    if (sc < 0) return sc;
+    // (the singular count comes with the readback that ends crk_derivatives)
+    CRK_TRY(crk_corrections(c, n, io->m0, io->m1, io->m2, io->gm0, io->gm1, io->gm2, io->A, io->B, io->gA, io->gB,
+                            nullptr));
     CRK_TRY(ensure(c, c->sv, (size_t)3 * n * sizeof(double)));
     CRK_TRY(ensure(c, c->sm, (size_t)n * sizeof(double)));
     CRK_TRY(ensure(c, c->su, (size_t)n * sizeof(double)));
     double *sv = (double *)c->sv.p, *sm = (double *)c->sm.p, *su = (double *)c->su.p;
     double *srho = nullptr;
-    CRK_TRY(crk_permute(c, io->v, sv, 3, 1));
-    CRK_TRY(crk_permute(c, io->m, sm, 1, 1));
-    CRK_TRY(crk_permute(c, io->u, su, 1, 1));
     if (io->rho) {
         CRK_TRY(ensure(c, c->srho, (size_t)n * sizeof(double)));
         srho = (double *)c->srho.p;
-        CRK_TRY(crk_permute(c, io->rho, srho, 1, 1));
     }
-    CRK_TRY(crk_derivatives(c, p, sv, sm, su, srho, io->V, io->A, io->B, io->gA, io->gB, io->gradv,
-                            io->dpdt, io->dudt));
+    CRK_TRY(permute_state(c, io->v, io->m, io->u, io->rho, sv, sm, su, srho));
+    const crk_status sd = crk_derivatives(c, p, sv, sm, su, srho, io->V, io->A, io->B, io->gA, io->gB, io->gradv,
+                                          io->dpdt, io->dudt);
+    if (!gm && n_singular && (sd == CRK_OK || sd == CRK_ERR_NONFINITE))
+        *n_singular = *((const int64_t *)c->pinned.p + 19);
+    if (sd < 0) return sd;
+    if (!gm) return n_singular && *n_singular > 0 ? CRK_WARN_SINGULAR : CRK_OK;
     if (gm) {
         // the counters of crk_corrections and crk_derivatives live in `misc`
         const bool adapt = p->precision == CRK_MIXED_ADAPT;
@@ -68,7 +69,7 @@ crk_status step_run(crk_ctx *c, int32_t nboxes, const int64_t *box_offsets, int6
             adapt ? (const int64_t *)c->fpos.p + n : nullptr, adapt ? (const int64_t *)c->tpos.p + n : nullptr);
         CRK_HIP(c, hipGetLastError());
     }
-    return sc;
+    return CRK_OK;
 }
 
 crk_status step_args(crk_ctx *c, int32_t nboxes, const int64_t *box_offsets, int64_t n,

@@ -191,16 +191,25 @@ struct KTimer {
     ~KTimer();
 };
 
+// v (three components), m, u and (may be null) rho into the last build's order
+crk_status permute_state(crk_ctx *c, const double *v, const double *m, const double *u, const double *rho, double *sv,
+                         double *sm, double *su, double *srho);
 // device-wide exclusive scan of n values (int64 in/out may alias)
 crk_status scan_exclusive_i64(crk_ctx *c, const int64_t *in, int64_t *out, int64_t n);
 // offsets of n rows from two int32 count arrays at once: oa[k] = sum of
 // a[0..k) for k = 0..n (oa[n] the total), likewise ob from b (b and ob
-// both null: a alone); with amax (device) also the largest entry of a (0
-// when n = 0); with ob32 also ob[0..n) as int32 (the totals fit in 31 bits)
+// both null: a alone); with tot (on the device, or pinned host memory) also
+// both totals and the largest entry of a (0 when n = 0); with ob32 also
+// ob[0..n) as int32 (the totals fit in 31 bits)
 crk_status scan_counts2(crk_ctx *c, const int32_t *a, const int32_t *b, int64_t n, int64_t *oa,
-                        int64_t *ob, int64_t *amax = nullptr, int32_t *ob32 = nullptr);
+                        int64_t *ob, int64_t *tot = nullptr, int32_t *ob32 = nullptr);
 // stable LSD radix sort of (key, value) pairs on the low `bits` bits of the keys
-crk_status radix_sort_pairs(crk_ctx *c, uint32_t *keys, int32_t *vals, int64_t n, int bits);
+// (with from_input the input lies where radix_input said: no copy at the end)
+crk_status radix_sort_pairs(crk_ctx *c, uint32_t *keys, int32_t *vals, int64_t n, int bits, bool from_input = false);
+// where that sort's input is best written: keys and vals, or, for an odd number
+// of passes, its own buffers
+crk_status radix_input(crk_ctx *c, uint32_t *keys, int32_t *vals, int64_t n, int bits, uint32_t **kin,
+                       int32_t **vin);
 
 // grid index remap that gives each XCD a contiguous run of logical blocks:
 // blocks are dispatched round-robin over the 8 XCDs, so block b runs on XCD

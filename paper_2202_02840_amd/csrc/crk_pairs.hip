@@ -1753,9 +1753,15 @@ __global__ __launch_bounds__(kBlock) void k_zero_marks(int32_t *a, int64_t n, in
     if (i == 0) *c0 = 0;
 }
 
+// (host, pinned: the flagged and the listed rows' counts, read once the stream
+// is done)
 __global__ __launch_bounds__(kBlock) void k_compact(int64_t n, const int64_t *__restrict__ pos,
-                                                    int32_t *list) {
+                                                    int32_t *list, const int64_t *nflag, int64_t *host) {
     int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (i == 0 && host) {
+        host[0] = *nflag;
+        host[1] = pos[n];
+    }
     if (i < n && pos[i + 1] != pos[i]) list[pos[i]] = (int32_t)i;
 }
 
@@ -2056,13 +2062,14 @@ static crk_status adapt_finish(crk_ctx *c, bool gm, AdaptRows &r) {
     const int32_t *eb = (const int32_t *)c->eb.p, *ee = (const int32_t *)c->ee.p,
                   *eidx = (const int32_t *)c->eidx.p;
     int64_t *fpos = (int64_t *)c->fpos.p, *tpos = (int64_t *)c->tpos.p;
+    int64_t *pin = (int64_t *)c->pinned.p + 40;
     {
         KTimer kt_(c, "k_flag");
         int32_t *mark = (int32_t *)fpos;
         k_mark<<<(unsigned)std::min<int64_t>(nblocks(n * 16), 1024), kBlock, 0, c->stream>>>(
             r.flist, fpos + n, goff, gidx, eb, ee, eidx, mark);
         CRK_TRY(scan_counts2(c, mark, nullptr, n, tpos, nullptr));
-        k_compact<<<nblocks(n), kBlock, 0, c->stream>>>(n, tpos, r.tlist);
+        k_compact<<<nblocks(n), kBlock, 0, c->stream>>>(n, tpos, r.tlist, fpos + n, gm ? nullptr : pin);
     }
     CRK_HIP(c, hipGetLastError());
     if (gm) {
@@ -2072,9 +2079,6 @@ static crk_status adapt_finish(crk_ctx *c, bool gm, AdaptRows &r) {
         r.nflag = r.ntouch = n;
         c->last_nflag = c->last_ntouch = -1;
     } else {
-        int64_t *pin = (int64_t *)c->pinned.p + 40;
-        CRK_HIP(c, hipMemcpyAsync(pin, fpos + n, sizeof(int64_t), hipMemcpyDeviceToHost, c->stream));
-        CRK_HIP(c, hipMemcpyAsync(pin + 1, tpos + n, sizeof(int64_t), hipMemcpyDeviceToHost, c->stream));
         CRK_HIP(c, hipStreamSynchronize(c->stream));
         r.nflag = pin[0];
         r.ntouch = pin[1];
@@ -2253,8 +2257,9 @@ crk_status crk_derivatives(crk_ctx *c, const crk_params *p, const double *v, con
     CRK_HIP(c, hipGetLastError());
     c->ts_valid = ts;
     if (gm) return CRK_OK;   // the graph's status kernel reads `bad`
+    // (with the singular count of the last crk_corrections: misc bytes 8 to 39)
     int *pin = (int *)c->pinned.p + 32;
-    CRK_HIP(c, hipMemcpyAsync(pin, bad, sizeof(int), hipMemcpyDeviceToHost, c->stream));
+    CRK_HIP(c, hipMemcpyAsync(pin, bad, 32, hipMemcpyDeviceToHost, c->stream));
     CRK_HIP(c, hipStreamSynchronize(c->stream));
     if (pin[0]) return set_err(c, CRK_ERR_NONFINITE, "non-finite or non-positive gas state");
     return CRK_OK;

@@ -3,6 +3,8 @@
 // exchange between the four waves of a block, and the sort ranks keys inside
 // a wave with eight ballots (one per digit bit), so each pass is stable and
 // the whole sort is deterministic.
+#include <utility>
+
 #include "crk_internal.h"
 
 namespace crk {
@@ -117,21 +119,26 @@ __global__ __launch_bounds__(kBlock) void k_scan_sums2(const int32_t *in0, const
     }
 }
 
-// the largest of m block maxima (one block)
-__global__ __launch_bounds__(kBlock) void k_max_i64(const int64_t *bm, int64_t m, int64_t *out) {
-    __shared__ int64_t lds[4];
-    int64_t mx = 0;
-    for (int64_t k = threadIdx.x; k < m; k += kBlock) mx = bm[k] > mx ? bm[k] : mx;
-    mx = block_max(mx, lds);
-    if (threadIdx.x == 0) *out = mx;
+// Sum over the 256 threads of a block, on every thread
+__device__ int64_t block_sum(int64_t v, int64_t *lds /* [4] */) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = v;
+    __syncthreads();
+    return (lds[0] + lds[1]) + (lds[2] + lds[3]);
 }
 
-// (with o32: the first nin offsets of the second array also as int32)
+// The offsets. scanned: the block sums are offsets already, otherwise each
+// block adds up those before its own (a launch less; a block reads a few
+// thousand sums at most). With o32 the first nin offsets of the second array
+// also as int32; with tot the totals of both arrays and the largest value of
+// the first (the maximum of bm).
 template <bool VEC>
 __global__ __launch_bounds__(kBlock) void k_scan_apply2(const int32_t *in0, const int32_t *in1, int64_t nin,
                                                         int64_t nout, int64_t *out0, int64_t *out1,
-                                                        const int64_t *bo0, const int64_t *bo1,
-                                                        int32_t *o32) {
+                                                        const int64_t *bo0, const int64_t *bo1, bool scanned,
+                                                        const int64_t *bm, int64_t *tot, int32_t *o32) {
     __shared__ int64_t lds[4];
     const int32_t *in = blockIdx.y ? in1 : in0;
     int64_t *out = blockIdx.y ? out1 : out0;
@@ -139,11 +146,26 @@ __global__ __launch_bounds__(kBlock) void k_scan_apply2(const int32_t *in0, cons
     int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
     int64_t v[8];
     load8<VEC>(in, base, nin, v);
+    int64_t before = 0;
+    if (scanned) {
+        before = boff[blockIdx.x];
+    } else {
+        for (int64_t k = threadIdx.x; k < blockIdx.x; k += kBlock) before += boff[k];
+        before = block_sum(before, lds);
+        __syncthreads();
+    }
     int64_t s = 0;
 #pragma unroll
     for (int k = 0; k < 8; k++) s += v[k];
     int64_t incl = block_inclusive_scan(s, lds);
-    int64_t run = incl - s + boff[blockIdx.x];
+    int64_t run = incl - s + before;
+    if (tot && blockIdx.x == gridDim.x - 1 && threadIdx.x == kBlock - 1) tot[blockIdx.y] = before + incl;
+    if (tot && blockIdx.x == 0 && blockIdx.y == 0) {
+        int64_t mx = 0;
+        for (int64_t k = threadIdx.x; k < gridDim.x; k += kBlock) mx = bm[k] > mx ? bm[k] : mx;
+        mx = block_max(mx, lds);
+        if (threadIdx.x == 0) tot[2] = mx;
+    }
     int64_t o[8];
 #pragma unroll
     for (int k = 0; k < 8; k++) {
@@ -171,46 +193,35 @@ __global__ __launch_bounds__(kBlock) void k_scan_apply2(const int32_t *in0, cons
     }
 }
 
-// block sums of both arrays scanned in place in one single-block launch
-__global__ __launch_bounds__(kBlock) void k_scan_bsum2(int64_t *bs0, int64_t *bs1, int64_t m) {
-    __shared__ int64_t lds[4];
-    int64_t *b = blockIdx.y ? bs1 : bs0;
-    int64_t v[kScanItems];
-    int64_t s = 0;
-    const int64_t base = (int64_t)threadIdx.x * kScanItems;
-#pragma unroll
-    for (int k = 0; k < kScanItems; k++) {
-        v[k] = (base + k < m) ? b[base + k] : 0;
-        s += v[k];
-    }
-    int64_t run = block_inclusive_scan(s, lds) - s;
-#pragma unroll
-    for (int k = 0; k < kScanItems; k++) {
-        if (base + k < m) b[base + k] = run;
-        run += v[k];
-    }
-}
-
 // ---------------------------------------------------------------- radix sort
 constexpr int kRadixBits = 8;
 constexpr int kBuckets = 1 << kRadixBits;
-constexpr int kSortItems = 8;                       // rounds of 256 per block
-constexpr int kSortTile = kBlock * kSortItems;
+// rounds of 256 per block, and the blocks up to which each block of the scatter
+// adds up the digit counts itself (DIRECT: 32-bit counts, a block's 256 side by
+// side) in place of a scan in three launches. A sort this small waits for its
+// launches: 125000 keys in 123 blocks of 1024 16.5 us a pass, in 62 of 2048
+// with the scan 26; 262144 in 128 of 2048 20 and 27.
+constexpr int kSortItems = 8, kSortItemsSmall = 4;
+constexpr int64_t kDirectBlocks = 128;
 
+template <int ITEMS, bool DIRECT>
 __global__ __launch_bounds__(kBlock) void k_radix_hist(const uint32_t *keys, int64_t n, int shift,
                                                        int64_t nblk, int64_t *hist) {
     __shared__ int cnt[kBuckets];
     cnt[threadIdx.x] = 0;
     __syncthreads();
-    int64_t base = (int64_t)blockIdx.x * kSortTile;
-    for (int r = 0; r < kSortItems; r++) {
+    int64_t base = (int64_t)blockIdx.x * (kBlock * ITEMS);
+#pragma unroll
+    for (int r = 0; r < ITEMS; r++) {
         int64_t i = base + (int64_t)r * kBlock + threadIdx.x;
         if (i < n) atomicAdd(&cnt[(keys[i] >> shift) & (kBuckets - 1)], 1);
     }
     __syncthreads();
-    hist[(int64_t)threadIdx.x * nblk + blockIdx.x] = cnt[threadIdx.x];
+    if (DIRECT) ((int32_t *)hist)[(int64_t)blockIdx.x * kBuckets + threadIdx.x] = cnt[threadIdx.x];
+    else hist[(int64_t)threadIdx.x * nblk + blockIdx.x] = cnt[threadIdx.x];
 }
 
+template <int ITEMS, bool DIRECT>
 __global__ __launch_bounds__(kBlock) void k_radix_scatter(const uint32_t *kin, const int32_t *vin,
                                                           uint32_t *kout, int32_t *vout, int64_t n,
                                                           int shift, int64_t nblk,
@@ -218,12 +229,26 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter(const uint32_t *kin, c
     __shared__ int64_t base[kBuckets];
     __shared__ int wcnt[4][kBuckets];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    base[tid] = offs[(int64_t)tid * nblk + blockIdx.x];
+    if (DIRECT) {
+        // this digit's keys in the blocks before, and after all smaller digits
+        __shared__ int64_t lds[4];
+        const int32_t *h = (const int32_t *)offs + tid;
+        int before = 0, all = 0;
+#pragma unroll 16
+        for (int b = 0; b < (int)nblk; b++) {
+            const int x = h[b * kBuckets];
+            all += x;
+            before += b < (int)blockIdx.x ? x : 0;
+        }
+        base[tid] = block_inclusive_scan<int64_t>(all, lds) - all + before;
+    } else {
+        base[tid] = offs[(int64_t)tid * nblk + blockIdx.x];
+    }
     for (int k = 0; k < 4; k++) wcnt[k][tid] = 0;
     __syncthreads();
     const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    int64_t tile = (int64_t)blockIdx.x * kSortTile;
-    for (int r = 0; r < kSortItems; r++) {
+    int64_t tile = (int64_t)blockIdx.x * (kBlock * ITEMS);
+    for (int r = 0; r < ITEMS; r++) {
         int64_t i = tile + (int64_t)r * kBlock + tid;
         bool valid = i < n;
         uint32_t key = valid ? kin[i] : 0u;
@@ -308,7 +333,7 @@ crk_status scan_exclusive_i64(crk_ctx *c, const int64_t *in, int64_t *out, int64
 }
 
 crk_status scan_counts2(crk_ctx *c, const int32_t *a, const int32_t *b, int64_t n, int64_t *oa,
-                        int64_t *ob, int64_t *amax, int32_t *ob32) {
+                        int64_t *ob, int64_t *tot, int32_t *ob32) {
     if (n < 0) return set_err(c, CRK_ERR_INVALID_ARG, "negative count");
     if ((b == nullptr) != (ob == nullptr) || (ob32 && !b))
         return set_err(c, CRK_ERR_INVALID_ARG, "scan_counts2: b, ob and ob32 do not match");
@@ -320,45 +345,69 @@ crk_status scan_counts2(crk_ctx *c, const int32_t *a, const int32_t *b, int64_t 
     auto al16 = [](const void *q) { return ((uintptr_t)q & 15u) == 0; };
     const bool vec = al16(a) && al16(oa) && (!b || (al16(b) && al16(ob))) && (!ob32 || al16(ob32));
     if (vec)
-        k_scan_sums2<true><<<dim3((unsigned)nblk, ny), kBlock, 0, c->stream>>>(a, b, n, bs0, bs1, amax ? bm : nullptr);
+        k_scan_sums2<true><<<dim3((unsigned)nblk, ny), kBlock, 0, c->stream>>>(a, b, n, bs0, bs1, tot ? bm : nullptr);
     else
-        k_scan_sums2<false><<<dim3((unsigned)nblk, ny), kBlock, 0, c->stream>>>(a, b, n, bs0, bs1, amax ? bm : nullptr);
+        k_scan_sums2<false><<<dim3((unsigned)nblk, ny), kBlock, 0, c->stream>>>(a, b, n, bs0, bs1, tot ? bm : nullptr);
     CRK_HIP(c, hipGetLastError());
-    if (amax) k_max_i64<<<1, kBlock, 0, c->stream>>>(bm, nblk, amax);
-    if (nblk <= kScanTile) {
-        k_scan_bsum2<<<dim3(1, ny), kBlock, 0, c->stream>>>(bs0, bs1, nblk);
-        CRK_HIP(c, hipGetLastError());
-    } else {
+    const bool scanned = nblk > 2 * kScanTile;   // (8.4 million rows)
+    if (scanned) {
         CRK_TRY(scan_with(c, bs0, bs0, nblk, tail));
         if (b) CRK_TRY(scan_with(c, bs1, bs1, nblk, tail));
     }
     if (vec)
-        k_scan_apply2<true><<<dim3((unsigned)nblk, ny), kBlock, 0, c->stream>>>(a, b, n, nout, oa, ob, bs0, bs1, ob32);
+        k_scan_apply2<true><<<dim3((unsigned)nblk, ny), kBlock, 0, c->stream>>>(a, b, n, nout, oa, ob, bs0, bs1, scanned,
+                                                                               bm, tot, ob32);
     else
-        k_scan_apply2<false><<<dim3((unsigned)nblk, ny), kBlock, 0, c->stream>>>(a, b, n, nout, oa, ob, bs0, bs1, ob32);
+        k_scan_apply2<false><<<dim3((unsigned)nblk, ny), kBlock, 0, c->stream>>>(a, b, n, nout, oa, ob, bs0, bs1,
+                                                                                scanned, bm, tot, ob32);
     CRK_HIP(c, hipGetLastError());
     return CRK_OK;
 }
 
-crk_status radix_sort_pairs(crk_ctx *c, uint32_t *keys, int32_t *vals, int64_t n, int bits) {
-    if (n <= 1 || bits <= 0) return CRK_OK;
-    int64_t nblk = (n + kSortTile - 1) / kSortTile;
+template <int ITEMS, bool DIRECT>
+static crk_status radix_pass(crk_ctx *c, const uint32_t *ka, const int32_t *va, uint32_t *kb, int32_t *vb, int64_t n,
+                             int shift, int64_t nblk, int64_t *hist) {
+    k_radix_hist<ITEMS, DIRECT><<<(unsigned)nblk, kBlock, 0, c->stream>>>(ka, n, shift, nblk, hist);
+    CRK_HIP(c, hipGetLastError());
+    if (!DIRECT) CRK_TRY(scan_exclusive_i64(c, hist, hist, nblk * kBuckets));
+    k_radix_scatter<ITEMS, DIRECT><<<(unsigned)nblk, kBlock, 0, c->stream>>>(ka, va, kb, vb, n, shift, nblk, hist);
+    CRK_HIP(c, hipGetLastError());
+    return CRK_OK;
+}
+
+crk_status radix_input(crk_ctx *c, uint32_t *keys, int32_t *vals, int64_t n, int bits, uint32_t **kin,
+                       int32_t **vin) {
     CRK_TRY(ensure(c, c->keyB, (size_t)n * sizeof(uint32_t)));
     CRK_TRY(ensure(c, c->valB, (size_t)n * sizeof(int32_t)));
-    CRK_TRY(ensure(c, c->hist, (size_t)nblk * kBuckets * sizeof(int64_t)));
+    const bool other = n > 1 && bits > 0 && ((bits + kRadixBits - 1) / kRadixBits) % 2;
+    *kin = other ? (uint32_t *)c->keyB.p : keys;
+    *vin = other ? (int32_t *)c->valB.p : vals;
+    return CRK_OK;
+}
+
+crk_status radix_sort_pairs(crk_ctx *c, uint32_t *keys, int32_t *vals, int64_t n, int bits, bool from_input) {
+    if (n <= 1 || bits <= 0) return CRK_OK;
+    const bool small = n <= kDirectBlocks * kBlock * kSortItemsSmall;
+    const int64_t tile = (int64_t)kBlock * (small ? kSortItemsSmall : kSortItems);
+    int64_t nblk = (n + tile - 1) / tile;
+    CRK_TRY(ensure(c, c->keyB, (size_t)n * sizeof(uint32_t)));
+    CRK_TRY(ensure(c, c->valB, (size_t)n * sizeof(int32_t)));
+    CRK_TRY(ensure(c, c->hist, (size_t)nblk * kBuckets * (nblk <= kDirectBlocks ? sizeof(int32_t) : sizeof(int64_t))));
     uint32_t *ka = keys, *kb = (uint32_t *)c->keyB.p;
     int32_t *va = vals, *vb = (int32_t *)c->valB.p;
     int64_t *hist = (int64_t *)c->hist.p;
     int passes = (bits + kRadixBits - 1) / kRadixBits;
+    if (from_input && passes % 2) {
+        std::swap(ka, kb);
+        std::swap(va, vb);
+    }
     for (int p = 0; p < passes; p++) {
         int shift = p * kRadixBits;
-        k_radix_hist<<<(unsigned)nblk, kBlock, 0, c->stream>>>(ka, n, shift, nblk, hist);
-        CRK_HIP(c, hipGetLastError());
-        CRK_TRY(scan_exclusive_i64(c, hist, hist, nblk * kBuckets));
-        k_radix_scatter<<<(unsigned)nblk, kBlock, 0, c->stream>>>(ka, va, kb, vb, n, shift, nblk, hist);
-        CRK_HIP(c, hipGetLastError());
-        uint32_t *tk = ka; ka = kb; kb = tk;
-        int32_t *tv = va; va = vb; vb = tv;
+        if (small) CRK_TRY((radix_pass<kSortItemsSmall, true>(c, ka, va, kb, vb, n, shift, nblk, hist)));
+        else if (nblk <= kDirectBlocks) CRK_TRY((radix_pass<kSortItems, true>(c, ka, va, kb, vb, n, shift, nblk, hist)));
+        else CRK_TRY((radix_pass<kSortItems, false>(c, ka, va, kb, vb, n, shift, nblk, hist)));
+        std::swap(ka, kb);
+        std::swap(va, vb);
     }
     if (ka != keys) {
         CRK_HIP(c, hipMemcpyAsync(keys, ka, (size_t)n * sizeof(uint32_t), hipMemcpyDeviceToDevice, c->stream));
