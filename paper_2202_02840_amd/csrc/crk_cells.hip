@@ -133,41 +133,56 @@ __device__ __forceinline__ int cell_of(double x, double inv_c, int nc) {
 }
 
 // key = (box << 3 bits) | Morton code of the particle's finest cell; the box
-// is found by bisection of the batch's particle offsets
+// is found by bisection of the batch's particle offsets. per_block particles a
+// block (a multiple of its threads); counts: the first digits of the block's
+// keys counted for the sort (null: not wanted)
 __global__ __launch_bounds__(kBlock) void k_keys(const double *x, const double *y, const double *z,
                                                  int64_t n, double inv_c, int nc, int bits,
                                                  const int64_t *__restrict__ boff, int nboxes,
-                                                 const double *H, double L, uint32_t *key, int32_t *val) {
-    int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i >= n) return;
-    int lo = 0, hi = nboxes - 1;
-    while (lo < hi) {
-        int mid = (lo + hi + 1) >> 1;
-        if (boff[mid] <= i) lo = mid;
-        else hi = mid - 1;
+                                                 const double *H, double L, uint32_t *key, int32_t *val,
+                                                 int64_t per_block, int32_t *counts) {
+    __shared__ int cnt[256];
+    static_assert(kBlock == 256, "a thread per digit");
+    cnt[threadIdx.x] = 0;
+    __syncthreads();
+    const int64_t i0 = (int64_t)blockIdx.x * per_block + threadIdx.x;
+    for (int64_t i = i0; i < i0 + per_block && i < n; i += kBlock) {
+        int lo = 0, hi = nboxes - 1;
+        while (lo < hi) {
+            int mid = (lo + hi + 1) >> 1;
+            if (boff[mid] <= i) lo = mid;
+            else hi = mid - 1;
+        }
+        double px = x[i], py = y[i], pz = z[i];
+        if (H && invalid_particle(px, py, pz, H[i], L)) {
+            double4 s = stand_in(i, L);
+            px = s.x;
+            py = s.y;
+            pz = s.z;
+        }
+        uint32_t m = morton3(cell_of(px, inv_c, nc), cell_of(py, inv_c, nc), cell_of(pz, inv_c, nc));
+        m |= (uint32_t)lo << (3 * bits);
+        key[i] = m;
+        val[i] = (int32_t)i;
+        if (counts) atomicAdd(&cnt[m & 255u], 1);
     }
-    double px = x[i], py = y[i], pz = z[i];
-    if (H && invalid_particle(px, py, pz, H[i], L)) {
-        double4 s = stand_in(i, L);
-        px = s.x;
-        py = s.y;
-        pz = s.z;
-    }
-    uint32_t m = morton3(cell_of(px, inv_c, nc), cell_of(py, inv_c, nc), cell_of(pz, inv_c, nc));
-    key[i] = ((uint32_t)lo << (3 * bits)) | m;
-    val[i] = (int32_t)i;
+    if (!counts) return;
+    __syncthreads();
+    counts[(int64_t)blockIdx.x * 256 + threadIdx.x] = cnt[threadIdx.x];
 }
 
-// sorted particles, the permutation for the caller, and the ntot entries of
-// both cell tables cleared (16-byte aligned, four entries a thread; the
-// launch covers both)
+// sorted particles, the permutation for the caller, the walk's counts cleared
+// (the extras' and that of the long rows), and the ntot entries of both cell
+// tables cleared (16-byte aligned, four entries a thread; the launch covers
+// both)
 __global__ __launch_bounds__(kBlock) void k_gather_sorted(const double *x, const double *y,
                                                           const double *z, const double *H,
                                                           const int32_t *perm, int64_t n,
                                                           int stand_ins, double L, double4 *posH,
                                                           int32_t *perm_out, int32_t *cbeg, int32_t *cend,
-                                                          int64_t ntot) {
+                                                          int64_t ntot, int32_t *ecnt, int32_t *longs) {
     int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (k == 0) longs[0] = 0;
     const int4 zero = make_int4(0, 0, 0, 0);
     if (4 * k + 4 <= ntot) {
         ((int4 *)cbeg)[k] = zero;
@@ -178,6 +193,7 @@ __global__ __launch_bounds__(kBlock) void k_gather_sorted(const double *x, const
     if (k >= n) return;
     int32_t i = perm[k];
     perm_out[k] = i;
+    ecnt[k] = 0;
     double4 p = make_double4(x[i], y[i], z[i], H[i]);
     if (stand_ins && invalid_particle(p.x, p.y, p.z, p.w, L)) p = stand_in(i, L);
     posH[k] = p;
@@ -1155,8 +1171,9 @@ static int walk_particles(int64_t n, int lanes) {
     return P;
 }
 
-// Neighbour lists for the current posH / cell tables.
-static crk_status build_lists(crk_ctx *c) {
+// Neighbour lists for the current posH / cell tables (cleared: so are the
+// walk's counts).
+static crk_status build_lists(crk_ctx *c, bool cleared) {
     int64_t n = c->n;
     Levels v = levels(c);
     CRK_TRY(ensure(c, c->ng, (size_t)n * sizeof(int32_t)));
@@ -1178,7 +1195,7 @@ static crk_status build_lists(crk_ctx *c) {
     // long rows: longs[0] counts them, their particles follow
     CRK_TRY(ensure(c, c->longs, (size_t)(n + 1) * sizeof(int32_t)));
     int32_t *longs = (int32_t *)c->longs.p;
-    k_zero_counts<<<nblocks(n / 4 + 1), kBlock, 0, c->stream>>>(ecnt, n, longs);
+    if (!cleared) k_zero_counts<<<nblocks(n / 4 + 1), kBlock, 0, c->stream>>>(ecnt, n, longs);
     {
         KTimer kt_(c, "k_walk");
         const int P = walk_particles(n, c->G_walk);
@@ -1300,26 +1317,34 @@ crk_status build_sorted(crk_ctx *c, const double *x, const double *y, const doub
     uint32_t *key_in;
     int32_t *pm_in;
     CRK_TRY(radix_input(c, key, pm, n, 3 * bits + boxbits, &key_in, &pm_in));
-    k_keys<<<nblocks(n), kBlock, 0, c->stream>>>(x, y, z, n, 1.0 / c->cell, c->nc, bits,
+    int64_t per_block;
+    int32_t *counts;
+    CRK_TRY(radix_count(c, n, 3 * bits + boxbits, &per_block, &counts));
+    const bool counted = per_block > 0;
+    if (!counted) per_block = kBlock;
+    k_keys<<<(unsigned)((n + per_block - 1) / per_block), kBlock, 0, c->stream>>>(x, y, z, n, 1.0 / c->cell, c->nc, bits,
                                                   (const int64_t *)(c->graph_mode ? c->gboff.p : c->boff.p),
-                                                  nboxes, stand_ins ? H : nullptr, c->L, key_in, pm_in);
+                                                  nboxes, stand_ins ? H : nullptr, c->L, key_in, pm_in, per_block,
+                                                  counted ? counts : nullptr);
     CRK_HIP(c, hipGetLastError());
     {
         KTimer kt_(c, "sort");
-        CRK_TRY(radix_sort_pairs(c, key, pm, n, 3 * bits + boxbits, true));
+        CRK_TRY(radix_sort_pairs(c, key, pm, n, 3 * bits + boxbits, true, counted));
     }
     // 3. sorted particles and the cell tables of every level of every box
     CRK_TRY(ensure(c, c->posH, (size_t)n * sizeof(double4)));
     CRK_TRY(ensure(c, c->cbeg, (size_t)ntot * sizeof(int32_t)));
     CRK_TRY(ensure(c, c->cend, (size_t)ntot * sizeof(int32_t)));
+    CRK_TRY(ensure(c, c->ecnt, (size_t)n * sizeof(int32_t)));
+    CRK_TRY(ensure(c, c->longs, (size_t)(n + 1) * sizeof(int32_t)));
     k_gather_sorted<<<nblocks(std::max(n, ntot / 4 + 1)), kBlock, 0, c->stream>>>(
         x, y, z, H, pm, n, stand_ins ? 1 : 0, c->L, (double4 *)c->posH.p, perm, (int32_t *)c->cbeg.p,
-        (int32_t *)c->cend.p, ntot);
+        (int32_t *)c->cend.p, ntot, (int32_t *)c->ecnt.p, (int32_t *)c->longs.p);
     k_tables<<<nblocks(n), kBlock, 0, c->stream>>>(key, n, levels(c), (int32_t *)c->cbeg.p,
                                                     (int32_t *)c->cend.p);
     CRK_HIP(c, hipGetLastError());
     // 4. neighbour lists
-    CRK_TRY(build_lists(c));
+    CRK_TRY(build_lists(c, true));
     if (n_pairs) *n_pairs = c->npairs;
     if (n_cells) *n_cells = c->nc;
     return CRK_OK;
@@ -1344,6 +1369,7 @@ crk_status crk_build_cells_batch(crk_ctx *c, int32_t nboxes, const int64_t *box_
                                  const crk_params *p, double cell_size, int32_t *perm,
                                  int64_t *n_pairs, int32_t *n_cells) {
     if (!c) return CRK_ERR_INVALID_ARG;
+    c->singular_clear = 0;
     if (n < 1 || !x || !y || !z || !H || !p || !perm || nboxes < 1 || !box_offsets)
         return set_err(c, CRK_ERR_INVALID_ARG, "crk_build_cells: n < 1 or NULL argument");
     if (n > INT32_MAX / 2) return set_err(c, CRK_ERR_INVALID_ARG, "n too large");
@@ -1431,7 +1457,7 @@ crk_status crk_update_support(crk_ctx *c, const double *H_sorted, int64_t *n_pai
     if ((k.flags & 4) || !(k.hmin > 0.0)) return set_err(c, CRK_ERR_SUPPORT, "H must be positive");
     if (!(k.hmax < 0.5 * c->L)) return set_err(c, CRK_ERR_SUPPORT, "max H %g >= L/2", k.hmax);
     k_set_H<<<nblocks(n), kBlock, 0, c->stream>>>((double4 *)c->posH.p, H_sorted, n);
-    CRK_TRY(build_lists(c));
+    CRK_TRY(build_lists(c, false));
     if (n_pairs) *n_pairs = c->npairs;
     return CRK_OK;
 }

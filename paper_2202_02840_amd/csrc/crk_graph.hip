@@ -111,6 +111,7 @@ crk_status crk_graph_capture(crk_ctx *c, int32_t nboxes, const int64_t *box_offs
                              const crk_step_io *io, const crk_params *p, double cell_size,
                              double headroom) {
     if (!c) return CRK_ERR_INVALID_ARG;
+    c->singular_clear = 0;
     CRK_TRY(step_args(c, nboxes, box_offsets, n, io, p));
     if (!(headroom >= 0.0 && headroom <= 16.0))
         return set_err(c, CRK_ERR_INVALID_ARG, "headroom must be in [0, 16]");
@@ -202,6 +203,7 @@ crk_status crk_graph_capture(crk_ctx *c, int32_t nboxes, const int64_t *box_offs
 
 crk_status crk_graph_replay(crk_ctx *c, crk_graph_status *out) {
     if (!c) return CRK_ERR_INVALID_ARG;
+    c->singular_clear = 0;
     if (!c->gexec) return set_err(c, CRK_ERR_STATE, "no recorded step (crk_graph_capture)");
     CRK_HIP(c, hipSetDevice(c->device));
     // the context now describes the replayed step

@@ -120,6 +120,8 @@ struct crk_ctx {
 
     // per-pass tuning: lanes per particle (1..64)
     int G_vol = 4, G_mom = 1, G_grad = 4, G_der = 8;
+    // the last moment pass cleared the singular count of the next corrections
+    int singular_clear = 0;
     // mean gather row and mean pair row of the last eager build
     double mean_row = 0.0, mean_pairs = 0.0;
     // volume, moment, velocity-gradient, derivative (and compatible)
@@ -204,8 +206,13 @@ crk_status scan_exclusive_i64(crk_ctx *c, const int64_t *in, int64_t *out, int64
 crk_status scan_counts2(crk_ctx *c, const int32_t *a, const int32_t *b, int64_t n, int64_t *oa,
                         int64_t *ob, int64_t *tot = nullptr, int32_t *ob32 = nullptr);
 // stable LSD radix sort of (key, value) pairs on the low `bits` bits of the keys
-// (with from_input the input lies where radix_input said: no copy at the end)
-crk_status radix_sort_pairs(crk_ctx *c, uint32_t *keys, int32_t *vals, int64_t n, int bits, bool from_input = false);
+// (with from_input the input lies where radix_input said: no copy at the end;
+// with counted its blocks' first digits are counted, as radix_count wants them)
+crk_status radix_sort_pairs(crk_ctx *c, uint32_t *keys, int32_t *vals, int64_t n, int bits, bool from_input = false,
+                            bool counted = false);
+// first digits of the keys for whoever writes them: 256 counts for every
+// per_block keys at counts (per_block 0: not wanted, the set is too large)
+crk_status radix_count(crk_ctx *c, int64_t n, int bits, int64_t *per_block, int32_t **counts);
 // where that sort's input is best written: keys and vals, or, for an odd number
 // of passes, its own buffers
 crk_status radix_input(crk_ctx *c, uint32_t *keys, int32_t *vals, int64_t n, int bits, uint32_t **kin,

@@ -514,6 +514,7 @@ crk_status crk_build_leaves(crk_ctx *c, int32_t nboxes, const int64_t *box_offse
                             int64_t *n_pairs, int32_t *n_leaves, int32_t *leaf_offsets,
                             int64_t leaf_cap) {
     if (!c) return CRK_ERR_INVALID_ARG;
+    c->singular_clear = 0;
     if (n < 1 || !x || !y || !z || !H || !p || !perm || nboxes < 1 || !box_offsets)
         return set_err(c, CRK_ERR_INVALID_ARG, "crk_build_leaves: n < 1 or NULL argument");
     if (n > INT32_MAX / 2) return set_err(c, CRK_ERR_INVALID_ARG, "n too large");

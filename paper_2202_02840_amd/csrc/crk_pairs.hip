@@ -293,13 +293,22 @@ __global__ __launch_bounds__(kBlock) void k_volume(const double4 *__restrict__ p
 __device__ constexpr int kSym2[3][3] = {{0, 1, 2}, {1, 3, 4}, {2, 4, 5}};
 __device__ constexpr int kSym3[3][3][3] = {{{0, 1, 2}, {1, 3, 4}, {2, 4, 5}}, {{1, 3, 4}, {3, 6, 7}, {4, 7, 8}}, {{2, 4, 5}, {4, 7, 8}, {5, 8, 9}}};
 
+// what the moment pass does by the way, a launch less each: the volumes that
+// the build summed to V and nsum (null: not wanted here, or written already),
+// and the singular count of the corrections cleared
+struct MomentExtras {
+    double *V, *nsum;
+    const double *vnsum;
+    unsigned long long *n_singular;
+};
+
 template <typename T, int G>
 __global__ __launch_bounds__(kBlock, 4) void k_moments(const double4 *__restrict__ posH,
                                                     const int64_t *__restrict__ goff,
                                                     const int32_t *__restrict__ gidx,
                                                     const double4 *__restrict__ posV, int64_t n, Box box,
                                                     double *m0, double *m1, double *m2, double *gm0,
-                                                    double *gm1, double *gm2) {
+                                                    double *gm1, double *gm2, MomentExtras ex) {
     // sums: 0 m0 | 1-3 m1 | 4-9 m2 | 10-12 gm0 | 13-18 Q2 | 19-28 Q3
     __shared__ RowTile<G> s_rows[kBlock / 64];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -312,7 +321,13 @@ __global__ __launch_bounds__(kBlock, 4) void k_moments(const double4 *__restrict
         T invH2 = invH * invH;
         T cw = (T)kW * invH2 * invH;
         T cg = (T)kG * invH2 * invH2 * invH;
-        if (l == 0) a[0].add((T)posV[i].w * cw);   // self pair: d = 0, so m0 only
+        if (l == 0) {
+            const double Vi = posV[i].w;
+            a[0].add((T)Vi * cw);   // self pair: d = 0, so m0 only
+            if (ex.V) ex.V[i] = Vi;
+            if (ex.nsum) ex.nsum[i] = ex.vnsum[i];
+            if (i == 0) *ex.n_singular = 0;
+        }
         const int64_t b = goff[i];
         const int cnt = (int)(goff[i + 1] - b);
         const auto term = [&](const double4 &pj) {   // x, y, z and V
@@ -1753,35 +1768,83 @@ __global__ __launch_bounds__(kBlock) void k_zero_marks(int32_t *a, int64_t n, in
     if (i == 0) *c0 = 0;
 }
 
-// (host, pinned: the flagged and the listed rows' counts, read once the stream
-// is done)
-__global__ __launch_bounds__(kBlock) void k_compact(int64_t n, const int64_t *__restrict__ pos,
-                                                    int32_t *list, const int64_t *nflag, int64_t *host) {
-    int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i == 0 && host) {
-        host[0] = *nflag;
-        host[1] = pos[n];
+// The marked rows in ascending order: counted for every kMarkBlock rows, then
+// listed, each block adding up the counts before its own. *total: how many.
+// host (pinned): that and the flagged rows' count, read once the stream is done.
+constexpr int kMarkBlock = 1024;
+__global__ __launch_bounds__(kMarkBlock) void k_mark_sums(const int32_t *__restrict__ mark, int64_t n, int64_t *sums) {
+    __shared__ int s[kMarkBlock / 64];
+    const int64_t i = (int64_t)blockIdx.x * kMarkBlock + threadIdx.x;
+    const uint64_t m = __ballot(i < n && mark[i]);
+    if ((threadIdx.x & 63) == 0) s[threadIdx.x >> 6] = __popcll(m);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int t = 0;
+        for (int q = 0; q < kMarkBlock / 64; q++) t += s[q];
+        sums[blockIdx.x] = t;
     }
-    if (i < n && pos[i + 1] != pos[i]) list[pos[i]] = (int32_t)i;
+}
+__global__ __launch_bounds__(kMarkBlock) void k_mark_list(const int32_t *__restrict__ mark, int64_t n,
+                                                          const int64_t *__restrict__ sums, int32_t *list,
+                                                          int64_t *total, const int64_t *nflag, int64_t *host) {
+    constexpr int W = kMarkBlock / 64;
+    __shared__ int64_t s_before[W];
+    __shared__ int s_here[W];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t i = (int64_t)blockIdx.x * kMarkBlock + threadIdx.x;
+    int64_t before = 0;
+    for (int64_t b = threadIdx.x; b < blockIdx.x; b += kMarkBlock) before += sums[b];
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) before += __shfl_xor(before, o, 64);
+    const uint64_t m = __ballot(i < n && mark[i]);
+    if (lane == 0) {
+        s_before[wave] = before;
+        s_here[wave] = __popcll(m);
+    }
+    __syncthreads();
+    int64_t at = 0, end = 0;
+    for (int q = 0; q < W; q++) {
+        at += s_before[q] + (q < wave ? s_here[q] : 0);
+        end += s_before[q] + s_here[q];
+    }
+    if (m >> lane & 1) list[at + __popcll(m & (((uint64_t)1 << lane) - 1))] = (int32_t)i;
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
+        *total = end;
+        if (host) {
+            host[0] = *nflag;
+            host[1] = end;
+        }
+    }
 }
 
 // FP32 velocity-gradient records: (v, V), then the 32-bit fixed-point
 // position q = floor(x 2^32 / L) (the bits in the float slots)
+// On the way, for the passes that follow: *bad cleared and, in the adaptive
+// mode, the FP64 records r6d written, the marks and the count *nflag cleared.
 __global__ __launch_bounds__(kBlock) void k_pack6_f(int64_t n, const double *v, const double *V,
                                                     const double4 *__restrict__ posH, double qinv,
-                                                    float4 *rec) {
+                                                    float4 *rec, int *bad, double4 *r6d, int32_t *mark,
+                                                    int64_t *nflag) {
     int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (i >= n) return;
-    rec[2 * i] = make_float4((float)v[i], (float)v[n + i], (float)v[2 * n + i], (float)V[i]);
+    const double4 r = make_double4(v[i], v[n + i], v[2 * n + i], V[i]);
+    rec[2 * i] = make_float4((float)r.x, (float)r.y, (float)r.z, (float)r.w);
     const double4 x = posH[i];
     const Fixed fx = fixed_q(x.x, qinv), fy = fixed_q(x.y, qinv), fz = fixed_q(x.z, qinv);
     rec[2 * i + 1] = make_float4(__uint_as_float(fx.q), __uint_as_float(fy.q), __uint_as_float(fz.q),
                                  __uint_as_float(pack_f(fx, fy, fz)));
+    if (r6d) {
+        r6d[i] = r;
+        mark[i] = 0;
+        if (i == 0) *nflag = 0;
+    }
+    if (i == 0) *bad = 0;
 }
 __global__ __launch_bounds__(kBlock) void k_pack6_d(int64_t n, const double *v, const double *V,
-                                                    double4 *rec) {
+                                                    double4 *rec, int *bad) {
     int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (i < n) rec[i] = make_double4(v[i], v[n + i], v[2 * n + i], V[i]);
+    if (i == 0) *bad = 0;
 }
 
 inline unsigned nblocks(int64_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
@@ -1886,8 +1949,13 @@ crk_status volume_moments(crk_ctx *c, int prec, const double4 *posH, const int64
     const int Gm = by_rule ? row_lanes(c, c->G_mom) : c->G_mom;
     CRK_TRY(ensure(c, c->posV, (size_t)n * sizeof(double4)));
     double4 *posV = (double4 *)c->posV.p;
-    if (sizeof(T) == 8 && c->vol_ready) {
+    CRK_TRY(ensure(c, c->misc, 256));
+    MomentExtras ex{nullptr, nullptr, (const double *)c->vnsum.p, (unsigned long long *)c->misc.p + 4};
+    if (sizeof(T) == 8 && c->vol_ready && want_m && Pm == 0) {
         // the build's compaction summed these FP64 volumes with the lists
+        ex.V = V;
+        ex.nsum = nsum;
+    } else if (sizeof(T) == 8 && c->vol_ready) {
         KTimer kt_(c, "k_volume");
         k_volume_out<<<nblocks(n), kBlock, 0, c->stream>>>(n, (const double *)c->vnsum.p, posV, nsum, V);
     } else {
@@ -1909,8 +1977,9 @@ crk_status volume_moments(crk_ctx *c, int prec, const double4 *posH, const int64
             CRK_DISPATCH_P(Pm, L_MOM);
 #undef L_MOM
         } else {
-#define L_MOM(GG) k_moments<T, GG><<<gblocks(n, GG), kBlock, 0, c->stream>>>(posH, goff, gidx, posV, n, box, m0, m1, m2, gm0, gm1, gm2)
+#define L_MOM(GG) k_moments<T, GG><<<gblocks(n, GG), kBlock, 0, c->stream>>>(posH, goff, gidx, posV, n, box, m0, m1, m2, gm0, gm1, gm2, ex)
             CRK_DISPATCH_G(Gm, L_MOM);
+            c->singular_clear = 1;
 #undef L_MOM
         }
     }
@@ -2006,7 +2075,8 @@ crk_status crk_corrections(crk_ctx *c, int64_t n, const double *m0, const double
     CRK_HIP(c, hipSetDevice(c->device));
     CRK_TRY(ensure(c, c->misc, 256));
     unsigned long long *cnt = (unsigned long long *)c->misc.p + 4;
-    CRK_TRY(zero_async(c, cnt, 2));
+    if (!c->singular_clear) CRK_TRY(zero_async(c, cnt, 2));   // (once per clearing moment pass)
+    c->singular_clear = 0;
     {
         KTimer kt_(c, "k_corrections");
         k_corrections<<<nblocks(n), kBlock, 0, c->stream>>>(n, m0, m1, m2, gm0, gm1, gm2, A, B, gA, gB, cnt);
@@ -2035,10 +2105,10 @@ struct AdaptRows {
 // fpos[n] counts the flagged rows (appended in any order: their fix is per
 // row), the int32 words below it mark the touched rows, whose offsets tpos
 // list them in ascending order (rows of neighbouring particles side by side
-// share their partners' loads in the fix). First the buffers, the cleared
-// marks and counter; the flagging follows (k_flag, or the record packing of
+// share their partners' loads in the fix). First the buffers and (clear) the
+// cleared marks and counter; the flagging follows (k_flag, or the record packing of
 // the derivative call), then adapt_finish.
-static crk_status adapt_prep(crk_ctx *c, AdaptRows &r) {
+static crk_status adapt_prep(crk_ctx *c, AdaptRows &r, bool clear) {
     const int64_t n = c->n;
     CRK_TRY(ensure(c, c->flag, (size_t)n * sizeof(int32_t)));
     CRK_TRY(ensure(c, c->flist, (size_t)n * sizeof(int32_t)));
@@ -2049,7 +2119,7 @@ static crk_status adapt_prep(crk_ctx *c, AdaptRows &r) {
     r.flist = (int32_t *)c->flist.p;
     r.tlist = (int32_t *)c->tlist.p;
     int64_t *fpos = (int64_t *)c->fpos.p;
-    k_zero_marks<<<nblocks(n), kBlock, 0, c->stream>>>((int32_t *)fpos, n, fpos + n);
+    if (clear) k_zero_marks<<<nblocks(n), kBlock, 0, c->stream>>>((int32_t *)fpos, n, fpos + n);
     CRK_HIP(c, hipGetLastError());
     return CRK_OK;
 }
@@ -2068,8 +2138,10 @@ static crk_status adapt_finish(crk_ctx *c, bool gm, AdaptRows &r) {
         int32_t *mark = (int32_t *)fpos;
         k_mark<<<(unsigned)std::min<int64_t>(nblocks(n * 16), 1024), kBlock, 0, c->stream>>>(
             r.flist, fpos + n, goff, gidx, eb, ee, eidx, mark);
-        CRK_TRY(scan_counts2(c, mark, nullptr, n, tpos, nullptr));
-        k_compact<<<nblocks(n), kBlock, 0, c->stream>>>(n, tpos, r.tlist, fpos + n, gm ? nullptr : pin);
+        // (tpos: the blocks' counts, and at n the total)
+        const unsigned mb = (unsigned)((n + kMarkBlock - 1) / kMarkBlock);
+        k_mark_sums<<<mb, kMarkBlock, 0, c->stream>>>(mark, n, tpos);
+        k_mark_list<<<mb, kMarkBlock, 0, c->stream>>>(mark, n, tpos, r.tlist, tpos + n, fpos + n, gm ? nullptr : pin);
     }
     CRK_HIP(c, hipGetLastError());
     if (gm) {
@@ -2092,7 +2164,7 @@ static crk_status adapt_finish(crk_ctx *c, bool gm, AdaptRows &r) {
 static crk_status adapt_rows(crk_ctx *c, const crk_params *p, const double *A, const double *B,
                              const double *gA, const double *gB, bool gm, AdaptRows &r) {
     const int64_t n = c->n;
-    CRK_TRY(adapt_prep(c, r));
+    CRK_TRY(adapt_prep(c, r, true));
     {
         KTimer kt_(c, "k_flag");
         k_flag<<<nblocks(n), kBlock, 0, c->stream>>>(n, (const double4 *)c->posH.p, A, B, gA, gB,
@@ -2136,8 +2208,7 @@ crk_status crk_derivatives(crk_ctx *c, const crk_params *p, const double *v, con
     const bool adapt = p->precision == CRK_MIXED_ADAPT;
     const DerivPrm dp = deriv_prm(p);
     CRK_TRY(ensure(c, c->misc, 256));
-    int *bad = (int *)c->misc.p + 2;
-    CRK_TRY(zero_async(c, bad, 1));
+    int *bad = (int *)c->misc.p + 2;   // (cleared by the first packing)
     // derivative pass: P_der particles a wave in balanced lane groups, or, at
     // 0, groups of G_der lanes
     const int Gg = row_lanes(c, c->G_grad), Gd = fix_lanes(c, c->G_der), Pg = c->P_grad;
@@ -2151,7 +2222,7 @@ crk_status crk_derivatives(crk_ctx *c, const crk_params *p, const double *v, con
     // part of a flagged particle's record (its pairs are left to FP64)
     const bool gm = c->graph_mode != 0;
     AdaptRows ar;
-    if (adapt) CRK_TRY(adapt_prep(c, ar));
+    if (adapt) CRK_TRY(adapt_prep(c, ar, false));   // (the first packing clears)
 
     if (f32) {
         CRK_TRY(ensure(c, c->rec6, (size_t)n * 2 * sizeof(float4)));
@@ -2166,8 +2237,10 @@ crk_status crk_derivatives(crk_ctx *c, const crk_params *p, const double *v, con
         }
         {
             KTimer kt_(c, "k_pack");
-            k_pack6_f<<<nblocks(n), kBlock, 0, c->stream>>>(n, v, V, posH, dp.qinv, r6);
-            if (adapt) k_pack6_d<<<nblocks(n), kBlock, 0, c->stream>>>(n, v, V, r6d);
+            int64_t *fpos = (int64_t *)c->fpos.p;
+            k_pack6_f<<<nblocks(n), kBlock, 0, c->stream>>>(n, v, V, posH, dp.qinv, r6, bad, r6d,
+                                                            adapt ? (int32_t *)fpos : nullptr,
+                                                            adapt ? fpos + n : nullptr);
         }
         {
             KTimer kt_(c, "k_gradv");
@@ -2225,7 +2298,7 @@ crk_status crk_derivatives(crk_ctx *c, const crk_params *p, const double *v, con
         double4 *r6 = (double4 *)c->rec6.p, *r7 = (double4 *)c->rec7.p;
         {
             KTimer kt_(c, "k_pack");
-            k_pack6_d<<<nblocks(n), kBlock, 0, c->stream>>>(n, v, V, r6);
+            k_pack6_d<<<nblocks(n), kBlock, 0, c->stream>>>(n, v, V, r6, bad);
         }
         {
             KTimer kt_(c, "k_gradv");

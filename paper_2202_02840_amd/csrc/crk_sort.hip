@@ -366,8 +366,8 @@ crk_status scan_counts2(crk_ctx *c, const int32_t *a, const int32_t *b, int64_t 
 
 template <int ITEMS, bool DIRECT>
 static crk_status radix_pass(crk_ctx *c, const uint32_t *ka, const int32_t *va, uint32_t *kb, int32_t *vb, int64_t n,
-                             int shift, int64_t nblk, int64_t *hist) {
-    k_radix_hist<ITEMS, DIRECT><<<(unsigned)nblk, kBlock, 0, c->stream>>>(ka, n, shift, nblk, hist);
+                             int shift, int64_t nblk, int64_t *hist, bool counted) {
+    if (!counted) k_radix_hist<ITEMS, DIRECT><<<(unsigned)nblk, kBlock, 0, c->stream>>>(ka, n, shift, nblk, hist);
     CRK_HIP(c, hipGetLastError());
     if (!DIRECT) CRK_TRY(scan_exclusive_i64(c, hist, hist, nblk * kBuckets));
     k_radix_scatter<ITEMS, DIRECT><<<(unsigned)nblk, kBlock, 0, c->stream>>>(ka, va, kb, vb, n, shift, nblk, hist);
@@ -385,14 +385,31 @@ crk_status radix_input(crk_ctx *c, uint32_t *keys, int32_t *vals, int64_t n, int
     return CRK_OK;
 }
 
-crk_status radix_sort_pairs(crk_ctx *c, uint32_t *keys, int32_t *vals, int64_t n, int bits, bool from_input) {
+// keys of a block, and how many blocks
+static int64_t radix_tile(int64_t n) {
+    return (int64_t)kBlock * (n <= kDirectBlocks * kBlock * kSortItemsSmall ? kSortItemsSmall : kSortItems);
+}
+static crk_status radix_hist(crk_ctx *c, int64_t n, int64_t *nblk) {
+    *nblk = (n + radix_tile(n) - 1) / radix_tile(n);
+    return ensure(c, c->hist, (size_t)*nblk * kBuckets * (*nblk <= kDirectBlocks ? sizeof(int32_t) : sizeof(int64_t)));
+}
+
+crk_status radix_count(crk_ctx *c, int64_t n, int bits, int64_t *per_block, int32_t **counts) {
+    int64_t nblk;
+    CRK_TRY(radix_hist(c, n, &nblk));
+    *per_block = n > 1 && bits > 0 && nblk <= kDirectBlocks ? radix_tile(n) : 0;
+    *counts = (int32_t *)c->hist.p;
+    return CRK_OK;
+}
+
+crk_status radix_sort_pairs(crk_ctx *c, uint32_t *keys, int32_t *vals, int64_t n, int bits, bool from_input,
+                            bool counted) {
     if (n <= 1 || bits <= 0) return CRK_OK;
-    const bool small = n <= kDirectBlocks * kBlock * kSortItemsSmall;
-    const int64_t tile = (int64_t)kBlock * (small ? kSortItemsSmall : kSortItems);
-    int64_t nblk = (n + tile - 1) / tile;
+    const bool small = radix_tile(n) == (int64_t)kBlock * kSortItemsSmall;
+    int64_t nblk;
+    CRK_TRY(radix_hist(c, n, &nblk));
     CRK_TRY(ensure(c, c->keyB, (size_t)n * sizeof(uint32_t)));
     CRK_TRY(ensure(c, c->valB, (size_t)n * sizeof(int32_t)));
-    CRK_TRY(ensure(c, c->hist, (size_t)nblk * kBuckets * (nblk <= kDirectBlocks ? sizeof(int32_t) : sizeof(int64_t))));
     uint32_t *ka = keys, *kb = (uint32_t *)c->keyB.p;
     int32_t *va = vals, *vb = (int32_t *)c->valB.p;
     int64_t *hist = (int64_t *)c->hist.p;
@@ -403,9 +420,10 @@ crk_status radix_sort_pairs(crk_ctx *c, uint32_t *keys, int32_t *vals, int64_t n
     }
     for (int p = 0; p < passes; p++) {
         int shift = p * kRadixBits;
-        if (small) CRK_TRY((radix_pass<kSortItemsSmall, true>(c, ka, va, kb, vb, n, shift, nblk, hist)));
-        else if (nblk <= kDirectBlocks) CRK_TRY((radix_pass<kSortItems, true>(c, ka, va, kb, vb, n, shift, nblk, hist)));
-        else CRK_TRY((radix_pass<kSortItems, false>(c, ka, va, kb, vb, n, shift, nblk, hist)));
+        const bool have = counted && p == 0;
+        if (small) CRK_TRY((radix_pass<kSortItemsSmall, true>(c, ka, va, kb, vb, n, shift, nblk, hist, have)));
+        else if (nblk <= kDirectBlocks) CRK_TRY((radix_pass<kSortItems, true>(c, ka, va, kb, vb, n, shift, nblk, hist, have)));
+        else CRK_TRY((radix_pass<kSortItems, false>(c, ka, va, kb, vb, n, shift, nblk, hist, have)));
         std::swap(ka, kb);
         std::swap(va, vb);
     }
