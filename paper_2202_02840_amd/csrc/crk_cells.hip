@@ -840,12 +840,19 @@ __global__ __launch_bounds__(kBlock) void k_walk_long(const double4 *__restrict_
 // dependent stores, so the atomics' round trips overlap instead of
 // following one another.
 //
-// With vnsum, each row's FP64 volume sum of eq. (vol) comes along: the
-// group re-reads its row (in cache) and adds W(r_ij, H_i) over the self
-// pair and every gather entry, the terms of the volume pass (same
-// separations, square root and weight) in another order; n_i goes to
-// vnsum[i] and (x_i, V_i = 1 / n_i) to posV[i]. The rows past cap get
-// theirs from k_volume_longs after the second walk.
+// With vnsum, each row's FP64 volume sum of eq. (vol) comes along: W(r_ij, H_i)
+// over the self pair and every gather entry, the terms of the volume pass
+// (same separations, square root and weight), summed in the order k = l,
+// l + G, ... of each lane; n_i goes to vnsum[i] and (x_i, V_i = 1 / n_i) to
+// posV[i]. The rows past cap get theirs from k_volume_longs after the second
+// walk.
+//
+// Bound: latency (three quarters of the wavefronts' time is waits) and the
+// extras' scattered 4-byte stores. The partners' positions load while the
+// atomics are on their way; with the row read again for the volumes once the
+// scatter was done, and eight entries at a time, 128^3 took 1.235 ms, three
+// entries (68 VGPRs, seven wavefronts a SIMD) 1.056; two 1.043, but 268
+// neighbours 0.229 ms against 0.212 (0.25 before).
 template <int G, int U>
 __global__ __launch_bounds__(kBlock) void k_compact_rows(const uint32_t *__restrict__ scratch, int cap,
                                                          int64_t n, const int32_t *__restrict__ ng,
@@ -865,56 +872,51 @@ __global__ __launch_bounds__(kBlock) void k_compact_rows(const uint32_t *__restr
     }
     const uint32_t *row = scratch + (size_t)i * cap;
     const int64_t gw = goff[i];
+    double4 pi = make_double4(0.0, 0.0, 0.0, 1.0);
+    if (vnsum) pi = posH[i];
+    const double invH = 1.0 / pi.w;
+    const double cw = kW * invH * invH * invH;
+    double sum = l == 0 ? cw : 0.0;   // the self pair: W(0, H_i)
     for (int k0 = l; k0 < cnt; k0 += G * U) {
         uint32_t w[U];
 #pragma unroll
         for (int u = 0; u < U; u++) w[u] = k0 + u * G < cnt ? row[k0 + u * G] : 0u;
-        bool ex[U];
+        // the partners' positions are on their way before the stores and atomics
+        double4 pj[U];
+        if (vnsum)
 #pragma unroll
-        for (int u = 0; u < U; u++) {
-            const int k = k0 + u * G;
-            ex[u] = k < cnt && (w[u] & 0x80000000u);
-            if (k < cnt) gidx[gw + k] = (int32_t)(w[u] & 0x7fffffffu);
-        }
+            for (int u = 0; u < U; u++) pj[u] = posH[k0 + u * G < cnt ? w[u] & 0x7fffffffu : (uint32_t)i];
         // the returned places are used only after every atomic is issued
         // (efill[j] starts at row j's offset, so the atomic returns the place)
         int32_t at[U];
 #pragma unroll
         for (int u = 0; u < U; u++) {
+            const int k = k0 + u * G;
             at[u] = -1;
-            if (ex[u]) at[u] = atomicAdd(&efill[(int32_t)(w[u] & 0x7fffffffu)], 1);
+            if (k < cnt) {
+                gidx[gw + k] = (int32_t)(w[u] & 0x7fffffffu);
+                if (w[u] & 0x80000000u) at[u] = atomicAdd(&efill[(int32_t)(w[u] & 0x7fffffffu)], 1);
+            }
         }
+        if (vnsum)
+#pragma unroll
+            for (int u = 0; u < U; u++) {
+                if (k0 + u * G >= cnt) break;
+                const double dx = pair_image(pi.x - pj[u].x, box), dy = pair_image(pi.y - pj[u].y, box),
+                             dz = pair_image(pi.z - pj[u].z, box);
+                const double q = sqrt_dist(dx * dx + dy * dy + dz * dz) * invH;
+                sum += kernel_w(q, cw);
+            }
 #pragma unroll
         for (int u = 0; u < U; u++)
             if (at[u] >= 0) etmp[at[u]] = (int32_t)i;
     }
     if (vnsum) {
-        const double4 pi = posH[i];
-        const double invH = 1.0 / pi.w;
-        const double cw = kW * invH * invH * invH;
-        double s = l == 0 ? cw : 0.0;   // the self pair: W(0, H_i)
-        // four partners' positions in flight at a time; the terms are added
-        // in the order k = l, l + G, ... all the same
-        constexpr int VB = 4;
-        for (int k0 = l; k0 < cnt; k0 += VB * G) {
-            double4 pj[VB];
 #pragma unroll
-            for (int u = 0; u < VB; u++)
-                if (k0 + u * G < cnt) pj[u] = posH[row[k0 + u * G] & 0x7fffffffu];
-#pragma unroll
-            for (int u = 0; u < VB; u++) {
-                if (k0 + u * G >= cnt) break;
-                const double dx = pair_image(pi.x - pj[u].x, box), dy = pair_image(pi.y - pj[u].y, box),
-                             dz = pair_image(pi.z - pj[u].z, box);
-                const double q = sqrt_dist(dx * dx + dy * dy + dz * dz) * invH;
-                s += kernel_w(q, cw);
-            }
-        }
-#pragma unroll
-        for (int m = G / 2; m >= 1; m >>= 1) s += __shfl_xor(s, m, G);
+        for (int m = G / 2; m >= 1; m >>= 1) sum += __shfl_xor(sum, m, G);
         if (l == 0) {
-            vnsum[i] = s;
-            posV[i] = make_double4(pi.x, pi.y, pi.z, 1.0 / s);
+            vnsum[i] = sum;
+            posV[i] = make_double4(pi.x, pi.y, pi.z, 1.0 / sum);
         }
     }
 }
@@ -1252,7 +1254,7 @@ static crk_status build_lists(crk_ctx *c, bool cleared) {
     const Box box{c->L, 1.0 / c->L};
     // (the long rows' volumes take the same lanes per row, so a row's sum
     // does not depend on which of the two kernels forms it)
-    constexpr int GC = 16, UC = 8;
+    constexpr int GC = 16, UC = 3;
     {
         KTimer kt_(c, "k_compact_rows");
         k_compact_rows<GC, UC><<<(unsigned)((n * GC + kBlock - 1) / kBlock), kBlock, 0, c->stream>>>(
