@@ -45,8 +45,8 @@ VALU_PEAK_PACKED_FP32 = 157.3
 # source (pair_deriv in crk_pairs.hip, an FMA counted as two flops, sqrt,
 # reciprocal and exp as one, the separation d not counted): 187 flops per
 # ordered pair, 4 of them the sums; bytes per particle: the packed record
-# (FP32: 144 bytes, the position riding in its padding as 42-bit fixed
-# point; FP64: 256 of 288, plus x, y, z (24)), m (8), row offsets (16),
+# (FP32: 128 bytes and the position as 42-bit fixed point in 16 more; FP64:
+# 256, plus x, y, z (24)), m (8), row offsets (16),
 # outputs (32); per ordered pair its 4-byte index
 DERIV_FLOPS_PER_PAIR = 187
 DERIV_BYTES_PER_PARTICLE = {"mixed": 144 + 8 + 16 + 32, "fp64": 24 + 256 + 8 + 16 + 32}
