@@ -287,7 +287,9 @@ __global__ __launch_bounds__(kBlock) void k_volume(const double4 *__restrict__ p
 // Bound by FP64 vector instructions (76 a pair) where the loads keep up:
 // 128^3, four lanes a row, 0.92 ms with the index rows read in the loop, 0.84
 // with them tiled through LDS and two records ahead; 64^3, one lane a row, 0.41
-// and 0.22 ms. Four wavefronts a SIMD: five would spill the 29 sums.
+// and 0.22 ms. Four wavefronts a SIMD: five would spill the 29 sums. The FP32
+// sums, compensated, take three (32^3 lattice, one lane a row: 0.057 ms with four
+// and one record ahead, 0.048 so; 64^3 0.123 and 0.128, 100^3 0.494 and 0.474).
 // index of the symmetric pair (a, b) among (0,0),(0,1),(0,2),(1,1),(1,2),(2,2),
 // and of the sorted triple (a, b, c) among the ten triples in lexicographic order
 __device__ constexpr int kSym2[3][3] = {{0, 1, 2}, {1, 3, 4}, {2, 4, 5}};
@@ -303,12 +305,10 @@ struct MomentExtras {
 };
 
 template <typename T, int G>
-__global__ __launch_bounds__(kBlock, 4) void k_moments(const double4 *__restrict__ posH,
-                                                    const int64_t *__restrict__ goff,
-                                                    const int32_t *__restrict__ gidx,
-                                                    const double4 *__restrict__ posV, int64_t n, Box box,
-                                                    double *m0, double *m1, double *m2, double *gm0,
-                                                    double *gm1, double *gm2, MomentExtras ex) {
+__global__ __launch_bounds__(kBlock, sizeof(T) == 8 ? 4 : 3) void k_moments(
+    const double4 *__restrict__ posH, const int64_t *__restrict__ goff, const int32_t *__restrict__ gidx,
+    const double4 *__restrict__ posV, int64_t n, Box box, double *m0, double *m1, double *m2, double *gm0,
+    double *gm1, double *gm2, MomentExtras ex) {
     // sums: 0 m0 | 1-3 m1 | 4-9 m2 | 10-12 gm0 | 13-18 Q2 | 19-28 Q3
     __shared__ RowTile<G> s_rows[kBlock / 64];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -359,8 +359,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_moments(const double4 *__restrict
 #pragma unroll
                     for (int z = y; z < 3; z++) a[19 + kSym3[x][y][z]].add(u * dd[kSym2[x][y]] * d[z]);
         };
-        row_sum<G, sizeof(T) == 8 ? 2 : 1>(s_rows[wave], gidx, b, cnt, (int32_t)i, lane,
-                                           [&](int32_t j) { return posV[j]; }, term);
+        row_sum<G, 2>(s_rows[wave], gidx, b, cnt, (int32_t)i, lane, [&](int32_t j) { return posV[j]; }, term);
     }
     group_reduce<T, G, 29>(a);
     if (i < n && l == 0) {
