@@ -1279,9 +1279,15 @@ static crk_status build_lists(crk_ctx *c, bool cleared) {
     // each extras row ascending in the emitting particle
     {
         KTimer kt_(c, "k_extra_rank");
-        constexpr int GR = 8;
-        k_extra_rank<GR, 128><<<(unsigned)((n * GR + kBlock - 1) / kBlock), kBlock, 0, c->stream>>>(
-            eoff, etmp, n, eidx, (int32_t *)c->eb.p, (int32_t *)c->ee.p);
+        // longer rows, more lanes and room for each: with 13 extras a particle
+        // (128^3) 0.170 ms with 8 lanes and rows of 128, 0.203 with 16 and 256;
+        // with 74 (45^3, 268 neighbours) 0.198 and 0.108. (In graph mode the last
+        // eager build's: the order is the same for both.)
+        const double mean = c->graph_mode ? c->mean_pairs - c->mean_row : (double)E / (double)n;
+#define L_RANK(GR, CAP) k_extra_rank<GR, CAP><<<(unsigned)((n * GR + kBlock - 1) / kBlock), kBlock, 0, c->stream>>>(eoff, etmp, n, eidx, (int32_t *)c->eb.p, (int32_t *)c->ee.p)
+        if (mean > 32.0) L_RANK(16, 256);
+        else L_RANK(8, 128);
+#undef L_RANK
     }
     CRK_HIP(c, hipGetLastError());
     if (c->graph_mode) {
