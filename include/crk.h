@@ -584,9 +584,10 @@ crk_status crk_set_wave_mapping(crk_ctx *ctx, int32_t vol_ppw, int32_t mom_ppw, 
 /* Lanes per particle of the four pair passes (volume, moments, velocity
  * gradient, derivatives): each particle's neighbour row is split over a
  * group of g lanes of one wavefront, g a power of two in 1..64; 0 keeps the
- * current value. The FP64 moment pass and the velocity gradient take more
- * lanes (up to 16) where rows are long or particles few. Tuning only: results
- * agree to rounding for every g. */
+ * current value. The velocity gradient takes more lanes (up to 16) where rows
+ * are long or particles few. Tuning only: results agree to rounding for every
+ * g (the corrections of a particle with a near-singular m2 to that of its
+ * moments, amplified). */
 crk_status crk_set_lanes(crk_ctx *ctx, int32_t g_vol, int32_t g_mom, int32_t g_grad,
                          int32_t g_der);
 

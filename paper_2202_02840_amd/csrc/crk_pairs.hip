@@ -1888,13 +1888,13 @@ inline unsigned pblocks(int64_t n, int P) {
     return (unsigned)(((n + P - 1) / P + kBlock / 64 - 1) / (kBlock / 64));
 }
 
-// Lanes per row of the FP64 moment pass and of the velocity gradient, from the
-// lanes asked for up to 16: at most 28 entries of a mean row a lane, and 4096
-// wavefronts, half of what the device holds, so that the last ones end
-// together (45^3 with 268 neighbours: moments 0.313 ms with 4 lanes, 0.152
-// with 16; gradient 0.302 and 0.122. 40^3, 1000 wavefronts at one lane: 0.122
-// with 1, 0.045 with 4, 0.042 with 8). More lanes than that cost more in the
-// reduction at a row's end (128^3: 0.84, 0.98 and 1.45 ms with 4, 8 and 16).
+// Lanes per row of the velocity gradient, from the lanes asked for up to 16: at
+// most 28 entries of a mean row a lane, and 4096 wavefronts, half of what the
+// device holds, so that the last ones end together (45^3 with 268 neighbours:
+// 0.302 ms with 4 lanes, 0.122 with 16). The gradient's sums take another order
+// at no more than their own rounding; the moments keep the lanes asked for, since
+// the corrections of a particle with a near-singular m2 amplify the last bit of
+// its sums without bound (the same order, the same corrections).
 int row_lanes(const crk_ctx *c, int G) {
     while (G < 16 && (c->n * G < (int64_t)64 * 4096 || c->mean_row > 28.0 * G)) G *= 2;
     return G;
@@ -1934,18 +1934,10 @@ __global__ __launch_bounds__(kBlock) void k_volume_out(int64_t n, const double *
 }
 
 template <typename T>
-crk_status volume_moments(crk_ctx *c, int prec, const double4 *posH, const int64_t *goff, const int32_t *gidx,
+crk_status volume_moments(crk_ctx *c, const double4 *posH, const int64_t *goff, const int32_t *gidx,
                           int64_t n, Box box, double *nsum, double *V, T *rv, bool want_m, double *m0,
                           double *m1, double *m2, double *gm0, double *gm1, double *gm2) {
-    const int Gv = c->G_vol, Pv = c->P_vol, Pm = c->P_mom;
-    // (FP32 sums depend on the lanes at the rounding of a term: they keep the
-    // lanes asked for. So do FP64 ones of large sets, which have particles
-    // whose corrections hang on the last bits of the moments, and those that
-    // FP32 passes go on from, where another order of the sums moves a rounding
-    // of the corrections to FP32; long rows and small sets have most to gain
-    // and least of either)
-    const bool by_rule = sizeof(T) == 8 && (n <= (int64_t)1 << (prec == CRK_FP64 ? 16 : 14) || c->mean_row > 112.0);
-    const int Gm = by_rule ? row_lanes(c, c->G_mom) : c->G_mom;
+    const int Gv = c->G_vol, Pv = c->P_vol, Gm = c->G_mom, Pm = c->P_mom;
     CRK_TRY(ensure(c, c->posV, (size_t)n * sizeof(double4)));
     double4 *posV = (double4 *)c->posV.p;
     CRK_TRY(ensure(c, c->misc, 256));
@@ -2054,10 +2046,10 @@ crk_status crk_moments(crk_ctx *c, const crk_params *p, double *nsum, double *V,
     CRK_TRY(ensure(c, c->recV, (size_t)n * (f32 ? 4 : 8)));
     if (f32) {
         float *rv = (float *)c->recV.p;
-        CRK_TRY(volume_moments<float>(c, p->precision, posH, goff, gidx, n, box, nsum, V, rv, want_m, m0, m1, m2, gm0, gm1, gm2));
+        CRK_TRY(volume_moments<float>(c, posH, goff, gidx, n, box, nsum, V, rv, want_m, m0, m1, m2, gm0, gm1, gm2));
     } else {
         double *rv = (double *)c->recV.p;
-        CRK_TRY(volume_moments<double>(c, p->precision, posH, goff, gidx, n, box, nsum, V, rv, want_m, m0, m1, m2, gm0, gm1, gm2));
+        CRK_TRY(volume_moments<double>(c, posH, goff, gidx, n, box, nsum, V, rv, want_m, m0, m1, m2, gm0, gm1, gm2));
     }
     CRK_HIP(c, hipGetLastError());
     c->have_V = 1;
