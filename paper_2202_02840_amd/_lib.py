@@ -539,11 +539,14 @@ class Context:
     def graph_replay(self, status: bool = True, check: bool = True):
         """Replay the recorded step; with status, wait and return (status
         code, status dict). check raises on an error code."""
+        gs = GraphStatus() if status else None
+        st = lib().crk_graph_replay(self._h, C.byref(gs) if status else None)
+        io = getattr(self, "_graph_io", None)
+        if io is not None:   # the context describes the recorded step again
+            self.n, self.perm = io["x"].shape[0], io["perm"]
         if not status:
-            self._check(lib().crk_graph_replay(self._h, None), "crk_graph_replay")
+            self._check(st, "crk_graph_replay")
             return 0, None
-        gs = GraphStatus()
-        st = lib().crk_graph_replay(self._h, C.byref(gs))
         if check:
             self._check(st, "crk_graph_replay")
         self.n_pairs = gs.n_pairs

@@ -1303,7 +1303,7 @@ static crk_status build_lists(crk_ctx *c, bool cleared) {
     }
     c->built = 1;
     c->have_V = 0;
-    c->vol_ready = vol ? 1 : 0;
+    c->vol_ready = c->vol_posV = vol ? 1 : 0;
     return CRK_OK;
 }
 

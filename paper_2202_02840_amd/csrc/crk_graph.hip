@@ -198,6 +198,7 @@ crk_status crk_graph_capture(crk_ctx *c, int32_t nboxes, const int64_t *box_offs
     c->geo.cell = c->cell;
     c->geo.nc = c->nc;
     c->geo.bits = c->bits;
+    c->geo.vol = c->vol_in_build;
     return CRK_OK;
 }
 
@@ -218,6 +219,8 @@ crk_status crk_graph_replay(crk_ctx *c, crk_graph_status *out) {
     c->built = 1;
     c->have_V = 1;
     c->prec_V = c->graph_prec;
+    // its volumes too (vnsum has the recorded size: growing it drops the graph)
+    c->vol_in_build = c->vol_ready = c->vol_posV = c->geo.vol;
     CRK_HIP(c, hipGraphLaunch(c->gexec, c->stream));
     if (!out) return CRK_OK;
     GraphStat *pin = (GraphStat *)((char *)c->pinned.p + 3072);

@@ -63,10 +63,11 @@ struct crk_ctx {
     int64_t nboxes = 1;
     int built = 0;          // lists valid
     int have_V = 0;         // recV valid (after crk_moments)
-    // FP64 volumes summed by the build's compaction (vnsum, and V in posV.w)
-    // for the current lists: wanted when the build's precision is not the
-    // pure FP32 one, valid until the lists or the supports change
-    int vol_in_build = 0, vol_ready = 0;
+    // FP64 volumes summed by the build's compaction (vnsum) for the current
+    // lists: wanted when the build's precision is not the pure FP32 one, valid
+    // until the lists or the supports change; vol_posV: posV.w holds their V
+    // (until a volume pass writes its own there)
+    int vol_in_build = 0, vol_ready = 0, vol_posV = 0;
     int prec_V = -1;        // precision recV was written in
     int64_t npairs = 0;     // sum of |N_s(i)|
     int64_t ngather = 0;    // sum of ng (excludes self)
@@ -111,8 +112,8 @@ struct crk_ctx {
     struct Geo {
         int64_t n, ntab, nboxes, lvl_off[12];
         double L, cell;
-        int nc, bits;
-    } geo{};                              // geometry the graph was recorded with
+        int nc, bits, vol;                // vol: the build sums the volumes
+    } geo{};                              // the recorded step's geometry and state
     int G_hsolve = 16, hs_round = 12, hs_cap = 320;
     double hs_factor = 1.15;
     int64_t last_nflag = 0, last_ntouch = 0;

@@ -1922,15 +1922,17 @@ int fix_lanes(const crk_ctx *c, int G) {
 
 // volume then (optionally) moment pass in type T, with the lane mapping of
 // the context (balanced groups of P particles per wave, or G lanes each)
-// n_i and V_i of the volumes the build summed (vnsum, posV.w) into the
-// caller's arrays
-__global__ __launch_bounds__(kBlock) void k_volume_out(int64_t n, const double *__restrict__ vnsum,
-                                                       const double4 *__restrict__ posV, double *nsum,
-                                                       double *V) {
+// n_i of the volumes the build summed (vnsum) and V_i = 1 / n_i into the
+// caller's arrays, V_i also beside the positions (where an FP32 volume pass may
+// have left its own)
+__global__ __launch_bounds__(kBlock) void k_volume_out(int64_t n, const double *__restrict__ vnsum, double4 *posV,
+                                                       double *nsum, double *V) {
     const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (i >= n) return;
-    if (nsum) nsum[i] = vnsum[i];
-    V[i] = posV[i].w;
+    const double ns = vnsum[i], Vi = 1.0 / ns;
+    if (nsum) nsum[i] = ns;
+    V[i] = Vi;
+    posV[i].w = Vi;
 }
 
 template <typename T>
@@ -1942,15 +1944,17 @@ crk_status volume_moments(crk_ctx *c, const double4 *posH, const int64_t *goff, 
     double4 *posV = (double4 *)c->posV.p;
     CRK_TRY(ensure(c, c->misc, 256));
     MomentExtras ex{nullptr, nullptr, (const double *)c->vnsum.p, (unsigned long long *)c->misc.p + 4};
-    if (sizeof(T) == 8 && c->vol_ready && want_m && Pm == 0) {
+    if (sizeof(T) == 8 && c->vol_ready && c->vol_posV && want_m && Pm == 0) {
         // the build's compaction summed these FP64 volumes with the lists
         ex.V = V;
         ex.nsum = nsum;
     } else if (sizeof(T) == 8 && c->vol_ready) {
         KTimer kt_(c, "k_volume");
+        c->vol_posV = 1;
         k_volume_out<<<nblocks(n), kBlock, 0, c->stream>>>(n, (const double *)c->vnsum.p, posV, nsum, V);
     } else {
         KTimer kt_(c, "k_volume");
+        c->vol_posV = 0;
         if (Pv > 0) {
 #define L_VOL(PP) k_volume_bal<T, PP><<<pblocks(n, PP), kBlock, 0, c->stream>>>(posH, goff, gidx, n, box, nsum, V, rv, posV)
             CRK_DISPATCH_P(Pv, L_VOL);
