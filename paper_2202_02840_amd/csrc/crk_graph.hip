@@ -199,6 +199,7 @@ crk_status crk_graph_capture(crk_ctx *c, int32_t nboxes, const int64_t *box_offs
     c->geo.nc = c->nc;
     c->geo.bits = c->bits;
     c->geo.vol = c->vol_in_build;
+    c->geo.ts = c->ts_valid;
     return CRK_OK;
 }
 
@@ -221,6 +222,8 @@ crk_status crk_graph_replay(crk_ctx *c, crk_graph_status *out) {
     c->prec_V = c->graph_prec;
     // its volumes too (vnsum has the recorded size: growing it drops the graph)
     c->vol_in_build = c->vol_ready = c->vol_posV = c->geo.vol;
+    // and the maxima of crk_timestep, or none
+    c->ts_valid = c->geo.ts;
     CRK_HIP(c, hipGraphLaunch(c->gexec, c->stream));
     if (!out) return CRK_OK;
     GraphStat *pin = (GraphStat *)((char *)c->pinned.p + 3072);

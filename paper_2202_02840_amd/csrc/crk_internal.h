@@ -112,7 +112,7 @@ struct crk_ctx {
     struct Geo {
         int64_t n, ntab, nboxes, lvl_off[12];
         double L, cell;
-        int nc, bits, vol;                // vol: the build sums the volumes
+        int nc, bits, vol, ts;            // vol: the build sums the volumes; ts: the maxima of crk_timestep
     } geo{};                              // the recorded step's geometry and state
     int G_hsolve = 16, hs_round = 12, hs_cap = 320;
     double hs_factor = 1.15;
