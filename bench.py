@@ -761,6 +761,7 @@ def main():
         tuned = at.load(prec, ppp)
         if tuned:
             at.apply(ctx, tuned)
+    der_wave = (tuned or {}).get("der_wave", -1)   # -1: the library's choice, 8 for a box this large
 
     for _ in range(args.warmup):
         out = pl.step(ctx, dev, prm, count_singular=False)
@@ -869,7 +870,7 @@ def main():
                    "lanes": tuned},
         "roofline": {"bound": "alu", "achieved": achieved_tf, "peak": VALU_PEAK_TFLOPS,
                      "unit": "TFLOP/s", "frac": achieved_tf / VALU_PEAK_TFLOPS,
-                     "traffic": deriv_traffic(args.precision, (tuned or {}).get("der_wave", 8)),
+                     "traffic": deriv_traffic(args.precision, der_wave if der_wave >= 0 else 8),
                      "traffic_unit": "bytes per launch", "algorithmic_bytes": bytes_alg,
                      "kernel": "k_deriv", "kernel_ms": deriv_ms,
                      "flops_per_pair": DERIV_FLOPS_PER_PAIR,

@@ -571,23 +571,26 @@ crk_status crk_export_neighbors(crk_ctx *ctx, int32_t which, int64_t *offsets, i
 
 /* Thread mapping of the volume, moment, velocity-gradient and derivative
  * (with the compatible-energy) passes: 4, 8, 16 or 32 particles per
- * wavefront (default 8 for the derivative pass, 0 for the others), whose
- * 64 lanes are split among them in proportion
+ * wavefront, whose 64 lanes are split among them in proportion
  * to their row lengths (each lane strides over its particle's row; the
  * lanes of a particle are summed in FP64 at the end, so the wavefront's
  * lanes stay busy however uneven the rows are); 0: the lanes-per-particle
  * mapping of crk_set_lanes (the compatible pass then keeps 8); -1 keeps the
- * current value. Tuning only: results agree to rounding for every choice. */
+ * current value. Until a value is given, the first three passes use 0 and the
+ * derivative pass 8, or 4 or 2 where particles are few or neighbours many (by
+ * n and n_h). Tuning only: results agree to rounding for every choice. */
 crk_status crk_set_wave_mapping(crk_ctx *ctx, int32_t vol_ppw, int32_t mom_ppw, int32_t grad_ppw,
                                 int32_t deriv_ppw);
 
 /* Lanes per particle of the four pair passes (volume, moments, velocity
  * gradient, derivatives): each particle's neighbour row is split over a
  * group of g lanes of one wavefront, g a power of two in 1..64; 0 keeps the
- * current value. The velocity gradient takes more lanes (up to 16) where rows
- * are long or particles few. Tuning only: results agree to rounding for every
- * g (the corrections of a particle with a near-singular m2 to that of its
- * moments, amplified). */
+ * current value. g_grad and g_der also hold for the rows that CRK_MIXED_ADAPT
+ * runs in FP64. Until a value is given: 4 for the volume, 1 for the moments, 4 to 16 for
+ * the gradient (more where particles are few or neighbours many, by n and n_h),
+ * 8 for the derivatives and 16 or 32 for the FP64 rows (by n). Tuning only:
+ * results agree to rounding for every g (the corrections of a particle with a
+ * near-singular m2 to that of its moments, amplified). */
 crk_status crk_set_lanes(crk_ctx *ctx, int32_t g_vol, int32_t g_mom, int32_t g_grad,
                          int32_t g_der);
 

@@ -24,19 +24,21 @@ from . import pipeline as pl
 HERE = os.path.dirname(os.path.abspath(__file__))
 TABLE = os.path.join(HERE, "tune_table.json")
 
-DEFAULT = {"walk": 8, "walk_level": 0, "vol": 4, "mom": 1, "grad": 4, "der": 8, "vol_wave": 0,
-           "mom_wave": 0, "grad_wave": 0, "der_wave": 8, "hsolve": 16}
+# grad and der 0, der_wave -1: left to the library, which goes by the number of
+# particles and n_h
+DEFAULT = {"walk": 8, "walk_level": 0, "vol": 4, "mom": 1, "grad": 0, "der": 0, "vol_wave": 0,
+           "mom_wave": 0, "grad_wave": 0, "der_wave": -1, "hsolve": 16}
 CANDIDATES = {
     "walk": (2, 4, 8, 16),
     "walk_level": (0, 1, 2),
     "vol": (1, 2, 4, 8, 16),
     "mom": (1, 2, 4, 8),
-    "grad": (2, 4, 8, 16),
-    "der": (4, 8, 16, 32),
+    "grad": (0, 2, 4, 8, 16),
+    "der": (0, 4, 8, 16, 32),
     "vol_wave": (0, 4, 8, 16),
     "mom_wave": (0, 4, 8, 16),
     "grad_wave": (0, 4, 8, 16),
-    "der_wave": (0, 4, 8, 16),
+    "der_wave": (-1, 0, 4, 8, 16),
     "hsolve": (4, 8, 16, 32),
 }
 KERNEL = {"walk": "k_walk", "walk_level": "k_walk", "vol": "k_volume", "mom": "k_moments", "grad": "k_gradv",
@@ -114,7 +116,9 @@ def _time_hsolve(ctx, dev, prm, nres: float, reps: int) -> float:
 
 def tune(ctx: Context, dev: dict, prm, nres: float = 64.0, start: dict | None = None,
          reps: int = 3, with_hsolve: bool = True, log=print, box_offsets=None) -> tuple[dict, dict]:
-    """Coordinate descent over the knobs; returns (best config, timings)."""
+    """Coordinate descent over the knobs, each candidate in a context of its own
+    (a mapping asked for cannot be handed back to the library); ctx gets the
+    best. Returns (best config, timings)."""
     cfg = dict(start or DEFAULT)
     timings = {}
     for knob, cands in CANDIDATES.items():
@@ -124,11 +128,13 @@ def tune(ctx: Context, dev: dict, prm, nres: float = 64.0, start: dict | None = 
         for g in cands:
             trial = dict(cfg)
             trial[knob] = g
-            apply(ctx, trial)
+            own = Context(ctx.device.index, ctx.stream)
+            apply(own, trial)
             if knob == "hsolve":
-                res[g] = _time_hsolve(ctx, dev, prm, nres, max(1, reps - 1))
+                res[g] = _time_hsolve(own, dev, prm, nres, max(1, reps - 1))
             else:
-                res[g] = _time_step(ctx, dev, prm, KERNEL[knob], reps, box_offsets)
+                res[g] = _time_step(own, dev, prm, KERNEL[knob], reps, box_offsets)
+            own.close()
         best = min(res, key=res.get)
         cfg[knob] = best
         timings[knob] = {str(k): v for k, v in res.items()}

@@ -1283,7 +1283,7 @@ static crk_status build_lists(crk_ctx *c, bool cleared) {
         // (128^3) 0.170 ms with 8 lanes and rows of 128, 0.203 with 16 and 256;
         // with 74 (45^3, 268 neighbours) 0.198 and 0.108. (In graph mode the last
         // eager build's: the order is the same for both.)
-        const double mean = c->graph_mode ? c->mean_pairs - c->mean_row : (double)E / (double)n;
+        const double mean = c->graph_mode ? c->mean_extras : (double)E / (double)n;
 #define L_RANK(GR, CAP) k_extra_rank<GR, CAP><<<(unsigned)((n * GR + kBlock - 1) / kBlock), kBlock, 0, c->stream>>>(eoff, etmp, n, eidx, (int32_t *)c->eb.p, (int32_t *)c->ee.p)
         if (mean > 32.0) L_RANK(16, 256);
         else L_RANK(8, 128);
@@ -1295,8 +1295,7 @@ static crk_status build_lists(crk_ctx *c, bool cleared) {
         c->ngather = c->nextra = c->npairs = -1;
     } else {
         c->ngather = G;
-        c->mean_row = (double)G / (double)n;
-        c->mean_pairs = (double)(G + E) / (double)n;
+        c->mean_extras = (double)E / (double)n;
         c->nextra = E;
         c->npairs = G + E;
         c->walk_cap_auto = walk_cap_next((double)G, (double)n, longest);

@@ -119,16 +119,18 @@ struct crk_ctx {
     int64_t last_nflag = 0, last_ntouch = 0;
     crk::Buf pinned;        // small host-pinned readback area
 
-    // per-pass tuning: lanes per particle (1..64)
-    int G_vol = 4, G_mom = 1, G_grad = 4, G_der = 8;
+    // per-pass tuning: lanes per particle (1..64; G_grad and G_der 0: not asked
+    // for, chosen by the pass)
+    int G_vol = 4, G_mom = 1, G_grad = 0, G_der = 0;
     // the last moment pass cleared the singular count of the next corrections
     int singular_clear = 0;
-    // mean gather row and mean pair row of the last eager build
-    double mean_row = 0.0, mean_pairs = 0.0;
+    // mean extras row of the last eager build
+    double mean_extras = 0.0;
     // volume, moment, velocity-gradient, derivative (and compatible)
     // passes: particles per wavefront of the balanced lane-group mapping
-    // (4, 8, 16 or 32); 0 = the G_* lanes per particle above
-    int P_vol = 0, P_mom = 0, P_grad = 0, P_der = 8;
+    // (4, 8, 16 or 32); 0 = the G_* lanes per particle above; P_der -1: not
+    // asked for, chosen by the pass
+    int P_vol = 0, P_mom = 0, P_grad = 0, P_der = -1;
     // neighbour walk: lanes per particle and scratch slots per row
     int G_walk = 8, walk_cap = 192;
     // scratch row slots the next walk uses at least: 2.5x the mean gather

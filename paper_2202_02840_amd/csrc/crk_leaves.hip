@@ -725,8 +725,6 @@ crk_status crk_build_leaves(crk_ctx *c, int32_t nboxes, const int64_t *box_offse
     }
     CRK_HIP(c, hipStreamSynchronize(c->stream));
     c->ngather = G;
-    c->mean_row = (double)G / (double)n;
-    c->mean_pairs = (double)(G + E) / (double)n;
     c->nextra = E;
     c->npairs = G + E;
     c->built = 1;

@@ -1888,40 +1888,46 @@ inline unsigned pblocks(int64_t n, int P) {
     return (unsigned)(((n + P - 1) / P + kBlock / 64 - 1) / (kBlock / 64));
 }
 
-// Lanes per row of the velocity gradient, from the lanes asked for up to 16: at
-// most 28 entries of a mean row a lane, and 4096 wavefronts, half of what the
-// device holds, so that the last ones end together (45^3 with 268 neighbours:
-// 0.302 ms with 4 lanes, 0.122 with 16). The gradient's sums take another order
-// at no more than their own rounding; the moments keep the lanes asked for, since
-// the corrections of a particle with a near-singular m2 amplify the last bit of
-// its sums without bound (the same order, the same corrections).
-int row_lanes(const crk_ctx *c, int G) {
-    while (G < 16 && (c->n * G < (int64_t)64 * 4096 || c->mean_row > 28.0 * G)) G *= 2;
+// ---- lane mappings that nobody asked for: from the number of particles and the
+// neighbours that n_h stands for, so that a step and its recorded form, which
+// share both, sum in the same order whatever the lists hold
+
+// neighbours within a support: the sphere of n_h mean separations
+double nominal_row(const crk_params *p) { return 4.0 / 3.0 * kPi * p->nh * p->nh * p->nh; }
+
+// Lanes per row of the velocity gradient, 4 to 16: at most 28 entries of a row a
+// lane, and 4096 wavefronts, half of what the device holds, so that the last
+// ones end together (45^3 with 268 neighbours: 0.302 ms with 4 lanes, 0.122 with
+// 16). (The moments keep to G_mom: the corrections of a particle with a
+// near-singular m2 amplify the last bit of its sums without bound.)
+int grad_lanes(const crk_ctx *c, const crk_params *p) {
+    if (c->G_grad > 0) return c->G_grad;
+    int G = 4;
+    while (G < 16 && (c->n * G < (int64_t)64 * 4096 || nominal_row(p) > 28.0 * G)) G *= 2;
     return G;
 }
 
 // Particles per wavefront of the derivative and compatible passes in balanced
-// groups, from P down to 2: fewer where there would be under 2048 wavefronts
-// (20^3: 0.022 ms with 8, 0.017 with 4; 12^3: 0.020 and 0.014), and 4 instead
-// of 8 where rows are long and the wavefronts few, so that the last ones end
-// together (45^3 with 268 neighbours: 0.246 and 0.222 ms; 40^3 with 64: 0.117
-// and 0.123).
-int deriv_particles(const crk_ctx *c, int P) {
+// groups, 8 down to 2: fewer where there would be under 2048 wavefronts (20^3:
+// 0.022 ms with 8, 0.017 with 4; 12^3: 0.020 and 0.014), and 4 instead of 8 where
+// rows are long and the wavefronts few, so that the last ones end together (45^3
+// with 268 neighbours: 0.246 and 0.222 ms; 40^3 with 64: 0.117 and 0.123).
+int deriv_particles(const crk_ctx *c, const crk_params *p) {
+    if (c->P_der >= 0) return c->P_der > 0 ? c->P_der : 8;
+    int P = 8;
     while (P > 2 && c->n < (int64_t)P * 2048) P /= 2;
-    if (P == 8 && c->n < (int64_t)P * 16384 && c->mean_pairs >= 160.0) P = 4;
+    if (P == 8 && c->n < (int64_t)P * 16384 && nominal_row(p) >= 128.0) P = 4;
     return P;
 }
 
 // lanes per listed row of the FP64 fixes: a list is short, so its rows are
 // spread wide (20^3: 0.024 ms with 8 lanes, 0.012 with 32; 128^3: 0.108, 0.105
 // with 16, 0.124 with 32)
-int fix_lanes(const crk_ctx *c, int G) {
-    const int least = c->n < (int64_t)1 << 18 ? 32 : 16;
-    return G > least ? G : least;
-}
+int fix_lanes(const crk_ctx *c, int asked) { return asked > 0 ? asked : c->n < (int64_t)1 << 18 ? 32 : 16; }
 
-// volume then (optionally) moment pass in type T, with the lane mapping of
-// the context (balanced groups of P particles per wave, or G lanes each)
+// lanes per particle of the derivative pass without balanced groups (0: with)
+int deriv_lanes(const crk_ctx *c) { return c->P_der != 0 ? 0 : c->G_der > 0 ? c->G_der : 8; }
+
 // n_i of the volumes the build summed (vnsum) and V_i = 1 / n_i into the
 // caller's arrays, V_i also beside the positions (where an FP32 volume pass may
 // have left its own)
@@ -2204,11 +2210,10 @@ crk_status crk_derivatives(crk_ctx *c, const crk_params *p, const double *v, con
     const DerivPrm dp = deriv_prm(p);
     CRK_TRY(ensure(c, c->misc, 256));
     int *bad = (int *)c->misc.p + 2;   // (cleared by the first packing)
-    // derivative pass: P_der particles a wave in balanced lane groups, or, at
-    // 0, groups of G_der lanes
-    const int Gg = row_lanes(c, c->G_grad), Gd = fix_lanes(c, c->G_der), Pg = c->P_grad;
-    const int Gf = c->P_der > 0 ? 0 : c->G_der;
-    const int Pd = c->P_der > 0 ? deriv_particles(c, c->P_der) : 64 / c->G_der;
+    // derivative pass: particles a wave in balanced lane groups, or groups of Gf lanes
+    const int Gg = grad_lanes(c, p), Pg = c->P_grad;
+    const int Ggf = fix_lanes(c, c->G_grad), Gd = fix_lanes(c, c->G_der);   // of the FP64 rows
+    const int Gf = deriv_lanes(c), Pd = Gf > 0 ? 64 / Gf : deriv_particles(c, p);
 
     // adaptive mode: FP64 rows for ill-conditioned RK templates, flagged by
     // the record packing (which reads the corrections anyway) after the FP32
@@ -2267,7 +2272,7 @@ crk_status crk_derivatives(crk_ctx *c, const crk_params *p, const double *v, con
         if (adapt && nflag > 0) {
 #define L_GV(GG) k_gradv<double, GG><<<fix_blocks(nflag, GG, gm), kBlock, 0, c->stream>>>(posH, goff, gidx, r6d, A, B, gA, gB, n, box, flist, nflag, nflag_dev, nullptr, gradv)
             KTimer kt_(c, "k_gradv_fix");
-            CRK_DISPATCH_G(Gd, L_GV);
+            CRK_DISPATCH_G(Ggf, L_GV);
 #undef L_GV
         }
         {
@@ -2392,7 +2397,7 @@ crk_status crk::compat_pass(crk_ctx *c, const crk_params *p, const double *v, co
     CRK_TRY(ensure(c, c->misc, 256));
     int *bad = (int *)c->misc.p + 2;
     CRK_TRY(zero_async(c, bad, 1));
-    const int Gd = fix_lanes(c, c->G_der), Pd = deriv_particles(c, c->P_der > 0 ? c->P_der : 8);
+    const int Gd = fix_lanes(c, c->G_der), Pd = deriv_particles(c, p);
     AdaptRows ar;
     // the records, FP64-row flags and lists of the derivative call just made
     // on this same state are reused when the caller says so (eager only)
