@@ -1281,7 +1281,8 @@ static crk_status build_lists(crk_ctx *c, bool cleared) {
         KTimer kt_(c, "k_extra_rank");
         // longer rows, more lanes and room for each: with 13 extras a particle
         // (128^3) 0.170 ms with 8 lanes and rows of 128, 0.203 with 16 and 256;
-        // with 74 (45^3, 268 neighbours) 0.198 and 0.108. (In graph mode the last
+        // with 23 (90^3, 96 neighbours) 0.114 both, with 32 0.180 and 0.169; with
+        // 75 (45^3, 268 neighbours) 0.204 and 0.111. (In graph mode the last
         // eager build's: the order is the same for both.)
         const double mean = c->graph_mode ? c->mean_extras : (double)E / (double)n;
 #define L_RANK(GR, CAP) k_extra_rank<GR, CAP><<<(unsigned)((n * GR + kBlock - 1) / kBlock), kBlock, 0, c->stream>>>(eoff, etmp, n, eidx, (int32_t *)c->eb.p, (int32_t *)c->ee.p)

@@ -1910,13 +1910,15 @@ int grad_lanes(const crk_ctx *c, const crk_params *p) {
 // Particles per wavefront of the derivative and compatible passes in balanced
 // groups, 8 down to 2: fewer where there would be under 2048 wavefronts (20^3:
 // 0.022 ms with 8, 0.017 with 4; 12^3: 0.020 and 0.014), and 4 instead of 8 where
-// rows are long and the wavefronts few, so that the last ones end together (45^3
-// with 268 neighbours: 0.246 and 0.222 ms; 40^3 with 64: 0.117 and 0.123).
+// rows are long and the wavefronts few, so that the last ones end together (8 and
+// 4, FP64 and FP32 rows, in us: 268 neighbours, 45^3 497 and 495, 244 and 220; 192,
+// 40^3 270 and 267, 134 and 121, 50^3 497 and 508, 229 and 219; but 160, 50^3 415
+// and 436, 191 and 190; 128, 50^3 339 and 367, 154 and 155).
 int deriv_particles(const crk_ctx *c, const crk_params *p) {
     if (c->P_der >= 0) return c->P_der > 0 ? c->P_der : 8;
     int P = 8;
     while (P > 2 && c->n < (int64_t)P * 2048) P /= 2;
-    if (P == 8 && c->n < (int64_t)P * 16384 && nominal_row(p) >= 128.0) P = 4;
+    if (P == 8 && c->n < (int64_t)P * 16384 && nominal_row(p) >= 180.0) P = 4;
     return P;
 }
 

@@ -61,3 +61,16 @@ def test_recorded_step_sums_like_an_eager_one():
     ctx.graph_replay()
     for k in ("perm", "V", "m2", "B", "gB", "gradv", "dpdt", "dudt"):
         assert torch.equal(io[k], ref[k]), k
+
+
+# particles a wavefront of the derivative pass: 8 from 2^14 particles on, 4 if their
+# rows are long
+@pytest.mark.parametrize("nres, wave", [(64.0, 8), (128.0, 8), (160.0, 8), (268.0, 4)])
+def test_own_choice_of_the_derivative_pass(nres, wave):
+    ps = ci.lognormal_box(26, sigma=1.0, seed=93, nngb=nres, hcap=0.45)
+    prm, dev = pl.params_for(ps, nres, CRK_FP64), pl.upload(ps)
+    own, asked = Context(0), Context(0)
+    asked.set_wave_mapping(deriv=wave)
+    a, b = pl.step(own, dev, prm, compat_dt=1e-3), pl.step(asked, dev, prm, compat_dt=1e-3)
+    for k in ("dpdt", "dudt", "du_compat"):
+        assert torch.equal(a[k], b[k]), k
