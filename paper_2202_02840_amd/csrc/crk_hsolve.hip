@@ -668,19 +668,23 @@ crk_status crk_hsolve(crk_ctx *c, double Nres, double tol, int32_t max_iter, dou
             // 530 and 42 us with 32 and 64 lanes and rows from memory, where a
             // support that has left its row walks the cells at every update, and
             // 136, 93 and 82 with 16)
-            const bool reg = rows && ((G == 8 && cap <= 8 * kRegSlots8) || (G == 16 && cap <= 16 * kRegSlots16));
+            const auto reg = [&](int g) {
+                return rows && ((g == 8 && cap <= 8 * kRegSlots8) || (g == 16 && cap <= 16 * kRegSlots16));
+            };
+            // (with fewer lanes asked for than register rows take, up to 16 and those:
+            // 40^3, four lanes, 3.26 ms with rows from memory, 2.56 with 8 and register
+            // rows, 1.54 with 16)
             int Gr = G;
-            while (!reg && Gr < 64 && mn * Gr < (int64_t)1 << 19) Gr *= 2;
+            while (!(reg(Gr) && (Gr == G || Gr == 16)) && Gr < 64 && mn * Gr < (int64_t)1 << 19) Gr *= 2;
             const int Rn = mn * G < (int64_t)1 << 19 ? 4 * c->hs_round : c->hs_round;
             // the wide pass runs longer rounds: its particles are few and slow
             const int Rw = 4 * c->hs_round;
             const int64_t mw0 = mw < prow ? mw : prow;   // wide particles in the first launch
             if (mw0 > 0) CRK_TRY(ensure(c, c->hs_pool, (size_t)mw0 * pcap * sizeof(double)));
             double *pool = (double *)c->hs_pool.p;
-            const bool reg8 = reg && G == 8, reg16 = reg && G == 16;
-            if (reg8)
+            if (reg(Gr) && Gr == 8)
                 CRK_TRY((hsolve_both<8, kRegSlots8>(c, a, la, mn, Rn, lw, mw0, Rw, pool, pcap)));
-            else if (reg16)
+            else if (reg(Gr))
                 CRK_TRY((hsolve_both<16, kRegSlots16>(c, a, la, mn, Rn, lw, mw0, Rw, pool, pcap)));
             else {
                 if (mn > 0) CRK_TRY(hsolve_round(c, a, Gr, la, mn, Rn, nullptr, 0, rows && Gr < 64));
