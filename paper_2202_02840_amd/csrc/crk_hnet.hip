@@ -351,10 +351,9 @@ __global__ __launch_bounds__(kBlock) void k_hnet_adam(const float *__restrict__ 
 // share the candidates and combine their five sums at the end, and each forms
 // one of the features (one logarithm a lane, where the first lane's six kept
 // the others waiting). When the
-// last build's gather rows are given and the H of a wavefront's particles are
-// the supports they were built with, the rows are the candidate sets (they
-// hold every j with r < H, self aside); otherwise a flattened walk of each
-// support. With the rows
+// last build's gather rows are given and a particle's H is the support they
+// were built with, its row is the candidate set (it holds every j with r < H,
+// self aside); otherwise a flattened walk of its support. With the rows
 // tiled through LDS and two partners loading ahead, 64^3 takes 133 us, 212
 // with the entries read one by one.
 template <int G>
@@ -387,7 +386,7 @@ __global__ __launch_bounds__(kBlock) void k_hnet_features(const double4 *__restr
         }
     };
     static_assert(G == 8, "a lane per feature");
-    // a wavefront's rows, or the tables of its walks: one or the other, so
+    // a wavefront's rows and the tables of its walks, one after the other, so
     // that five blocks fit a CU
     constexpr int NR = flat_ranges<G>(), NG = 64 / G;
     struct Walks {
@@ -400,7 +399,7 @@ __global__ __launch_bounds__(kBlock) void k_hnet_features(const double4 *__restr
         RowTile<G, 4> rows;
     } s_w[kBlock / 64];
     auto &sw = s_w[threadIdx.x >> 6];
-    if (!__any(!goff || h != pi.w)) {
+    if (goff && h == pi.w) {
         if (l == 0) add(0.0, 0.0);   // self
         const int64_t b = goff[i];
         const int cnt = (int)(goff[i + 1] - b);
