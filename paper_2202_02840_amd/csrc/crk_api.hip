@@ -302,7 +302,7 @@ crk_status crk_workspace_estimate(const crk_ctx *c, int64_t n, int32_t nboxes,
     if (uses & CRK_WS_TIMESTEP) t += 2 * held(8.0 * N);
     if (uses & CRK_WS_COMPAT) t += held(32.0 * N * (f64 ? 2 : 1)) + (adapt ? held(64.0 * N) : 0.0);
     if (uses & CRK_WS_HSOLVE) {
-        t += held(8.0 * N) + 2 * held(4.0 * N) + held(8.0 * (N / 1024.0 + 2.0)) + held(8.0 * N * hs_cap) +
+        t += held(8.0 * N) + 2 * held(4.0 * N) + held(8.0 * (N / 1024.0 + 3.0)) + held(8.0 * N * hs_cap) +
              held(4.0 * N) + held(8.0 * N);
         // rows of the particles whose candidates pass the cap: at most 8 GiB
         const double pcap = std::max(4096.0, 8.0 * hs_cap);

@@ -525,26 +525,30 @@ __global__ __launch_bounds__(kHsBlock) void k_hs_sums(const int32_t *__restrict_
         int64_t t = 0;
         for (int q = 0; q < kHsBlock / 64; q++) t += s[q];
         sums[blockIdx.x] = t;
+        if (blockIdx.x == gridDim.x - 1 && gridDim.x > kAddBlocks) sums[gridDim.x] = 0;
     }
 }
 
 // Those particles to out, the narrow ones first, in the order of the list;
-// every block adds up the counts before its own. host: both totals, then
+// every block adds up the counts before its own, or, with scanned, sums holds
+// their offsets and the total behind. host: both totals, then
 // stopped[0] and [1], for the host to read once the stream is done.
 __global__ __launch_bounds__(kHsBlock) void k_hs_compact(const int32_t *__restrict__ list, int64_t m,
                                                          const int32_t *__restrict__ state,
-                                                         const int64_t *__restrict__ sums, int32_t *out,
-                                                         const int32_t *__restrict__ stopped, int64_t *host) {
+                                                         const int64_t *__restrict__ sums, bool scanned,
+                                                         int32_t *out, const int32_t *__restrict__ stopped,
+                                                         int64_t *host) {
     constexpr int W = kHsBlock / 64;
     __shared__ int64_t s_all[W], s_before[W], s_here[W];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t k = (int64_t)blockIdx.x * kHsBlock + threadIdx.x;
     int64_t all = 0, before = 0;
-    for (int64_t b = threadIdx.x; b < gridDim.x; b += kHsBlock) {
-        const int64_t t = sums[b];
-        all += t;
-        if (b < blockIdx.x) before += t;
-    }
+    if (!scanned)
+        for (int64_t b = threadIdx.x; b < gridDim.x; b += kHsBlock) {
+            const int64_t t = sums[b];
+            all += t;
+            if (b < blockIdx.x) before += t;
+        }
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) {
         all += __shfl_xor(all, o, 64);
@@ -559,7 +563,7 @@ __global__ __launch_bounds__(kHsBlock) void k_hs_compact(const int32_t *__restri
         s_here[wave] = __popcll(mn) + ((int64_t)__popcll(mw) << 32);
     }
     __syncthreads();
-    int64_t total = 0, at = 0;
+    int64_t total = scanned ? sums[gridDim.x] : 0, at = scanned ? sums[blockIdx.x] : 0;
     for (int q = 0; q < W; q++) {
         total += s_all[q];
         at += s_before[q] + (q < wave ? s_here[q] : 0);
@@ -632,8 +636,9 @@ crk_status crk_hsolve(crk_ctx *c, double Nres, double tol, int32_t max_iter, dou
     Levels v = levels(c);
     CRK_TRY(ensure(c, c->hs_list, (size_t)2 * n * sizeof(int32_t)));
     CRK_TRY(ensure(c, c->hs_state, (size_t)n * sizeof(int32_t)));
-    // the blocks' counts of running particles, then the two counts of stopped ones
-    const int64_t nsums = (n + kHsBlock - 1) / kHsBlock;
+    // the blocks' counts of running particles (and one entry more), then the two
+    // counts of stopped ones
+    const int64_t nsums = (n + kHsBlock - 1) / kHsBlock + 1;
     CRK_TRY(ensure(c, c->hs_pos, (size_t)(nsums + 1) * sizeof(int64_t)));
     CRK_TRY(ensure(c, c->hs_iters, (size_t)n * sizeof(int32_t)));
     int32_t *la = (int32_t *)c->hs_list.p, *lb = la + n;
@@ -706,7 +711,9 @@ crk_status crk_hsolve(crk_ctx *c, double Nres, double tol, int32_t max_iter, dou
             const int64_t m = mn + mw;
             const unsigned mb = (unsigned)((m + kHsBlock - 1) / kHsBlock);
             k_hs_sums<<<mb, kHsBlock, 0, c->stream>>>(la, m, state, sums, stopped);
-            k_hs_compact<<<mb, kHsBlock, 0, c->stream>>>(la, m, state, sums, lb, stopped, pin);
+            const bool scanned = mb > kAddBlocks;
+            if (scanned) CRK_TRY(scan_exclusive_i64(c, sums, sums, (int64_t)mb + 1));
+            k_hs_compact<<<mb, kHsBlock, 0, c->stream>>>(la, m, state, sums, scanned, lb, stopped, pin);
             CRK_HIP(c, hipGetLastError());
             CRK_HIP(c, hipStreamSynchronize(c->stream));
             mn = pin[0] & 0xffffffff;

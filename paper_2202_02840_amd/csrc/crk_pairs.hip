@@ -1768,8 +1768,10 @@ __global__ __launch_bounds__(kBlock) void k_zero_marks(int32_t *a, int64_t n, in
 }
 
 // The marked rows in ascending order: counted for every kMarkBlock rows, then
-// listed, each block adding up the counts before its own. *total: how many.
-// host (pinned): that and the flagged rows' count, read once the stream is done.
+// listed, each block adding up the counts before its own, or, with scanned, from
+// their offsets (then sums holds one entry more: see kAddBlocks). *total: how
+// many. host (pinned): that and the flagged rows' count, read once the stream is
+// done.
 constexpr int kMarkBlock = 1024;
 __global__ __launch_bounds__(kMarkBlock) void k_mark_sums(const int32_t *__restrict__ mark, int64_t n, int64_t *sums) {
     __shared__ int s[kMarkBlock / 64];
@@ -1781,18 +1783,21 @@ __global__ __launch_bounds__(kMarkBlock) void k_mark_sums(const int32_t *__restr
         int t = 0;
         for (int q = 0; q < kMarkBlock / 64; q++) t += s[q];
         sums[blockIdx.x] = t;
+        if (blockIdx.x == gridDim.x - 1 && gridDim.x > kAddBlocks) sums[gridDim.x] = 0;
     }
 }
 __global__ __launch_bounds__(kMarkBlock) void k_mark_list(const int32_t *__restrict__ mark, int64_t n,
-                                                          const int64_t *__restrict__ sums, int32_t *list,
-                                                          int64_t *total, const int64_t *nflag, int64_t *host) {
+                                                          const int64_t *__restrict__ sums, bool scanned,
+                                                          int32_t *list, int64_t *total, const int64_t *nflag,
+                                                          int64_t *host) {
     constexpr int W = kMarkBlock / 64;
     __shared__ int64_t s_before[W];
     __shared__ int s_here[W];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t i = (int64_t)blockIdx.x * kMarkBlock + threadIdx.x;
     int64_t before = 0;
-    for (int64_t b = threadIdx.x; b < blockIdx.x; b += kMarkBlock) before += sums[b];
+    if (!scanned)
+        for (int64_t b = threadIdx.x; b < blockIdx.x; b += kMarkBlock) before += sums[b];
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) before += __shfl_xor(before, o, 64);
     const uint64_t m = __ballot(i < n && mark[i]);
@@ -1801,7 +1806,7 @@ __global__ __launch_bounds__(kMarkBlock) void k_mark_list(const int32_t *__restr
         s_here[wave] = __popcll(m);
     }
     __syncthreads();
-    int64_t at = 0, end = 0;
+    int64_t at = scanned ? sums[blockIdx.x] : 0, end = at;
     for (int q = 0; q < W; q++) {
         at += s_before[q] + (q < wave ? s_here[q] : 0);
         end += s_before[q] + s_here[q];
@@ -2144,7 +2149,10 @@ static crk_status adapt_finish(crk_ctx *c, bool gm, AdaptRows &r) {
         // (tpos: the blocks' counts, and at n the total)
         const unsigned mb = (unsigned)((n + kMarkBlock - 1) / kMarkBlock);
         k_mark_sums<<<mb, kMarkBlock, 0, c->stream>>>(mark, n, tpos);
-        k_mark_list<<<mb, kMarkBlock, 0, c->stream>>>(mark, n, tpos, r.tlist, tpos + n, fpos + n, gm ? nullptr : pin);
+        const bool scanned = mb > kAddBlocks;
+        if (scanned) CRK_TRY(scan_exclusive_i64(c, tpos, tpos, (int64_t)mb + 1));
+        k_mark_list<<<mb, kMarkBlock, 0, c->stream>>>(mark, n, tpos, scanned, r.tlist, tpos + n, fpos + n,
+                                                      gm ? nullptr : pin);
     }
     CRK_HIP(c, hipGetLastError());
     if (gm) {
