@@ -443,12 +443,20 @@ __device__ __forceinline__ void wide_body(const HsArgs &a, const int32_t *__rest
     double *row = pool + (size_t)k * pcap;
     double Rmax;
     const int c = make_row<64>(a, i, pi, H, pcap, row, Rmax, l, &fl);
-    double rr[S];
-    const int most = load_row<64>(row, c, Rmax, l, rr);
-    int st = thacker_updates(a, H, it, R, Rmax, false, [&](double h) {
-        if (c > pcap || !(h <= Rmax)) return nsum_group<64>(a.posH, a.cbeg, a.cend, a.v, i, pi, h, l);
-        return c <= 64 * S ? count_row<64>(rr, most, h) : nsum_row<64>(row, c, h, l);
-    });
+    int st = 0;
+    const int end = it + R;
+    if (c <= 64 * S) {
+        double rr[S];
+        const int most = load_row<64>(row, c, Rmax, l, rr);
+        st = thacker_updates(a, H, it, R, Rmax, true, [&](double h) { return count_row<64>(rr, most, h); });
+    }
+    // a longer row, or the updates left once H is outside (apart from those
+    // above: with the registers of both, a SIMD held a wavefront less)
+    if (st == 0 && it < end)
+        st = thacker_updates(a, H, it, end - it, Rmax, false, [&](double h) {
+            return c > pcap || !(h <= Rmax) ? nsum_group<64>(a.posH, a.cbeg, a.cend, a.v, i, pi, h, l)
+                                            : nsum_row<64>(row, c, h, l);
+        });
     if (st == 0 && c > a.cap) st = 4;   // (a row that fits goes back to the narrow pass)
     if (l == 0) {
         a.H[i] = H;
