@@ -840,7 +840,7 @@ __global__ __launch_bounds__(kBlock) void k_walk_long(const double4 *__restrict_
 // dependent stores, so the atomics' round trips overlap instead of
 // following one another.
 //
-// With vnsum, each row's FP64 volume sum of eq. (vol) comes along: W(r_ij, H_i)
+// With VOL, each row's FP64 volume sum of eq. (vol) comes along: W(r_ij, H_i)
 // over the self pair and every gather entry, the terms of the volume pass
 // (same separations, square root and weight), summed in the order k = l,
 // l + G, ... of each lane; n_i goes to vnsum[i] and (x_i, V_i = 1 / n_i) to
@@ -852,8 +852,10 @@ __global__ __launch_bounds__(kBlock) void k_walk_long(const double4 *__restrict_
 // atomics are on their way; with the row read again for the volumes once the
 // scatter was done, and eight entries at a time, 128^3 took 1.235 ms, three
 // entries (68 VGPRs, seven wavefronts a SIMD) 1.056; two 1.043, but 268
-// neighbours 0.229 ms against 0.212 (0.25 before).
-template <int G, int U>
+// neighbours 0.229 ms against 0.212 (0.25 before). Without volumes eight entries
+// (128^3 0.91 ms with three, 0.88; lattice 100^3 with 128 neighbours 0.284 and
+// 0.245).
+template <int G, int U, bool VOL>
 __global__ __launch_bounds__(kBlock) void k_compact_rows(const uint32_t *__restrict__ scratch, int cap,
                                                          int64_t n, const int32_t *__restrict__ ng,
                                                          const int64_t *__restrict__ goff, int32_t *gidx,
@@ -873,7 +875,7 @@ __global__ __launch_bounds__(kBlock) void k_compact_rows(const uint32_t *__restr
     const uint32_t *row = scratch + (size_t)i * cap;
     const int64_t gw = goff[i];
     double4 pi = make_double4(0.0, 0.0, 0.0, 1.0);
-    if (vnsum) pi = posH[i];
+    if (VOL) pi = posH[i];
     const double invH = 1.0 / pi.w;
     const double cw = kW * invH * invH * invH;
     double sum = l == 0 ? cw : 0.0;   // the self pair: W(0, H_i)
@@ -883,7 +885,7 @@ __global__ __launch_bounds__(kBlock) void k_compact_rows(const uint32_t *__restr
         for (int u = 0; u < U; u++) w[u] = k0 + u * G < cnt ? row[k0 + u * G] : 0u;
         // the partners' positions are on their way before the stores and atomics
         double4 pj[U];
-        if (vnsum)
+        if (VOL)
 #pragma unroll
             for (int u = 0; u < U; u++) pj[u] = posH[k0 + u * G < cnt ? w[u] & 0x7fffffffu : (uint32_t)i];
         // the returned places are used only after every atomic is issued
@@ -898,7 +900,7 @@ __global__ __launch_bounds__(kBlock) void k_compact_rows(const uint32_t *__restr
                 if (w[u] & 0x80000000u) at[u] = atomicAdd(&efill[(int32_t)(w[u] & 0x7fffffffu)], 1);
             }
         }
-        if (vnsum)
+        if (VOL)
 #pragma unroll
             for (int u = 0; u < U; u++) {
                 if (k0 + u * G >= cnt) break;
@@ -911,7 +913,7 @@ __global__ __launch_bounds__(kBlock) void k_compact_rows(const uint32_t *__restr
         for (int u = 0; u < U; u++)
             if (at[u] >= 0) etmp[at[u]] = (int32_t)i;
     }
-    if (vnsum) {
+    if (VOL) {
 #pragma unroll
         for (int m = G / 2; m >= 1; m >>= 1) sum += __shfl_xor(sum, m, G);
         if (l == 0) {
@@ -1254,11 +1256,13 @@ static crk_status build_lists(crk_ctx *c, bool cleared) {
     const Box box{c->L, 1.0 / c->L};
     // (the long rows' volumes take the same lanes per row, so a row's sum
     // does not depend on which of the two kernels forms it)
-    constexpr int GC = 16, UC = 3;
+    constexpr int GC = 16;
     {
         KTimer kt_(c, "k_compact_rows");
-        k_compact_rows<GC, UC><<<(unsigned)((n * GC + kBlock - 1) / kBlock), kBlock, 0, c->stream>>>(
-            scratch, cap, n, ng, goff, (int32_t *)c->gidx.p, efill, etmp, longs, posH, box, vnsum, posV);
+#define L_COMPACT(U, VOL) k_compact_rows<GC, U, VOL><<<(unsigned)((n * GC + kBlock - 1) / kBlock), kBlock, 0, c->stream>>>(scratch, cap, n, ng, goff, (int32_t *)c->gidx.p, efill, etmp, longs, posH, box, vnsum, posV)
+        if (vol) L_COMPACT(3, true);
+        else L_COMPACT(8, false);
+#undef L_COMPACT
     }
     if (longest > cap) {
         // the rows over the cap are few and long: 32 lanes each (the row is
