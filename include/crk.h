@@ -588,7 +588,7 @@ crk_status crk_set_wave_mapping(crk_ctx *ctx, int32_t vol_ppw, int32_t mom_ppw, 
  * current value. g_grad and g_der also hold for the rows that CRK_MIXED_ADAPT
  * runs in FP64. Until a value is given: 4 for the volume, 1 for the moments, 4 to 16 for
  * the gradient (more where particles are few or neighbours many, by n and n_h),
- * 8 for the derivatives and 16 or 32 for the FP64 rows (by n). Tuning only:
+ * 8 for the derivatives and 8 to 32 for the FP64 rows (likewise). Tuning only:
  * results agree to rounding for every g (the corrections of a particle with a
  * near-singular m2 to that of its moments, amplified). */
 crk_status crk_set_lanes(crk_ctx *ctx, int32_t g_vol, int32_t g_mom, int32_t g_grad,

@@ -1927,10 +1927,16 @@ int deriv_particles(const crk_ctx *c, const crk_params *p) {
     return P;
 }
 
-// lanes per listed row of the FP64 fixes: a list is short, so its rows are
-// spread wide (20^3: 0.024 ms with 8 lanes, 0.012 with 32; 128^3: 0.108, 0.105
-// with 16, 0.124 with 32)
-int fix_lanes(const crk_ctx *c, int asked) { return asked > 0 ? asked : c->n < (int64_t)1 << 18 ? 32 : 16; }
+// Lanes per listed row of the FP64 fixes. A list is short, so its rows are spread
+// wide (20^3: 0.024 ms with 8 lanes, 0.012 with 32; 128^3: 0.108, 0.105 with 16,
+// 0.124 with 32), but with few neighbours it is long and its rows are short (24
+// neighbours, a quarter to a half of the rows: 45^3 0.054 with 8 lanes, 0.061 with
+// 16, 0.083 with 32, 90^3 0.41, 0.50, 0.73; 23^3 0.019, 0.017, 0.021).
+int fix_lanes(const crk_ctx *c, const crk_params *p, int asked) {
+    if (asked > 0) return asked;
+    if (nominal_row(p) < 56.0) return c->n < (int64_t)1 << 16 ? 16 : 8;
+    return c->n < (int64_t)1 << 18 ? 32 : 16;
+}
 
 // lanes per particle of the derivative pass without balanced groups (0: with)
 int deriv_lanes(const crk_ctx *c) { return c->P_der != 0 ? 0 : c->G_der > 0 ? c->G_der : 8; }
@@ -2222,7 +2228,7 @@ crk_status crk_derivatives(crk_ctx *c, const crk_params *p, const double *v, con
     int *bad = (int *)c->misc.p + 2;   // (cleared by the first packing)
     // derivative pass: particles a wave in balanced lane groups, or groups of Gf lanes
     const int Gg = grad_lanes(c, p), Pg = c->P_grad;
-    const int Ggf = fix_lanes(c, c->G_grad), Gd = fix_lanes(c, c->G_der);   // of the FP64 rows
+    const int Ggf = fix_lanes(c, p, c->G_grad), Gd = fix_lanes(c, p, c->G_der);   // of the FP64 rows
     const int Gf = deriv_lanes(c), Pd = Gf > 0 ? 64 / Gf : deriv_particles(c, p);
 
     // adaptive mode: FP64 rows for ill-conditioned RK templates, flagged by
@@ -2407,7 +2413,7 @@ crk_status crk::compat_pass(crk_ctx *c, const crk_params *p, const double *v, co
     CRK_TRY(ensure(c, c->misc, 256));
     int *bad = (int *)c->misc.p + 2;
     CRK_TRY(zero_async(c, bad, 1));
-    const int Gd = fix_lanes(c, c->G_der), Pd = deriv_particles(c, p);
+    const int Gd = fix_lanes(c, p, c->G_der), Pd = deriv_particles(c, p);
     AdaptRows ar;
     // the records, FP64-row flags and lists of the derivative call just made
     // on this same state are reused when the caller says so (eager only)

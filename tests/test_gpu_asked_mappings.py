@@ -74,3 +74,15 @@ def test_own_choice_of_the_derivative_pass(nres, wave):
     a, b = pl.step(own, dev, prm, compat_dt=1e-3), pl.step(asked, dev, prm, compat_dt=1e-3)
     for k in ("dpdt", "dudt", "du_compat"):
         assert torch.equal(a[k], b[k]), k
+
+
+# lanes of the FP64 rows: by n and the neighbours
+@pytest.mark.parametrize("side, nres, lanes", [(10, 64.0, 32), (10, 24.0, 16), (41, 24.0, 8), (64, 64.0, 16)])
+def test_own_choice_of_the_fp64_rows(side, nres, lanes):
+    ps = ci.lognormal_box(side, sigma=1.0, seed=94, nngb=nres, hcap=0.45)
+    prm, dev = pl.params_for(ps, nres, CRK_MIXED_ADAPT, kappa_max=0.0), pl.upload(ps)
+    own, asked = Context(0), Context(0)
+    asked.set_lanes(der=lanes)
+    a, b = pl.step(own, dev, prm, compat_dt=1e-3), pl.step(asked, dev, prm, compat_dt=1e-3)
+    for k in ("dpdt", "dudt", "du_compat"):
+        assert torch.equal(a[k], b[k]), k
