@@ -1942,8 +1942,8 @@ int fix_lanes(const crk_ctx *c, const crk_params *p, int asked) {
 int deriv_lanes(const crk_ctx *c) { return c->P_der != 0 ? 0 : c->G_der > 0 ? c->G_der : 8; }
 
 // n_i of the volumes the build summed (vnsum) and V_i = 1 / n_i into the
-// caller's arrays, V_i also beside the positions (where an FP32 volume pass may
-// have left its own)
+// caller's arrays, with posV V_i also beside the positions (where another volume
+// pass has left its own)
 __global__ __launch_bounds__(kBlock) void k_volume_out(int64_t n, const double *__restrict__ vnsum, double4 *posV,
                                                        double *nsum, double *V) {
     const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
@@ -1951,7 +1951,7 @@ __global__ __launch_bounds__(kBlock) void k_volume_out(int64_t n, const double *
     const double ns = vnsum[i], Vi = 1.0 / ns;
     if (nsum) nsum[i] = ns;
     V[i] = Vi;
-    posV[i].w = Vi;
+    if (posV) posV[i].w = Vi;
 }
 
 template <typename T>
@@ -1969,8 +1969,9 @@ crk_status volume_moments(crk_ctx *c, const double4 *posH, const int64_t *goff, 
         ex.nsum = nsum;
     } else if (sizeof(T) == 8 && c->vol_ready) {
         KTimer kt_(c, "k_volume");
+        k_volume_out<<<nblocks(n), kBlock, 0, c->stream>>>(n, (const double *)c->vnsum.p,
+                                                           c->vol_posV ? nullptr : posV, nsum, V);
         c->vol_posV = 1;
-        k_volume_out<<<nblocks(n), kBlock, 0, c->stream>>>(n, (const double *)c->vnsum.p, posV, nsum, V);
     } else {
         KTimer kt_(c, "k_volume");
         c->vol_posV = 0;
