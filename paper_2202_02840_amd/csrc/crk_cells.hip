@@ -381,8 +381,8 @@ __device__ __forceinline__ void walk_row_flat(const double4 *__restrict__ posH, 
 //
 // Consecutive particles of the sort lie next to one another, so the cells
 // about one of them are mostly the cells about all of them. The wavefront
-// takes its particles in runs (see walk_run) and lists the cells about the
-// whole run once, 64 cells a step; the concatenated candidates of those cells
+// takes its particles in runs (one box, one level, a small block of cells) and
+// lists the cells about the whole run once, 64 cells a step; the concatenated candidates of those cells
 // then go 64 at a time, one per lane, past every particle of the run, whose
 // position and squared support sit in scalar registers. A candidate is loaded
 // and located once for P tests, and a test is the separation, r^2, two
@@ -393,9 +393,9 @@ __device__ __forceinline__ void walk_row_flat(const double4 *__restrict__ posH, 
 // the cells that only other particles of the run need hold no hit of this one:
 // every row is the list a walk of its own gives, entry for entry.
 //
-// Bound: vector instruction issue (about three quarters of the time), then the
-// latency of a batch; eight wavefronts per SIMD hide it, hence the register
-// bound. A lognormal box of 128^3 (67 gather partners a particle): a group of
+// Bound: vector instruction issue (0.87 instructions a CU and cycle; a loop of
+// fused multiply-adds reaches 0.97), then the latency of a batch; seven or eight
+// wavefronts per SIMD hide it, hence the register bound. A lognormal box of 128^3 (67 gather partners a particle): a group of
 // lanes per particle tested 218 candidates each for 400 vector instructions a
 // particle and 1.67 ms; here 370 candidates a particle pass for 255, 1.21 ms
 // (64^3: 0.355 to 0.18 ms). Of that, listing only cells in reach of some
@@ -1162,8 +1162,8 @@ Levels levels(const crk_ctx *c) {
 }
 
 // Particles per wavefront of the walk. More of them share a listed cell and a
-// loaded candidate, fewer leave more wavefronts: the device holds 8192 at
-// eight per SIMD, and a wavefront of four particles is worth its half as many
+// loaded candidate, fewer leave more wavefronts: the device holds 8192 (7168 of
+// eight particles), and a wavefront of four particles is worth its half as many
 // once it fills that (32^3: 28 us with four, 32 with two and 37 with one;
 // 20^3: 57, 45 and 40), one of eight once there are 16 rounds of them, so that
 // the last round is a small part (128^3: 1.21 ms with eight, 1.25 with four;

@@ -354,7 +354,7 @@ __global__ __launch_bounds__(kBlock) void k_hnet_adam(const float *__restrict__ 
 // last build's gather rows are given and a particle's H is the support they
 // were built with, its row is the candidate set (it holds every j with r < H,
 // self aside); otherwise a flattened walk of its support. With the rows
-// tiled through LDS and two partners loading ahead, 64^3 takes 133 us, 212
+// tiled through LDS and two partners loading ahead, 64^3 takes 106 us, 212
 // with the entries read one by one.
 template <int G>
 __global__ __launch_bounds__(kBlock) void k_hnet_features(const double4 *__restrict__ posH,

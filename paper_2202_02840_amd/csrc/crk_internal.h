@@ -16,7 +16,8 @@
 //                           (eoff [n+1] int64 holds the same row offsets)
 //   recV   T       [n]      volumes in the pass precision
 //   rec6   T4      [n]      {vx, vy, vz, V}            (velocity-gradient pass)
-//   rec7   T4      [8][n]   packed per-particle records (derivative pass)
+//   rec7   T4      [n][8]   packed per-particle records (derivative and compatible
+//                           passes); FP32: behind them [n] positions in fixed point
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -131,12 +132,13 @@ struct crk_ctx {
     // (4, 8, 16 or 32); 0 = the G_* lanes per particle above; P_der -1: not
     // asked for, chosen by the pass
     int P_vol = 0, P_mom = 0, P_grad = 0, P_der = -1;
-    // neighbour walk: lanes per particle and scratch slots per row
+    // neighbour walk: at most 64 / G_walk particles a wavefront (and 8), and
+    // scratch slots per row
     int G_walk = 8, walk_cap = 192;
-    // scratch row slots the next walk uses at least: 2.5x the mean gather
-    // row of the last eager build (a multiple of 64, at most 1024), so that
-    // rows past the cap, walked twice, stay rare when supports hold many
-    // more neighbours than the default cap
+    // scratch row slots the next walk uses at least (walk_cap_next): from the
+    // mean and the longest gather row of the last eager build, a multiple of
+    // 64, so that rows past the cap, walked twice, stay rare when supports hold
+    // many more neighbours than the default cap
     int walk_cap_auto = 0;
     // walked level: the first whose cell side is at least 2^(walk_shift-1) H
     int walk_shift = 0;

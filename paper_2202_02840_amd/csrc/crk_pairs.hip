@@ -165,8 +165,8 @@ __device__ __forceinline__ int64_t group_index(int G, int &lane) {
 //
 // Derivative pass, 128^3 lognormal, 1.70e8 pairs: 1.69 ms with a load of its
 // own for each piece (L1 accesses 1.67e9), 1.375 ms here (6.4e8), now bound by
-// vector instruction issue (about 90% of the time); in FP64 at 64^3 0.452 to
-// 0.399 ms; 268 neighbours at 45^3 0.335 to 0.245 ms. The compatible pass of
+// vector instruction issue (0.89 instructions a CU and cycle; a loop of fused
+// multiply-adds reaches 0.97); in FP64 at 64^3 0.452 to 0.399 ms; 268 neighbours at 45^3 0.335 to 0.245 ms. The compatible pass of
 // two kicks, 50^3 lattice: 0.110 to 0.092 ms (three wavefronts a SIMD: a
 // register bound for four spills, and a spill's reload waits for every record
 // on its way: 0.170 ms).
@@ -285,9 +285,9 @@ __global__ __launch_bounds__(kBlock) void k_volume(const double4 *__restrict__ p
 // in their indices (6 and 10 distinct sums), since d/dx_i (d_a W) = delta W +
 // d_a grad W. Same sums as the term-by-term form, grouped differently.
 // Bound by FP64 vector instructions (76 a pair) where the loads keep up:
-// 128^3, four lanes a row, 0.92 ms with the index rows read in the loop, 0.84
-// with them tiled through LDS and two records ahead; 64^3, one lane a row, 0.41
-// and 0.22 ms. Four wavefronts a SIMD: five would spill the 29 sums. The FP32
+// 128^3, four lanes a row, 0.92 ms with the index rows read in the loop, 0.82
+// with them tiled through LDS and two records ahead; 64^3, one lane a row, 0.34
+// and 0.19 ms. Four wavefronts a SIMD: five would spill the 29 sums. The FP32
 // sums, compensated, take three (32^3 lattice, one lane a row: 0.057 ms with four
 // and one record ahead, 0.048 so; 64^3 0.123 and 0.128, 100^3 0.494 and 0.474).
 // index of the symmetric pair (a, b) among (0,0),(0,1),(0,2),(1,1),(1,2),(2,2),
@@ -500,7 +500,7 @@ __device__ __forceinline__ void rk_grad(const Coef<T> &k, const T d[3], T w, T g
 // i = list[g] when a list is given (the FP64 rows of the adaptive mode),
 // else i = g; rows with skip[i] set are left to another launch. Index rows as
 // in the moment pass: 128^3 FP32 rows 0.74 ms with 8 lanes a row and the
-// indices read in the loop, 0.62 with 4 lanes and tiles (0.71 with 8).
+// indices read in the loop, 0.60 with 4 lanes and tiles (a fifth more with 8).
 template <typename T, int G>
 __global__ __launch_bounds__(kBlock) void k_gradv(const double4 *__restrict__ posH,
                                                   const int64_t *__restrict__ goff,
@@ -2108,9 +2108,9 @@ crk_status crk_corrections(crk_ctx *c, int64_t n, const double *m0, const double
 }
 
 // FP64 rows of the adaptive mode: flags the particles whose RK template is
-// ill-conditioned (flist) and lists every particle with a flagged pair side
-// (tlist), each list in no particular order. In graph mode the counts stay
-// on the device.
+// ill-conditioned (flist, in no particular order) and lists every particle with a
+// flagged pair side (tlist, ascending). In graph mode the counts stay on the
+// device.
 struct AdaptRows {
     int32_t *flag = nullptr, *flist = nullptr, *tlist = nullptr;
     int64_t nflag = 0, ntouch = 0;
@@ -2118,9 +2118,9 @@ struct AdaptRows {
 };
 
 // fpos[n] counts the flagged rows (appended in any order: their fix is per
-// row), the int32 words below it mark the touched rows, whose offsets tpos
-// list them in ascending order (rows of neighbouring particles side by side
-// share their partners' loads in the fix). First the buffers and (clear) the
+// row), the int32 words below it mark the touched rows, and tlist lists them in
+// ascending order (rows of neighbouring particles side by side share their
+// partners' loads in the fix; tpos: the blocks' counts, at n the total). First the buffers and (clear) the
 // cleared marks and counter; the flagging follows (k_flag, or the record packing of
 // the derivative call), then adapt_finish.
 static crk_status adapt_prep(crk_ctx *c, AdaptRows &r, bool clear) {
